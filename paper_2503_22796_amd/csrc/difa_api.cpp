@@ -58,9 +58,10 @@ struct TimingPair {
 struct difa_plan {
     difa_plan_desc_t desc;
     float scale;
-    int32_t bm, bn;
+    int32_t bm, bn;                // query rows per work record, keys per tile
+    int32_t band_rows;             // query rows per block of the block-granular band
     int32_t item_capacity;
-    int32_t n_wg, n_xcd;           // persistent workgroups (one per compute unit), accelerator dies
+    int32_t n_wg, n_xcd;           // persistent workgroups (wgs_per_cu on every compute unit), accelerator dies
     size_t buf_bytes, heads_bytes; // schedule buffer: cached-head list, then the schedule
     float* part_o = nullptr;       // device scratch for records cut into pieces: 2 * n_wg slots
     float* part_ml = nullptr;
@@ -342,7 +343,9 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     p->desc = *desc;
     for (double& sp : p->die_speed) sp = 1.0;
     p->scale = desc->softmax_scale > 0.f ? desc->softmax_scale : 1.0f / sqrtf((float)desc->head_dim);
-    difa_tile_shape(desc->head_dim, desc->dtype, &p->bm, &p->bn);
+    difa_tile_shape(desc->head_dim, desc->dtype, &p->band_rows, &p->bn);
+    const bool bf16 = desc->dtype == DIFA_DTYPE_BF16;
+    p->bm = bf16 ? difa::rows_per_wg(desc->head_dim) : p->band_rows;
     const int64_t q_tiles = ((int64_t)desc->max_tokens + p->bm - 1) / p->bm;
     const int64_t cap = (int64_t)desc->batch * desc->heads * q_tiles;
     if (cap > (int64_t)1 << 24) {
@@ -350,7 +353,7 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
         return fail(nullptr, DIFA_ERR_UNSUPPORTED, "batch*heads*query tiles exceeds the work-list limit");
     }
     p->item_capacity = (int32_t)cap;
-    p->n_wg = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
+    p->n_wg = (prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1) * (bf16 ? difa::wgs_per_cu(desc->head_dim) : 1);
     p->n_xcd = p->n_wg % kXcd == 0 ? kXcd : 1;
     p->heads_bytes = ((size_t)desc->heads * sizeof(int32_t) + 63) / 64 * 64;
     // worst case: every record whole plus two pieces per workgroup, one merge entry per workgroup
@@ -622,7 +625,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         lru->valid = false;
         int32_t n_items = 0, n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
         char* hb = (char*)stg.h_buf;
-        difa_status_t st = difa_worklist_build(B, H, head_plan, window, n_text, n_img, p->bm, p->bn, 1, p->desc.flags,
+        difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, p->bm, p->band_rows, p->bn, p->desc.flags,
                                                p->recs.data(), p->item_capacity, &n_items, (int32_t*)hb, &n_copy);
         if (st != DIFA_OK) return fail(p, st, "work-list compilation failed");
         size_t used = p->heads_bytes;
@@ -633,7 +636,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             const int32_t seg_cap = n_items + 2 * p->n_wg;
             lru->merges_off = (lru->segs_off + (size_t)seg_cap * sizeof(difa_segment_t) + 63) / 64 * 64;
             const bool dies = p->h_times != nullptr;
-            st = difa::schedule_for_dies(p->recs.data(), n_items, p->n_wg, p->n_xcd, dies && lru->version == 1 ? p->die_speed : nullptr,
+            st = difa::schedule_for_dies(difa::kGenericCosts, p->recs.data(), n_items, p->n_wg, p->n_xcd, dies && lru->version == 1 ? p->die_speed : nullptr,
                                          dies ? lru->die_span : nullptr, (difa_segment_t*)(hb + lru->segs_off),
                                          seg_cap, (int32_t*)(hb + lru->wg_off), &n_segs,
                                          (difa_merge_item_t*)(hb + lru->merges_off), 2 * p->n_wg, &n_merges, &n_slots);
@@ -746,7 +749,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
                 a.n_copy = slot->n_copy;
                 a.copy_vec_shift = shift;
                 a.copy_head_vecs = N << shift;
-                a.copy_chunks_per_head = (a.copy_head_vecs + difa::kCopyVecs - 1) / difa::kCopyVecs;
+                a.copy_chunks_per_head = (a.copy_head_vecs + difa::copy_chunk_vecs(D) - 1) / difa::copy_chunk_vecs(D);
                 const int64_t chunks = (int64_t)B * slot->n_copy * a.copy_chunks_per_head;
                 if (chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
                 a.copy_chunks = (int32_t)chunks;

@@ -7,9 +7,19 @@
 
 namespace difa {
 
-constexpr int kBM = 256;  // query rows per workgroup (8 wavefronts x 32 rows)
+constexpr int kBM = 256;  // query rows per block of the block-granular band, and per work record of the fp32 path
 constexpr int kBN = 64;   // keys per K/V tile
-constexpr int kCopyVecs = 8192;  // 16-byte vectors per chunk of the cached-head copy (128 KiB)
+// bf16 kernel: query rows per work record and workgroup (32 per wavefront), and how many such workgroups a compute unit
+// holds.  Either way a SIMD has two wavefronts.  At head_dim 128 they belong to one workgroup, whose K/V rings fill the
+// LDS.  At head_dim 64 the rings are half the size and the softmax's share of an iteration twice as large, so what counts
+// is that a wavefront has another one to hide its barriers, masks and segment ends behind: two workgroups of four
+// wavefronts that know nothing of each other.  Clocks per 256 rows x 64 keys on MI355X, one workgroup of eight against two
+// of four: 2190-2360 against 2050 in the loop; the SD3-like 512 px layers 1.13 times as fast, the 1K layer up to 1.05; at 2K
+// (where the clock gives way as the loop gets denser) the same.  64 rows per wavefront as well: 2010 clocks, 2K the same,
+// 1K 0.75 times as fast (records twice as long).
+constexpr int rows_per_wg(int head_dim) { return head_dim == 64 ? 128 : 256; }
+constexpr int wgs_per_cu(int head_dim) { return 256 / rows_per_wg(head_dim); }
+constexpr int copy_chunk_vecs(int head_dim) { return 32 * rows_per_wg(head_dim); }   // 16-byte vectors per chunk of the cached-head copy: 16 per thread
 
 // Arguments common to the attention kernels.  Strides are in elements.
 struct AttnArgs {
@@ -21,8 +31,8 @@ struct AttnArgs {
     const difa_segment_t* segs;     // device: segments grouped by workgroup (bf16 kernel)
     const int32_t* wg_begin;        // device: first segment of each workgroup, n_wg + 1 entries
     const difa_merge_item_t* merges;  // device: records cut into pieces
-    float* part_o;                  // device scratch: [slot][kBM][head_dim] unnormalised accumulators
-    float* part_ml;                 // device scratch: [slot][kBM][2] row reference (log2 domain), row sum
+    float* part_o;                  // device scratch: [slot][rows_per_wg][head_dim] unnormalised accumulators
+    float* part_ml;                 // device scratch: [slot][rows_per_wg][2] row reference (log2 domain), row sum
     int32_t* tickets;               // device, one per cut record, zero between launches: pieces finished so far
     const void* residual;           // device, shaped like out: kept differences of the residual-sharing heads (or NULL)
     // cached heads (bf16 kernel): out[b, h] = copy_src[b, h] for the heads listed in copy_heads

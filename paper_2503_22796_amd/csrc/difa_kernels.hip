@@ -35,9 +35,10 @@ __device__ __forceinline__ float halves_sum(float x) {
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA attention.
 //
-// A workgroup is 8 / QB wavefronts (QB = 32-row blocks per wavefront; 1 in the shipped build, so eight
-// wavefronts, two per SIMD) and stays resident: it walks the list of segments the host scheduler gave
-// it.  A segment is a 256-row query tile of one (batch, head) together with a
+// A workgroup is 8 / QB wavefronts at head_dim 128 and 4 / QB at 64 (QB = 32-row blocks per wavefront; 1 in the
+// shipped build, so eight wavefronts or two times four on a compute unit, two per SIMD) and stays resident: it walks
+// the list of segments the host scheduler gave it.  A segment is a 256-row (head_dim 64: 128-row) query tile of one
+// (batch, head) together with a
 // run of that record's key/value tiles (the whole run for most records; a few records are cut so
 // that every workgroup ends at the same time, and their pieces leave fp32 partial results that the
 // piece finishing last folds into its own).  Wavefront w owns rows 32*QB*w .. 32*QB*(w+1)-1 as QB 32-row blocks.
@@ -107,9 +108,10 @@ struct RowState {
 };
 
 template <int D, int QB>
-__global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
-    constexpr int NW = 8 / QB;              // wavefronts per workgroup; each owns 32*QB query rows
+__global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(AttnArgs a) {
+    constexpr int BM = rows_per_wg(D);      // query rows per record
     constexpr int RW = 32 * QB;
+    constexpr int NW = BM / RW;             // wavefronts per workgroup; each owns 32*QB query rows
     constexpr int KS = D / 16;              // MFMA k-steps of S^T = K Q^T
     constexpr int DB = D / 32;              // 32-row blocks of O^T
     constexpr int CPR = D / 8;              // 16-byte chunks per K/V row
@@ -249,7 +251,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
         const __bf16* qg = (const __bf16*)a.q + base;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const int i_r = sg.q_tile * kBM + wave * RW + 32 * qb + l32;
+            const int i_r = sg.q_tile * BM + wave * RW + 32 * qb + l32;
             const int i = i_r < N ? i_r : N - 1;            // rows past the end recompute row N-1
             // B operand of S^T = K Q^T: column = query l32, k-slots 8*half..8*half+7 of each 16-wide step
             const __bf16* qrow = qg + (int64_t)i * a.stride_n + 8 * half;
@@ -267,12 +269,12 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
     const int seg_end = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x + 1]);
     const int seg_first = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x]);
     // ---- cached heads (Sec. 3.2; the cache fill that ends Alg. 1): out[b, h] = cache[b, h], bit for bit.
-    // HBM-bound work that needs no matrix core.  It is cut into chunks of kCopyVecs 16-byte vectors of one
+    // HBM-bound work that needs no matrix core.  It is cut into chunks of copy_chunk_vecs(D) 16-byte vectors of one
     // (batch entry, cached head); workgroup p takes chunks p, p + gridDim.x, ... and moves one after each of
     // its attention segments, when it waits for the next segment's first tiles anyway, so the copy is
     // spread over the launch and runs in the shadow of the other workgroups' arithmetic.
     auto copy_chunk = [&](int chunk) __attribute__((always_inline)) {
-        constexpr int PER = kCopyVecs / (NW * 64);          // vectors per thread and chunk, all in flight together
+        constexpr int PER = copy_chunk_vecs(D) / (NW * 64);          // vectors per thread and chunk, all in flight together
         const AttnArgs* ca = cold_args();
         const int per_head = ca->copy_chunks_per_head, n_copy = ca->n_copy, shift = ca->copy_vec_shift;
         const int head_vecs = ca->copy_head_vecs;
@@ -287,7 +289,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
         bool live[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            int vi = cc * kCopyVecs + u * (NW * 64) + tid;                // vector inside the head
+            int vi = cc * copy_chunk_vecs(D) + u * (NW * 64) + tid;                // vector inside the head
             live[u] = vi < head_vecs;
             vi = live[u] ? vi : head_vecs - 1;                            // past the end: reread the last one, store nothing
             off[u] = (unsigned)(vi >> shift) * row_bytes + (unsigned)(vi & ((1 << shift) - 1)) * 16u;
@@ -299,6 +301,11 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
             if (live[u]) *(uintx4*)(dst + off[u]) = val[u];
     };
     int next_chunk = (int)blockIdx.x;
+    // Two workgroups share a compute unit at head_dim 64, and its SIMDs serve the older wavefront first: left to
+    // itself the workgroup that was dispatched second runs at 2500 clocks an iteration beside 1735 of the other, and the
+    // schedule, which gives both the same work, waits for it.  So the younger half of the grid takes the higher priority
+    // for two iterations out of four: 2130 beside 1950.
+    const bool younger = blockIdx.x >= gridDim.x / 2;
 
     difa_segment_t seg_next{};
     int sbase = 0;                                          // ring stage of the current segment's tile 0
@@ -338,7 +345,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
 
     const int b = it.bh / a.heads, h = it.bh - b * a.heads;
     __bf16* __restrict__ og = (__bf16*)a.out + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const int row0 = it.q_tile * kBM + wave * RW;           // first query row of this wavefront
+    const int row0 = it.q_tile * BM + wave * RW;           // first query row of this wavefront
 
     // ---- per-lane query rows (two: one per 32-row block) and their allowed key ranges
     RowState rs[QB];
@@ -398,7 +405,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
     // of the workgroup's 256 rows has a forbidden key in it; for the rows of one wavefront most such
     // blocks lie entirely inside the band, or are cut by one band edge only.  That is decided here from
     // scalars, so that the common cases cost nothing or two plain integer instructions per score.
-    const int row_first = it.q_tile * kBM + (int)wave_u * RW;              // this wavefront's rows (uniform)
+    const int row_first = it.q_tile * BM + (int)wave_u * RW;              // this wavefront's rows (uniform)
     const int row_last = row_first + RW - 1 < N - 1 ? row_first + RW - 1 : N - 1;
     auto mask_block = [&](int j0, floatx16 (&s)[QB]) {
         const bool plain = j0 >= img0 && j0 + 31 < img1 && row_first >= img0 && row_last < img1 && it.window >= 0;
@@ -406,6 +413,8 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
         const bool low = row_last - it.window > j0;                        // some row's band starts after j0
         const bool high = row_first + it.window < j0 + 31;                 // some row's band ends before the block does
         if (plain && !low && !high) return;
+        // a wavefront of text rows, or a block of text keys, inside the sequence: nothing to mask either
+        if (j0 + 31 < N && (row_last < img0 || row_first >= img1 || j0 + 31 < img0 || j0 >= img1)) return;
         const unsigned ninf = 0xff800000u;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -684,6 +693,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
         constexpr int P = decltype(stage_c)::value;         // ring stage of tile idx
         constexpr int KC = P * TILE, KN = ((P + 1) & 3) * TILE, KL = ((P + 3) & 3) * TILE;
         constexpr int VP = ((P + 3) & 3) * TILE, VC = P * TILE, VL = ((P + 2) & 3) * TILE;
+        if (wgs_per_cu(D) > 1 && (P & 1) == 0 && younger) __builtin_amdgcn_s_setprio(P == 0 ? 1 : 0);
         msk_cur = msk_nxt;
         msk_nxt = pos_masked(idx + 1);
         tb_v = tb_k;
@@ -757,26 +767,28 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
         // whole L2, the K/V tiles its workgroups share included.
         const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(a.part_o, 0, 0x7fffffff, 0x00020000);
         const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml, 0, 0x7fffffff, 0x00020000);
+        auto slot_bytes = [&](int slot, int qb) { return ((slot * NW + (int)wave_u) * QB + qb) * (32 * D * 4); };
+        // A slot holds the accumulators in the order of the registers, 1 KiB per wavefront and store: the piece
+        // that folds it in has them in the same registers, so no other order is ever needed.
+        const int slot_lane = (half * 32 + l32) * 16;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const int rl = it.part_slot * kBM + wave * RW + 32 * qb + l32;       // row inside the scratch
-            if (i_raw[qb] < N) {
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        floatx4 w4;
+                for (int g = 0; g < 4; ++g) {
+                    floatx4 w4;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) w4[e] = o[db][qb][4 * g + e];
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, w4), ro,
-                                                               (rl * D + 32 * db + 8 * g + 4 * half) * 4, 0, kDeviceCoherent);
-                    }
-                if (half == 0) {
-                    floatx2 ml;
-                    ml[0] = rs[qb].m;
-                    ml[1] = l_fin[qb];
-                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, ml), rm, rl * 8, 0, kDeviceCoherent);
+                    for (int e = 0; e < 4; ++e) w4[e] = o[db][qb][4 * g + e];
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, w4), ro, slot_lane + 1024 * (4 * db + g),
+                                                           slot_bytes(it.part_slot, qb), kDeviceCoherent);
                 }
+            if (half == 0) {
+                floatx2 ml;
+                ml[0] = rs[qb].m;
+                ml[1] = l_fin[qb];
+                const int rl = it.part_slot * BM + wave * RW + 32 * qb + l32;       // row inside the scratch
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, ml), rm, rl * 8, 0, kDeviceCoherent);
             }
         }
         // The slot has to be written before the ticket is taken.  The next segment's query rows and first
@@ -803,7 +815,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
                 if (slot == it.part_slot) continue;
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {
-                    const int rl = slot * kBM + wave * RW + 32 * qb + l32;
+                    const int rl = slot * BM + wave * RW + 32 * qb + l32;
                     // (whole vectors are reinterpreted: a bit_cast applied to one vector element reads element 0)
                     const floatx2 ml = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rm, rl * 8, 0, kDeviceCoherent));
                     floatx4 x[DB][4];
@@ -812,7 +824,7 @@ __global__ __launch_bounds__(512 / QB, 1) void attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
                         for (int g = 0; g < 4; ++g)
                             x[db][g] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                ro, (rl * D + 32 * db + 8 * g + 4 * half) * 4, 0, kDeviceCoherent));
+                                ro, slot_lane + 1024 * (4 * db + g), slot_bytes(slot, qb), kDeviceCoherent));
                     const float m_new = fmaxf(rs[qb].m, ml[0]);
                     const float w_mine = __builtin_amdgcn_exp2f(rs[qb].m - m_new), w_other = __builtin_amdgcn_exp2f(ml[0] - m_new);
                     rs[qb].m = m_new;
@@ -954,9 +966,9 @@ constexpr int kRowBlocks = 1;
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int n_wg, hipStream_t stream) {
     if (n_wg <= 0) return hipSuccess;
     if (head_dim == 128)
-        hipLaunchKernelGGL((attn_bf16_kernel<128, kRowBlocks>), dim3(n_wg), dim3(512 / kRowBlocks), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<128, kRowBlocks>), dim3(n_wg), dim3(2 * rows_per_wg(128) / kRowBlocks), 0, stream, a);
     else if (head_dim == 64)
-        hipLaunchKernelGGL((attn_bf16_kernel<64, kRowBlocks>), dim3(n_wg), dim3(512 / kRowBlocks), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<64, kRowBlocks>), dim3(n_wg), dim3(2 * rows_per_wg(64) / kRowBlocks), 0, stream, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

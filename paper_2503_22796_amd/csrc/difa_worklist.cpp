@@ -75,14 +75,14 @@ extern "C" int32_t difa_tile_shape(int32_t head_dim, int32_t dtype, int32_t* bm,
 }
 
 namespace {
-difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_plan,
+difa_status_t worklist_build(int32_t band_rows, int32_t batch, int32_t heads, const int32_t* head_plan,
                              const int32_t* window, int32_t n_text, int32_t n_img,
                              int32_t bm, int32_t bn, int32_t n_xcd, uint32_t flags,
                              difa_work_item_t* items,
                              int32_t capacity, int32_t* n_items_out,
                              int32_t* copy_heads, int32_t* n_copy_out) {
     if (!head_plan || !n_items_out || batch < 1 || heads < 1 || n_text < 0 || n_img < 0 ||
-        bm < 1 || bn < 1 || n_xcd < 1 || n_xcd > 64 || capacity < 0 || (capacity > 0 && !items) ||
+        bm < 1 || bn < 1 || band_rows < bm || band_rows % bm != 0 || n_xcd < 1 || n_xcd > 64 || capacity < 0 || (capacity > 0 && !items) ||
         (flags & ~(uint32_t)(DIFA_FLAG_BLOCK_BAND | DIFA_FLAG_IMAGE_FIRST)) != 0)
         return DIFA_ERR_INVALID_ARG;
     const int64_t n64 = (int64_t)n_text + (int64_t)n_img;
@@ -94,6 +94,7 @@ difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_p
         if ((mode == DIFA_HEAD_ARROW || mode == DIFA_HEAD_ARROW_RESIDUAL) && (!window || window[h] < 0)) return DIFA_ERR_INVALID_ARG;
     }
     const bool image_first = (flags & DIFA_FLAG_IMAGE_FIRST) != 0 && n_text > 0 && n_img > 0;
+    const bool block_band = (flags & DIFA_FLAG_BLOCK_BAND) != 0;
     const int n_kv_tiles = (int)((n64 + bn - 1) / bn);
     Geometry g{n_text, (int)n64, bm, bn, 0, 0, 0, n_kv_tiles};
     if (image_first) { g.img0 = 0; g.img1 = n_img; g.rot = n_img / bn; }
@@ -124,6 +125,10 @@ difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_p
             HeadSpan span{recs.size(), 0, 0};
             for (int qt = 0; qt < n_q_tiles; ++qt) {
                 const int i0 = qt * bm, i1 = std::min(i0 + bm, g.n_tokens);
+                // rows whose bands decide which key tiles are visited: the record's own, or with the block-granular
+                // band those of the block of band_rows rows that holds the record
+                const int v0 = block_band ? i0 / band_rows * band_rows : i0;
+                const int v1 = block_band ? std::min(v0 + band_rows, g.n_tokens) : i1;
                 difa_work_item_t r{};
                 r.bh = b * heads + h;
                 r.q_tile = qt;
@@ -132,7 +137,7 @@ difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_p
                 if (full && !image_first) {
                     r.kv0_end = n_kv_tiles;
                     r.kv1_begin = r.kv1_end = n_kv_tiles;
-                } else if (full || i0 < g.img0 || i1 > g.img1) {
+                } else if (full || v0 < g.img0 || v1 > g.img1) {
                     // every key: a full head, or a tile that holds text queries (they see every key).
                     // (Two ranges when the order is rotated, so that the sequence tail, the one tile a
                     // full head masks, ends the first range and the image tiles are mask-free as a run.)
@@ -143,8 +148,8 @@ difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_p
                     r.kv0_end = text_tiles;
                     // image keys [lo, hi] that some row of the tile sees, as tiles; the tiles that also hold
                     // text keys are in the first range already
-                    const int lo = std::max(g.img0, i0 - w);
-                    const int hi = std::min(g.img1 - 1, (i1 - 1) + w);
+                    const int lo = std::max(g.img0, v0 - w);
+                    const int hi = std::min(g.img1 - 1, (v1 - 1) + w);
                     if (image_first) {
                         const int t_lo = lo / bn, t_hi = std::min(hi / bn, g.rot - 1);
                         r.kv1_begin = text_tiles + t_lo;
@@ -156,7 +161,7 @@ difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_p
                 }
                 // Block-granular band (Sec. 3.3, Fig. 4): every visited block is dense, so the record is
                 // masked like a full head's: on the sequence tail only.
-                const int wm = (flags & DIFA_FLAG_BLOCK_BAND) ? -1 : w;
+                const int wm = block_band ? -1 : w;
                 r.window = wm;
                 int b0, e0;
                 mask_free_run(g, wm, i0, i1, 0, r.kv0_end, true, &b0, &e0);
@@ -230,7 +235,19 @@ extern "C" difa_status_t difa_worklist_build(int32_t batch, int32_t heads, const
                                              int32_t capacity, int32_t* n_items_out,
                                              int32_t* copy_heads, int32_t* n_copy_out) {
     try {
-        return worklist_build(batch, heads, head_plan, window, n_text, n_img, bm, bn, n_xcd, flags, items, capacity,
+        return worklist_build(bm, batch, heads, head_plan, window, n_text, n_img, bm, bn, n_xcd, flags, items, capacity,
+                              n_items_out, copy_heads, n_copy_out);
+    } catch (const std::bad_alloc&) {
+        return DIFA_ERR_ALLOC;
+    }
+}
+
+difa_status_t difa::worklist_for_kernel(int32_t batch, int32_t heads, const int32_t* head_plan, const int32_t* window,
+                                        int32_t n_text, int32_t n_img, int32_t rows, int32_t band_rows, int32_t bn,
+                                        uint32_t flags, difa_work_item_t* items, int32_t capacity, int32_t* n_items_out,
+                                        int32_t* copy_heads, int32_t* n_copy_out) {
+    try {
+        return worklist_build(band_rows, batch, heads, head_plan, window, n_text, n_img, rows, bn, 1, flags, items, capacity,
                               n_items_out, copy_heads, n_copy_out);
     } catch (const std::bad_alloc&) {
         return DIFA_ERR_ALLOC;
@@ -253,20 +270,10 @@ extern "C" difa_status_t difa_worklist_build(int32_t batch, int32_t heads, const
 // ------------------------------------------------------------------------------------------
 namespace {
 
-// Cost model of a segment, in eighths of a plain key-tile iteration.  Fitted on MI355X from clock counters
-// around the kernel's phases, regressed per workgroup on what the schedule had given it (head_dim 128 and
-// 64, the 1K and 2K layers): a plain iteration takes about 3000 clocks (2300 at head_dim 64), one on a tile
-// that needs the element mask 0.8-1.0 iterations more; starting and finishing a whole record costs 4-5
-// iterations; a piece of a cut record 7-12 (its partial result goes to scratch and a ticket is drawn, both
-// round trips to memory), and the piece that arrives last pays 3-9 more per other piece it folds in.  Who
-// arrives last is not known here, so every piece is charged its share.
+// Cost model of a segment: difa::CostModel, in eighths of a plain key-tile iteration.
+using difa::CostModel;
 constexpr int kUnit = 8;                  // cost units per key-tile iteration
-constexpr int kMaskedExtra = 7;           // extra units of an iteration on a masked tile
-constexpr int kWholeOverhead = 36;        // starting and finishing a whole record
-constexpr int kPieceOverhead = 72;        // ... a piece of a cut record, without the fold
-constexpr int kFoldPerSlot = 40;          // folding one other piece's partial result in
-constexpr int kPieceExpected = kPieceOverhead + kFoldPerSlot / 2;   // what a piece is charged while cutting
-constexpr int kMinPiece = 12;             // shortest piece (in key tiles) worth cutting off a record
+int piece_expected(const CostModel& m) { return m.piece + m.fold / 2; }   // what a piece is charged while cutting
 
 // Masked tiles among positions [p0, p1) of a record's visiting order.
 int masked_between(const difa_work_item_t& r, int p0, int p1) {
@@ -282,10 +289,10 @@ int masked_between(const difa_work_item_t& r, int p0, int p1) {
     return n;
 }
 
-int64_t tiles_cost(const difa_work_item_t& r, int p0, int p1) {
-    return (int64_t)kUnit * (p1 - p0) + (int64_t)kMaskedExtra * masked_between(r, p0, p1);
+int64_t tiles_cost(const CostModel& m, const difa_work_item_t& r, int p0, int p1) {
+    return (int64_t)kUnit * (p1 - p0) + (int64_t)m.masked * masked_between(r, p0, p1);
 }
-int64_t whole_cost(const difa_work_item_t& r) { return tiles_cost(r, 0, r.n_tiles) + kWholeOverhead; }
+int64_t whole_cost(const CostModel& m, const difa_work_item_t& r) { return tiles_cost(m, r, 0, r.n_tiles) + m.whole; }
 
 difa_segment_t whole_segment(const difa_work_item_t& r) {
     difa_segment_t s{};
@@ -315,12 +322,12 @@ struct DiePlan {
 
 struct Piece { int wg, pos_begin, pos_end; };
 
-void finish_record(DiePlan& plan, const difa_work_item_t& r, const std::vector<Piece>& pieces, bool dry) {
+void finish_record(const CostModel& m, DiePlan& plan, const difa_work_item_t& r, const std::vector<Piece>& pieces, bool dry) {
     const int n = (int)pieces.size();
     plan.most_parts = std::max(plan.most_parts, n);
     if (n > 1) {
-        // the pieces were charged kPieceExpected each; put the fold at what this record's piece count makes it
-        const int64_t fold = (int64_t)kFoldPerSlot * (n - 1) / n - kFoldPerSlot / 2;
+        // the pieces were charged piece_expected() each; put the fold at what this record's piece count makes it
+        const int64_t fold = (int64_t)m.fold * (n - 1) / n - m.fold / 2;
         for (const Piece& pc : pieces) plan.load[(size_t)pc.wg] += fold;
     }
     if (dry) {
@@ -356,7 +363,7 @@ void close_plan(DiePlan& plan) {
 // loaded, and so on.  Rooms are therefore of the order of a record when long records are cut (two or three
 // pieces each, so the workgroup that folds them together at the end reads one or two slots, not ten), and
 // short records, which are not worth cutting, fill the gaps that remain.
-DiePlan deal_and_pour(const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
+DiePlan deal_and_pour(const CostModel& m, const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
                       int64_t target, int slot_budget, bool dry) {
     DiePlan plan;
     if (!dry) plan.lists.resize((size_t)per_die);
@@ -367,7 +374,7 @@ DiePlan deal_and_pour(const std::vector<difa_work_item_t>& q, const std::vector<
     std::vector<size_t> n_whole((size_t)per_die, 0);
     std::vector<char> poured((size_t)per_die, 0);
     int cur = -1;
-    auto room_of = [&](int w) { return (target - load[(size_t)w] - kPieceExpected) / kUnit; };   // in key tiles
+    auto room_of = [&](int w) { return (target - load[(size_t)w] - piece_expected(m)) / kUnit; };   // in key tiles
     for (size_t i = 0; i < q.size(); ++i) {
         const difa_work_item_t& r = q[i];
         const int64_t c = cost[i];
@@ -381,7 +388,7 @@ DiePlan deal_and_pour(const std::vector<difa_work_item_t>& q, const std::vector<
         pieces.clear();
         int pos = 0;
         while (pos < r.n_tiles) {
-            if (cur < 0 || room_of(cur) < kMinPiece) cur = least();
+            if (cur < 0 || room_of(cur) < m.min_piece) cur = least();
             const int w = cur;
             const int remaining = r.n_tiles - pos;
             const int64_t room = room_of(w);
@@ -389,21 +396,21 @@ DiePlan deal_and_pour(const std::vector<difa_work_item_t>& q, const std::vector<
             const bool may_cut = plan.n_slots + (int)pieces.size() + 2 <= slot_budget;
             if (pos == 0 && load[(size_t)w] + c <= target) {
                 // the whole record fits
-            } else if (may_cut && room >= kMinPiece && room < remaining) {
+            } else if (may_cut && room >= m.min_piece && room < remaining) {
                 take = (int)room;
-                if (remaining - take < kMinPiece) take = remaining - kMinPiece >= kMinPiece ? remaining - kMinPiece : remaining;
-            } else if (may_cut && room < kMinPiece && remaining >= 4 * kMinPiece) {
+                if (remaining - take < m.min_piece) take = remaining - m.min_piece >= m.min_piece ? remaining - m.min_piece : remaining;
+            } else if (may_cut && room < m.min_piece && remaining >= 4 * m.min_piece) {
                 // no room anywhere (the target was too low): spread what is left over the least loaded
                 // workgroups in pieces of two to four times the shortest one, rather than on one of them
-                const int n = (remaining + 3 * kMinPiece - 1) / (3 * kMinPiece);
+                const int n = (remaining + 3 * m.min_piece - 1) / (3 * m.min_piece);
                 take = (remaining + n - 1) / n;
             }
             pieces.push_back(Piece{w, pos, pos + take});
-            load[(size_t)w] += tiles_cost(r, pos, pos + take) + (take == r.n_tiles ? kWholeOverhead : kPieceExpected);
+            load[(size_t)w] += tiles_cost(m, r, pos, pos + take) + (take == r.n_tiles ? m.whole : piece_expected(m));
             poured[(size_t)w] = 1;
             pos += take;
         }
-        finish_record(plan, r, pieces, dry);
+        finish_record(m, plan, r, pieces, dry);
     }
     // A poured room holds the tail of one record and the head of the next one, neighbouring query tiles of
     // one head as a rule.  Run in the order of their first key position (the shorter one first among equals),
@@ -425,7 +432,7 @@ DiePlan deal_and_pour(const std::vector<difa_work_item_t>& q, const std::vector<
 
 // The records laid end to end and handed out in runs of the target cost: workgroup 0 is filled, then
 // workgroup 1, ...; a record that crosses a boundary is cut there.
-DiePlan fill_in_order(const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
+DiePlan fill_in_order(const CostModel& m, const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
                       int64_t target, int slot_budget, bool dry) {
     DiePlan plan;
     if (!dry) plan.lists.resize((size_t)per_die);
@@ -438,25 +445,25 @@ DiePlan fill_in_order(const std::vector<difa_work_item_t>& q, const std::vector<
         pieces.clear();
         int pos = 0;
         if (w < per_die - 1 && load[(size_t)w] > 0 && load[(size_t)w] + cost[i] > target &&
-            (target - load[(size_t)w] - kPieceExpected) / kUnit < kMinPiece)
+            (target - load[(size_t)w] - piece_expected(m)) / kUnit < m.min_piece)
             ++w;                                                      // no room worth a piece: the next workgroup goes on
         while (pos < r.n_tiles) {
             const int remaining = r.n_tiles - pos;
-            const int64_t ovh = pos == 0 ? kWholeOverhead : kPieceExpected;
+            const int64_t ovh = pos == 0 ? m.whole : piece_expected(m);
             int take = remaining;
-            if (w < per_die - 1 && load[(size_t)w] + tiles_cost(r, pos, r.n_tiles) + ovh > target) {
-                const int64_t room = (target - load[(size_t)w] - kPieceExpected) / kUnit;   // in key tiles
+            if (w < per_die - 1 && load[(size_t)w] + tiles_cost(m, r, pos, r.n_tiles) + ovh > target) {
+                const int64_t room = (target - load[(size_t)w] - piece_expected(m)) / kUnit;   // in key tiles
                 const bool may_cut = plan.n_slots + (int)pieces.size() + 2 <= slot_budget;
-                if (may_cut && room >= kMinPiece && remaining - room >= kMinPiece) take = (int)room;
-                else if (may_cut && room >= kMinPiece && remaining - kMinPiece >= kMinPiece) take = remaining - kMinPiece;
+                if (may_cut && room >= m.min_piece && remaining - room >= m.min_piece) take = (int)room;
+                else if (may_cut && room >= m.min_piece && remaining - m.min_piece >= m.min_piece) take = remaining - m.min_piece;
                 else if (load[(size_t)w] > 0 && pos == 0) { ++w; continue; }   // rather start it on the next workgroup
             }                                                         // else: overfill
             pieces.push_back(Piece{w, pos, pos + take});
-            load[(size_t)w] += tiles_cost(r, pos, pos + take) + (take == r.n_tiles ? kWholeOverhead : kPieceExpected);
+            load[(size_t)w] += tiles_cost(m, r, pos, pos + take) + (take == r.n_tiles ? m.whole : piece_expected(m));
             pos += take;
             if (pos < r.n_tiles && w < per_die - 1) ++w;              // cut: the rest starts the next workgroup
         }
-        finish_record(plan, r, pieces, dry);
+        finish_record(m, plan, r, pieces, dry);
     }
     close_plan(plan);
     return plan;
@@ -496,7 +503,7 @@ DiePlan deal_whole(const std::vector<difa_work_item_t>& q, const std::vector<int
     return plan;
 }
 
-difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int32_t n_wg,
+difa_status_t schedule_build(const CostModel& m, const difa_work_item_t* items, int32_t n_items, int32_t n_wg,
                              int32_t n_xcd, const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                              int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out, difa_merge_item_t* merges,
                              int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out) {
@@ -520,7 +527,7 @@ difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int
     for (size_t i = 0; i < recs.size();) {
         size_t j = i;
         int64_t cost = 0;
-        while (j < recs.size() && recs[j].bh == recs[i].bh) { cost += whole_cost(recs[j]); ++j; }
+        while (j < recs.size() && recs[j].bh == recs[i].bh) { cost += whole_cost(m, recs[j]); ++j; }
         spans.push_back({i, j - i, cost});
         i = j;
     }
@@ -553,7 +560,7 @@ difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int
         for (const HeadSpan& sp : spans)
             for (size_t k = 0; k < sp.count; ++k) {
                 const difa_work_item_t& r = recs[sp.first + k];
-                const int64_t c = whole_cost(r);
+                const int64_t c = whole_cost(m, r);
                 const double mid = total > 0 ? (double)(2 * cum + c) / (double)(2 * total) : 0.0;
                 while (x_at < n_xcd - 1 && mid >= upto[(size_t)x_at + 1]) ++x_at;
                 die[(size_t)x_at].push_back(r);
@@ -566,7 +573,7 @@ difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int
             // query tiles of a head cost the same and stay neighbours
             {
                 std::vector<std::pair<int64_t, int>> key(q.size());
-                for (size_t i = 0; i < q.size(); ++i) key[i] = {-whole_cost(q[i]), (int)i};
+                for (size_t i = 0; i < q.size(); ++i) key[i] = {-whole_cost(m, q[i]), (int)i};
                 std::sort(key.begin(), key.end());                   // (ties keep their order: the index decides)
                 std::vector<difa_work_item_t> sorted(q.size());
                 cost.resize(q.size());
@@ -577,9 +584,9 @@ difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int
             for (size_t i = 0; i < q.size(); ++i) die_cost += cost[i];
             const int budget = slot_capacity - slots_so_far - 2 * per_die * (n_xcd - 1 - x);   // this die's share of the slots
             // every workgroup is expected to take one piece
-            const int64_t first = (die_cost + (int64_t)per_die * kPieceExpected + per_die - 1) / per_die;
-            auto deal = [&](int64_t t, bool dry) { return deal_and_pour(q, cost, per_die, t, budget, dry); };
-            auto fill = [&](int64_t t, bool dry) { return fill_in_order(q, cost, per_die, t, budget, dry); };
+            const int64_t first = (die_cost + (int64_t)per_die * piece_expected(m) + per_die - 1) / per_die;
+            auto deal = [&](int64_t t, bool dry) { return deal_and_pour(m, q, cost, per_die, t, budget, dry); };
+            auto fill = [&](int64_t t, bool dry) { return fill_in_order(m, q, cost, per_die, t, budget, dry); };
             DiePlan dealt = deal(settle_target(first, per_die, deal), false);
             // When the records are few and long compared with a workgroup's share (small layers), dealing whole
             // records and cutting the rest leaves the workgroups uneven; filling them one after the other may
@@ -623,9 +630,9 @@ difa_status_t schedule_build(const difa_work_item_t* items, int32_t n_items, int
                 if (sg.part_slot >= 0) { sg.part_slot += n_slots; sg.first_slot += n_slots; sg.merge_idx += (int32_t)merge_list.size(); }
                 lists[(size_t)(w * n_xcd + x)].push_back(sg);
             }
-        for (difa_merge_item_t m : dealt.merges) {
-            m.first_slot += n_slots;
-            merge_list.push_back(m);
+        for (difa_merge_item_t cut : dealt.merges) {
+            cut.first_slot += n_slots;
+            merge_list.push_back(cut);
         }
         n_slots += dealt.n_slots;
     }
@@ -651,7 +658,7 @@ extern "C" difa_status_t difa_schedule_build(const difa_work_item_t* items, int3
                                              int32_t* wg_begin, int32_t* n_segs_out, difa_merge_item_t* merges,
                                              int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out) {
     try {
-        return schedule_build(items, n_items, n_wg, n_xcd, nullptr, nullptr, segs, seg_capacity, wg_begin, n_segs_out,
+        return schedule_build(difa::kGenericCosts, items, n_items, n_wg, n_xcd, nullptr, nullptr, segs, seg_capacity, wg_begin, n_segs_out,
                               merges, merge_capacity, n_merges_out, n_slots_out);
     } catch (const std::bad_alloc&) {
         return DIFA_ERR_ALLOC;
@@ -660,13 +667,13 @@ extern "C" difa_status_t difa_schedule_build(const difa_work_item_t* items, int3
 
 // The same for the library's own calls: with the dies' relative speeds as measured on earlier launches (NULL:
 // all alike), and returning each die's predicted finishing time in the scheduler's cost units.
-difa_status_t difa::schedule_for_dies(const difa_work_item_t* items, int32_t n_items, int32_t n_wg, int32_t n_xcd,
+difa_status_t difa::schedule_for_dies(const CostModel& m, const difa_work_item_t* items, int32_t n_items, int32_t n_wg, int32_t n_xcd,
                                       const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                                       int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out,
                                       difa_merge_item_t* merges, int32_t merge_capacity, int32_t* n_merges_out,
                                       int32_t* n_slots_out) {
     try {
-        return schedule_build(items, n_items, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin, n_segs_out,
+        return schedule_build(m, items, n_items, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin, n_segs_out,
                               merges, merge_capacity, n_merges_out, n_slots_out);
     } catch (const std::bad_alloc&) {
         return DIFA_ERR_ALLOC;
