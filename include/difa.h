@@ -117,8 +117,8 @@ difa_status_t difa_joint_attention(difa_plan_t* plan, const void* q, const void*
  * device array that is part of the library's code object (68 157 440 bytes per GPU, there from the
  * moment the library is loaded until the process ends) instead of the plan object's own buffer.  The
  * call makes no hipMalloc / hipFree and calls no allocating library routine.
- * Limit: a call whose schedule needs more than the array holds -- pieces * 256 rows * (head_dim + 2)
- * floats; 512 pieces at head_dim 128, which covers every schedule for a GPU of up to 256 compute
+ * Limit: a call whose schedule needs more than the array holds -- 512 pieces of 256 rows * (head_dim + 2)
+ * floats at head_dim 128, 2016 of 128 rows at 64, which covers every schedule for a GPU of up to 256 compute
  * units -- fails with DIFA_ERR_UNSUPPORTED and a message naming both sizes.
  * Every call of this entry point on one GPU uses the same array, whatever the plan object or stream:
  * two such calls that overlap in time on one GPU race and produce wrong rows; the caller orders them
@@ -198,7 +198,8 @@ typedef struct {
 } difa_work_item_t;
 enum { DIFA_ITEM_ADD_RESIDUAL = 1 };
 
-/* Tile shape (query rows bm, keys bn) the kernels use for a head_dim/dtype; 0 on success. */
+/* Block shape (query rows bm, keys bn) of the block-granular band for a head_dim/dtype, and the tile shape callers of
+ * the two functions below should use; 0 on success.  (The kernels' own records may be a whole fraction of bm rows.) */
 int32_t difa_tile_shape(int32_t head_dim, int32_t dtype, int32_t* bm, int32_t* bn);
 
 /*
@@ -321,11 +322,11 @@ difa_status_t difa_plan_timing_read(difa_plan_t* plan, double* attn_ms, double* 
 difa_status_t difa_plan_timing_read_head_rse(difa_plan_t* plan, double* rse_ms, int64_t* launches, int32_t reset);
 /*
  * What the plan object has learnt about the accelerator dies.  Under load the dies of one GPU settle at
- * clocks a few percent apart; the bf16 kernel reports how long each workgroup ran, the object averages the
- * dies' relative speeds from the reports of finished launches, and a layer's schedule exists in two versions:
- * dies alike, or work in proportion to the speeds.  The version made first runs until three launches of it
- * have been timed, then the other one, then the faster of the two stays (so a memoised schedule is made
- * again at most twice in its life).  No call waits for a report: a call uses what has arrived by then.
+ * clocks a few percent apart; the bf16 kernel reports how long each workgroup ran, and the object averages the
+ * dies' relative speeds from the reports of finished launches.  A layer's schedule is first made for those; after
+ * three launches it is made again for the rates at which the dies went through that very schedule, if they do not
+ * finish together, and again after 3, 16 and 32 launches more; a version that turns out slower than the one before
+ * it gives way to it for good.  No call waits for a report: a call uses what has arrived by then.
  *   speeds     HOST array of `capacity` doubles: receives the relative speeds (mean 1), one per die.
  *   n_dies     number of dies the scheduler distinguishes (1: the mechanism is off).
  *   samples    launches whose reports went into the running average (a new plan object starts from what

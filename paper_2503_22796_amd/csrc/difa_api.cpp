@@ -18,11 +18,14 @@
 
 namespace {
 
-constexpr int kSlots = 8;      // distinct (head plan, n_text, n_img) schedules kept resident on the device
+constexpr int kSlots = 32;     // distinct (head plan, n_text, n_img) schedules kept resident on the device: a layer's plans for one
+                               // denoising loop (28 steps are usual), so that the next loop compiles none of them again
 constexpr int kStagings = 16;  // pinned host buffers the schedules are uploaded from, used in turn
 constexpr int kXcd = 8;        // accelerator dies of an MI355X: workgroup p runs on die p % 8
 
 constexpr int kMaxDies = 16;
+constexpr int kTrials = 4;     // versions of a memoised schedule that are timed, and for how many launches each
+constexpr int kTrialLaunches[kTrials] = {3, 3, 16, 32};
 constexpr int kRecent = 64;
 
 struct Slot {
@@ -32,14 +35,18 @@ struct Slot {
     bool valid = false;
     uint64_t stamp = 0;
     int64_t die_span[kMaxDies] = {};    // predicted finishing time of each die, in the scheduler's cost units
-    // The schedule exists in two versions: dies alike (0), or work in proportion to the measured die speeds (1).
-    // Which one is faster is measured, not assumed: the one made first runs until three launches of it have
-    // been timed, then the other one, then the faster of the two stays.
-    int version = 0;                    // the one in the buffer
-    int trial = 0;                      // 0: first version on trial, 1: second version on trial, 2: settled
+    // A schedule is made for die speeds: at first those the plan object has learnt so far, then the rates at which the dies
+    // have gone through this very schedule (how fast a die goes depends on what it is given: dies with short band records
+    // clock higher than dies with full heads).  A version runs until a few launches of it have been timed (kTrialLaunches);
+    // the dies not finishing together, the next one is made from what they took, and one that turned out slower gives
+    // way to the best so far for good.
+    double speed[kMaxDies] = {};        // what the one in the buffer was made for
+    double best_speed[kMaxDies] = {};   // ... the fastest one before it
+    double best_ticks = 0.0;            // mean launch time of that one
+    int trial = 0;                      // versions timed so far; kTrials: settled
     uint32_t sched_id = 0;              // names this compilation (run-time reports are credited to it)
-    double ticks[2] = {0.0, 0.0};       // measured launch times per version, summed
-    int timed[2] = {0, 0};
+    double ticks = 0.0, die_ticks[kMaxDies] = {};   // measured times of the launches and of their dies, summed
+    int timed = 0;
 };
 
 struct Staging {
@@ -90,6 +97,8 @@ struct difa_plan {
     std::vector<int32_t> keys;          // memo keys: kSlots rows of 2 * heads + 2, then one row for the call's own
     Slot slots[kSlots];
     Staging stagings[kStagings];
+    char* d_slots = nullptr;            // the slots' device buffers and the pinned staging buffers, one allocation each
+    char* h_stagings = nullptr;
     int next_staging = 0;
     uint64_t clock = 0;
     std::string err;
@@ -143,15 +152,15 @@ std::string hip_msg(const char* what, hipError_t e) noexcept {
 size_t elem_size(int dtype) { return dtype == DIFA_DTYPE_BF16 ? 2 : 4; }
 
 void free_buffers(difa_plan* p) {
-    for (Slot& s : p->slots) {
-        if (s.d_buf) (void)hipFree(s.d_buf);
-        s = Slot();
-    }
+    for (Slot& s : p->slots) s = Slot();
+    if (p->d_slots) (void)hipFree(p->d_slots);
     for (Staging& g : p->stagings) {
-        if (g.h_buf) (void)hipHostFree(g.h_buf);
         if (g.copied) (void)hipEventDestroy(g.copied);
         g = Staging();
     }
+    if (p->h_stagings) (void)hipHostFree(p->h_stagings);
+    p->d_slots = nullptr;
+    p->h_stagings = nullptr;
     if (p->h_times) (void)hipHostFree(p->h_times);
     p->h_times = p->d_times = nullptr;
     if (p->part_o) (void)hipFree(p->part_o);
@@ -192,10 +201,11 @@ void harvest_die_speeds(difa_plan* p) {
         Slot& sl = p->slots[l.slot];
         unsigned long long longest = 0;
         for (int x = 0; x < n_xcd; ++x) longest = std::max(longest, ticks[x]);
-        if (sl.valid && sl.sched_id == l.sched_id && sl.trial < 2 && longest > 0) {
+        if (sl.valid && sl.sched_id == l.sched_id && sl.trial < kTrials && longest > 0) {
             if (p->reports_seen > 0) {                                // (the process's very first launch runs on a cold chip)
-                sl.ticks[sl.version] += (double)longest;
-                ++sl.timed[sl.version];
+                sl.ticks += (double)longest;
+                for (int x = 0; x < n_xcd; ++x) sl.die_ticks[x] += (double)ticks[x];
+                ++sl.timed;
             }
         }
     }
@@ -220,6 +230,38 @@ void harvest_die_speeds(difa_plan* p) {
         for (int x = 0; x < n_xcd; ++x) g.speed[x] = p->die_speed[x];
         g.n_dies = n_xcd;
     }
+}
+
+// What the timed launches of a memoised schedule say: false if it stays (for now, or for good), true if it is to be made
+// again for the speeds in `want`.
+bool retune_wanted(Slot& s, int n_dies, double* want) {
+    const double mine = s.ticks / s.timed;
+    double mean = 0.0, rate_mean = 0.0, longest = 0.0;
+    for (int x = 0; x < n_dies; ++x) {
+        mean += s.die_ticks[x] / s.timed / n_dies;
+        longest = std::max(longest, s.die_ticks[x] / s.timed);
+    }
+    bool rates = true;                                                // every die was busy long enough to have a rate
+    for (int x = 0; x < n_dies; ++x) {
+        rates &= s.die_span[x] >= 256 && s.die_ticks[x] >= 1000.0 * s.timed;
+        want[x] = rates ? (double)s.die_span[x] * s.timed / s.die_ticks[x] : 1.0;
+        rate_mean += want[x] / n_dies;
+    }
+    for (int x = 0; x < kMaxDies; ++x)
+        want[x] = x < n_dies ? std::min(1.3, std::max(0.7, want[x] / rate_mean)) : 1.0;
+    if (s.trial > 0 && mine > s.best_ticks * 0.997) {                 // the earlier version was faster after all
+        memcpy(want, s.best_speed, sizeof s.best_speed);
+        s.trial = kTrials;
+        return true;
+    }
+    ++s.trial;
+    if (!rates || longest < mean * 1.015 || s.trial == kTrials) {     // the dies finish together, as far as that goes
+        s.trial = kTrials;
+        return false;
+    }
+    memcpy(s.best_speed, s.speed, sizeof s.speed);
+    s.best_ticks = mine;
+    return true;
 }
 
 // Puts what is about to be enqueued on `stream` behind everything this object enqueued before.
@@ -360,8 +402,9 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     p->buf_bytes = p->heads_bytes + ((size_t)p->n_wg + 1) * sizeof(int32_t) + 64 +
                    ((size_t)cap + 2 * (size_t)p->n_wg) * sizeof(difa_segment_t) + 64 +
                    2 * (size_t)p->n_wg * sizeof(difa_merge_item_t) + 64 + (size_t)cap * sizeof(difa_work_item_t);
+    p->buf_bytes = (p->buf_bytes + 255) / 256 * 256;
     try {
-        p->recs.resize((size_t)cap);
+        p->recs.reserve((size_t)cap);
         p->keys.assign((size_t)(kSlots + 1) * (2 * (size_t)desc->heads + 2), 0);
     } catch (const std::bad_alloc&) {
         delete p;
@@ -401,10 +444,12 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     if (e == hipSuccess) {
         what = "allocating work-list buffers";
         e = hipEventCreateWithFlags(&p->order_ev, hipEventDisableTiming);
-        for (int s = 0; s < kSlots && e == hipSuccess; ++s) e = hipMalloc(&p->slots[s].d_buf, p->buf_bytes);
+        if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, (size_t)kSlots * p->buf_bytes);
+        if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_stagings, (size_t)kStagings * p->buf_bytes, hipHostMallocDefault);
+        for (int s = 0; s < kSlots && e == hipSuccess; ++s) p->slots[s].d_buf = p->d_slots + (size_t)s * p->buf_bytes;
         for (int s = 0; s < kStagings && e == hipSuccess; ++s) {
-            e = hipHostMalloc(&p->stagings[s].h_buf, p->buf_bytes, hipHostMallocDefault);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&p->stagings[s].copied, hipEventDisableTiming);
+            p->stagings[s].h_buf = p->h_stagings + (size_t)s * p->buf_bytes;
+            e = hipEventCreateWithFlags(&p->stagings[s].copied, hipEventDisableTiming);
         }
     }
     if (e == hipSuccess) {
@@ -573,22 +618,14 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
     harvest_die_speeds(p);
     const bool speeds_known = p->h_times && p->speed_samples >= 3;
     Slot* slot = nullptr;
-    int victim = -1, want_version = -1;
+    int victim = -1;
+    double want[kMaxDies];                                            // die speeds the schedule is to be made again for
     for (int s = 0; s < kSlots; ++s)
         if (p->slots[s].valid && memcmp(p->keys.data() + (size_t)s * key_len, key, key_len * sizeof(int32_t)) == 0) {
             slot = &p->slots[s];
-            // The trial of the schedule's two versions (see Slot): made again at most twice in its life.
-            if (p->h_times && slot->n_items > 0 && slot->trial < 2 && slot->timed[slot->version] >= 3) {
-                const int other = 1 - slot->version;
-                if (slot->trial == 0) {
-                    if (other == 0 || speeds_known) { want_version = other; slot->trial = 1; }
-                } else {
-                    const double mine = slot->ticks[slot->version] / slot->timed[slot->version];
-                    const double theirs = slot->timed[other] > 0 ? slot->ticks[other] / slot->timed[other] : 1e300;
-                    if (theirs < mine * 0.997) want_version = other;  // the earlier version was faster after all
-                    slot->trial = 2;
-                }
-                if (want_version >= 0) { victim = s; slot = nullptr; }
+            if (p->h_times && slot->n_items > 0 && slot->trial < kTrials && slot->timed >= kTrialLaunches[slot->trial] && retune_wanted(*slot, p->n_xcd, want)) {
+                victim = s;
+                slot = nullptr;
             }
             break;
         }
@@ -604,13 +641,14 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         Slot* lru = &p->slots[victim];
         if (retune) {
             ++p->retunes;
-            lru->version = want_version;
+            memcpy(lru->speed, want, sizeof want);
         } else {
-            lru->version = speeds_known ? 1 : 0;
+            for (int x = 0; x < kMaxDies; ++x) lru->speed[x] = speeds_known ? p->die_speed[x] : 1.0;
             lru->trial = 0;
-            lru->ticks[0] = lru->ticks[1] = 0.0;
-            lru->timed[0] = lru->timed[1] = 0;
         }
+        lru->ticks = 0.0;
+        memset(lru->die_ticks, 0, sizeof lru->die_ticks);
+        lru->timed = 0;
         lru->sched_id = ++p->next_sched_id;
         // The device buffer may still be read by launches enqueued earlier: the copy below goes on `stream`,
         // behind all of them.  The pinned buffer it is written into on the host may still be the source of a
@@ -623,11 +661,13 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         }
         stg.pending = false;
         lru->valid = false;
-        int32_t n_items = 0, n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
+        int32_t n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
         char* hb = (char*)stg.h_buf;
-        difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, p->bm, p->band_rows, p->bn, p->desc.flags,
-                                               p->recs.data(), p->item_capacity, &n_items, (int32_t*)hb, &n_copy);
+        difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, p->bm, p->band_rows, p->bn,
+                                                     p->desc.flags, p->recs, (int32_t*)hb, &n_copy);
+        if (st == DIFA_OK && p->recs.size() > (size_t)p->item_capacity) st = DIFA_ERR_ALLOC;    // (cannot be: sized from max_tokens)
         if (st != DIFA_OK) return fail(p, st, "work-list compilation failed");
+        const int32_t n_items = (int32_t)p->recs.size();
         size_t used = p->heads_bytes;
         lru->wg_off = lru->segs_off = lru->merges_off = lru->items_off = used;
         if (p->desc.dtype == DIFA_DTYPE_BF16) {
@@ -636,7 +676,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             const int32_t seg_cap = n_items + 2 * p->n_wg;
             lru->merges_off = (lru->segs_off + (size_t)seg_cap * sizeof(difa_segment_t) + 63) / 64 * 64;
             const bool dies = p->h_times != nullptr;
-            st = difa::schedule_for_dies(difa::kGenericCosts, p->recs.data(), n_items, p->n_wg, p->n_xcd, dies && lru->version == 1 ? p->die_speed : nullptr,
+            st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, p->n_wg, p->n_xcd, dies ? lru->speed : nullptr,
                                          dies ? lru->die_span : nullptr, (difa_segment_t*)(hb + lru->segs_off),
                                          seg_cap, (int32_t*)(hb + lru->wg_off), &n_segs,
                                          (difa_merge_item_t*)(hb + lru->merges_off), 2 * p->n_wg, &n_merges, &n_slots);

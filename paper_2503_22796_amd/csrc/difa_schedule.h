@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <vector>
+
 #include "difa.h"
 
 namespace difa {
@@ -16,15 +18,24 @@ struct CostModel {
     int min_piece;   // shortest piece, in key tiles, worth cutting off a record
 };
 constexpr CostModel kGenericCosts{7, 36, 72, 40, 12};   // what difa_schedule_build prices with
+// Measured on MI355X: clock counters around every segment, regressed per workgroup on what its list held (1K and 2K
+// layers).  head_dim 128, one workgroup of eight wavefronts on a compute unit: 2950 clocks a plain iteration, 0.5-0.6
+// iterations more on a masked tile, 5.9 for starting and finishing a whole record, 6.1 for a piece (9-11 while slots were
+// laid out by rows), 2.4 for folding one other slot in.  head_dim 64, two workgroups of four wavefronts sharing the
+// compute unit: 2000 clocks, 1.4, 1-3, 3-5 and 2.7 iterations.
+constexpr CostModel kernel_costs(int head_dim) {
+    return head_dim == 64 ? CostModel{11, 12, 28, 21, 8} : CostModel{8, 26, 36, 19, 8};
+}
 
-// difa_worklist_build (n_xcd = 1) for a kernel whose records are `rows` query rows, a divisor of the block-granular
-// band's block of `band_rows` rows: the key tiles a record visits are then those of the block it lies in.
+// The records of difa_worklist_build, head by head and query tiles in ascending order, for a kernel whose records are
+// `rows` query rows, a divisor of the block-granular band's block of `band_rows` rows: the key tiles a record visits
+// are then those of the block it lies in.  `recs` is overwritten.  May throw std::bad_alloc, as the next one may.
 difa_status_t worklist_for_kernel(int32_t batch, int32_t heads, const int32_t* head_plan, const int32_t* window,
                                   int32_t n_text, int32_t n_img, int32_t rows, int32_t band_rows, int32_t bn,
-                                  uint32_t flags, difa_work_item_t* items, int32_t capacity, int32_t* n_items_out,
-                                  int32_t* copy_heads, int32_t* n_copy_out);
+                                  uint32_t flags, std::vector<difa_work_item_t>& recs, int32_t* copy_heads,
+                                  int32_t* n_copy_out);
 
-// difa_schedule_build with three more arguments:
+// difa_schedule_build for records in that order, with three more arguments:
 //   m           what a segment costs
 //   die_speed   n_xcd relative speeds of the accelerator dies (NULL: all alike).  Under a heavy load the
 //               dies of one chip settle at clocks a few percent apart; a die is given work in
@@ -32,7 +43,7 @@ difa_status_t worklist_for_kernel(int32_t batch, int32_t heads, const int32_t* h
 //   die_span    receives, per die, the predicted finishing time of its slowest workgroup in the
 //               scheduler's cost units at speed 1 (NULL: not wanted).  The caller divides it by the die's
 //               measured time to learn the speeds.
-difa_status_t schedule_for_dies(const CostModel& m, const difa_work_item_t* items, int32_t n_items, int32_t n_wg, int32_t n_xcd,
+difa_status_t schedule_for_dies(const CostModel& m, const std::vector<difa_work_item_t>& recs, int32_t n_wg, int32_t n_xcd,
                                 const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                                 int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out,
                                 difa_merge_item_t* merges, int32_t merge_capacity, int32_t* n_merges_out,

@@ -41,27 +41,33 @@ bool tile_needs_mask(const Geometry& g, int w, int i0, int i1, int j0) {
     return (kj1 - qi0 > w) || (qi1 - kj0 > w);
 }
 
-// Mask-free tiles of a range [begin, end) of positions in the rotated order: for the first range the
+// Mask-free tiles of a range [begin, end) of positions in the rotated order: for the first range (prefix_only) the
 // mask-free prefix, for the second the longest run of consecutive mask-free tiles.  Treating a mask-free tile as masked
-// is always safe, so any sub-run is a valid answer.
+// is always safe, so any sub-run is a valid answer.  A layer has thousands of records of hundreds of tiles, so the run
+// comes from the band's edges and not from a look at every tile.
 void mask_free_run(const Geometry& g, int w, int i0, int i1, int begin, int end, bool prefix_only,
                    int* run_begin, int* run_end) {
-    int best_b = begin, best_e = begin;
-    int t = begin;
-    while (t < end) {
-        if (tile_needs_mask(g, w, i0, i1, g.tile_at(t) * g.bn)) {
-            if (prefix_only) break;
-            ++t;
-            continue;
-        }
-        int e = t;
-        while (e < end && !tile_needs_mask(g, w, i0, i1, g.tile_at(e) * g.bn)) ++e;
-        if (e - t > best_e - best_b) { best_b = t; best_e = e; }
-        if (prefix_only) break;
-        t = e;
+    *run_begin = *run_end = begin;
+    if (begin >= end) return;
+    const int qi0 = std::max(i0, g.img0), qi1 = std::min(i1, g.img1) - 1;          // image rows [qi0, qi1]
+    if (w < 0 || qi0 > qi1) {
+        // only the tile with the end of the sequence needs the mask
+        const int tail = g.n_tokens % g.bn ? g.n_kv_tiles - 1 - g.rot : g.n_kv_tiles;   // its position
+        if (tail < begin || tail >= end) *run_end = end;
+        else if (prefix_only || tail - begin >= end - tail - 1) *run_end = tail;
+        else { *run_begin = tail + 1; *run_end = end; }
+        return;
     }
-    *run_begin = best_b;
-    *run_end = best_e;
+    if (prefix_only) {                                                             // the few tiles with text keys
+        while (*run_end < end && !tile_needs_mask(g, w, i0, i1, g.tile_at(*run_end) * g.bn)) ++*run_end;
+        return;
+    }
+    // The second range holds image keys only, tiles first, first + 1, ...: mask-free are those whose first key is at
+    // most w below the last row, whose last key is at most w above the first row, and which lie inside the sequence.
+    const int64_t first = g.tile_at(begin), low = std::max(0, qi1 - w), high = (int64_t)qi0 + w + 1;
+    const int64_t t0 = (low + g.bn - 1) / g.bn, t1 = std::min<int64_t>(high, g.n_tokens) / g.bn;    // tiles [t0, t1)
+    const int64_t b = std::max<int64_t>(begin, begin + (t0 - first)), e = std::min<int64_t>(end, begin + (t1 - first));
+    if (b < e) { *run_begin = (int)b; *run_end = (int)e; }
 }
 
 }  // namespace
@@ -75,14 +81,16 @@ extern "C" int32_t difa_tile_shape(int32_t head_dim, int32_t dtype, int32_t* bm,
 }
 
 namespace {
-difa_status_t worklist_build(int32_t band_rows, int32_t batch, int32_t heads, const int32_t* head_plan,
-                             const int32_t* window, int32_t n_text, int32_t n_img,
-                             int32_t bm, int32_t bn, int32_t n_xcd, uint32_t flags,
-                             difa_work_item_t* items,
-                             int32_t capacity, int32_t* n_items_out,
-                             int32_t* copy_heads, int32_t* n_copy_out) {
-    if (!head_plan || !n_items_out || batch < 1 || heads < 1 || n_text < 0 || n_img < 0 ||
-        bm < 1 || bn < 1 || band_rows < bm || band_rows % bm != 0 || n_xcd < 1 || n_xcd > 64 || capacity < 0 || (capacity > 0 && !items) ||
+struct HeadSpan { size_t first, count; int64_t cost; };
+
+// The records of a layer, head by head, query tiles in ascending order (`spans`, optional: where each head's lie).
+// band_rows: query rows of the block-granular band's blocks, a multiple of the record's bm.
+difa_status_t collect_records(int32_t band_rows, int32_t batch, int32_t heads, const int32_t* head_plan,
+                              const int32_t* window, int32_t n_text, int32_t n_img, int32_t bm, int32_t bn, uint32_t flags,
+                              std::vector<difa_work_item_t>& recs, std::vector<HeadSpan>* spans, int32_t* copy_heads,
+                              int32_t* n_copy_out) {
+    if (!head_plan || batch < 1 || heads < 1 || n_text < 0 || n_img < 0 ||
+        bm < 1 || bn < 1 || band_rows < bm || band_rows % bm != 0 ||
         (flags & ~(uint32_t)(DIFA_FLAG_BLOCK_BAND | DIFA_FLAG_IMAGE_FIRST)) != 0)
         return DIFA_ERR_INVALID_ARG;
     const int64_t n64 = (int64_t)n_text + (int64_t)n_img;
@@ -104,10 +112,7 @@ difa_status_t worklist_build(int32_t band_rows, int32_t batch, int32_t heads, co
     // tiles that hold at least one text key: the first ones of the rotated order
     const int text_tiles = image_first ? n_kv_tiles - g.rot : (n_text + bn - 1) / bn;
 
-    // Records are first collected head by head (query tiles in ascending order).
-    struct HeadSpan { size_t first, count; int64_t cost; };
-    std::vector<difa_work_item_t> recs;
-    std::vector<HeadSpan> spans;
+    recs.clear();
     int n_copy = 0;
     for (int b = 0; b < batch; ++b) {
         for (int h = 0; h < heads; ++h) {
@@ -172,9 +177,26 @@ difa_status_t worklist_build(int32_t band_rows, int32_t batch, int32_t heads, co
                 span.cost += r.n_tiles;
             }
             span.count = recs.size() - span.first;
-            spans.push_back(span);
+            if (spans) spans->push_back(span);
         }
     }
+    *n_copy_out = n_copy;
+    return DIFA_OK;
+}
+
+difa_status_t worklist_build(int32_t batch, int32_t heads, const int32_t* head_plan,
+                             const int32_t* window, int32_t n_text, int32_t n_img,
+                             int32_t bm, int32_t bn, int32_t n_xcd, uint32_t flags,
+                             difa_work_item_t* items,
+                             int32_t capacity, int32_t* n_items_out,
+                             int32_t* copy_heads, int32_t* n_copy_out) {
+    if (!n_items_out || n_xcd < 1 || n_xcd > 64 || capacity < 0 || (capacity > 0 && !items)) return DIFA_ERR_INVALID_ARG;
+    std::vector<difa_work_item_t> recs;
+    std::vector<HeadSpan> spans;
+    int32_t n_copy = 0;
+    const difa_status_t st = collect_records(bm, batch, heads, head_plan, window, n_text, n_img, bm, bn, flags, recs, &spans,
+                                             copy_heads, &n_copy);
+    if (st != DIFA_OK) return st;
     if (n_xcd == 1) {
         // Heaviest records first: the hardware hands workgroups out in index order, so the long
         // full-attention tiles start early and the short band tiles fill the tail.
@@ -235,7 +257,7 @@ extern "C" difa_status_t difa_worklist_build(int32_t batch, int32_t heads, const
                                              int32_t capacity, int32_t* n_items_out,
                                              int32_t* copy_heads, int32_t* n_copy_out) {
     try {
-        return worklist_build(bm, batch, heads, head_plan, window, n_text, n_img, bm, bn, n_xcd, flags, items, capacity,
+        return worklist_build(batch, heads, head_plan, window, n_text, n_img, bm, bn, n_xcd, flags, items, capacity,
                               n_items_out, copy_heads, n_copy_out);
     } catch (const std::bad_alloc&) {
         return DIFA_ERR_ALLOC;
@@ -244,14 +266,10 @@ extern "C" difa_status_t difa_worklist_build(int32_t batch, int32_t heads, const
 
 difa_status_t difa::worklist_for_kernel(int32_t batch, int32_t heads, const int32_t* head_plan, const int32_t* window,
                                         int32_t n_text, int32_t n_img, int32_t rows, int32_t band_rows, int32_t bn,
-                                        uint32_t flags, difa_work_item_t* items, int32_t capacity, int32_t* n_items_out,
-                                        int32_t* copy_heads, int32_t* n_copy_out) {
-    try {
-        return worklist_build(band_rows, batch, heads, head_plan, window, n_text, n_img, rows, bn, 1, flags, items, capacity,
-                              n_items_out, copy_heads, n_copy_out);
-    } catch (const std::bad_alloc&) {
-        return DIFA_ERR_ALLOC;
-    }
+                                        uint32_t flags, std::vector<difa_work_item_t>& recs, int32_t* copy_heads,
+                                        int32_t* n_copy_out) {
+    return collect_records(band_rows, batch, heads, head_plan, window, n_text, n_img, rows, bn, flags, recs, nullptr,
+                           copy_heads, n_copy_out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -263,10 +281,9 @@ difa_status_t difa::worklist_for_kernel(int32_t batch, int32_t heads, const int3
 // whole records are dealt out, costliest first, to the least loaded workgroup of their die (which keeps
 // the workgroups of a die on neighbouring query tiles of one head, marching through its K/V together),
 // and the records that no longer fit under a target load are cut along their key-tile positions into
-// pieces that fill the workgroups up to it.  The target is found by a few dry runs (a cut costs a
-// good part of a short record, so how much load there is depends on how much is cut); for layers of few,
-// long records, filling the workgroups one after the other, or not cutting at all, is tried as well, and
-// the plan with the earliest predicted finish is kept.
+// pieces that fill the workgroups up to it.  A few targets above the mean load are tried.  A plan that its caller has not used lately is compiled while that
+// caller waits, so the search works on loads and indices (a heap of the workgroups' loads, the part that
+// every target has in common done once), and segments are written out for the plan that is kept only.
 // ------------------------------------------------------------------------------------------
 namespace {
 
@@ -294,6 +311,17 @@ int64_t tiles_cost(const CostModel& m, const difa_work_item_t& r, int p0, int p1
 }
 int64_t whole_cost(const CostModel& m, const difa_work_item_t& r) { return tiles_cost(m, r, 0, r.n_tiles) + m.whole; }
 
+// Positions of r from p0 on (at most `most`) whose iterations cost no more than `room` units.
+int tiles_within(const CostModel& m, const difa_work_item_t& r, int p0, int most, int64_t room) {
+    int lo = 0, hi = (int)std::min<int64_t>(most, room / kUnit);
+    if (tiles_cost(m, r, p0, p0 + hi) <= room) return hi;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) / 2;
+        if (tiles_cost(m, r, p0, p0 + mid) <= room) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 difa_segment_t whole_segment(const difa_work_item_t& r) {
     difa_segment_t s{};
     s.bh = r.bh; s.q_tile = r.q_tile;
@@ -310,230 +338,214 @@ difa_segment_t whole_segment(const difa_work_item_t& r) {
     return s;
 }
 
-// One die's share of the schedule.  A dry run fills in the loads and counts only.
-struct DiePlan {
-    std::vector<std::vector<difa_segment_t>> lists;   // a segment list per workgroup, slots numbered from 0
-    std::vector<difa_merge_item_t> merges;
-    std::vector<int64_t> load;
-    int n_slots = 0;
-    int most_parts = 1;
-    int64_t makespan = 0, total = 0;
+// Workgroups by load: a binary heap, the least loaded on top (the lower number among equals).
+class LoadHeap {
+public:
+    void reset(int n) {
+        at_.resize((size_t)n);
+        for (int i = 0; i < n; ++i) at_[(size_t)i] = {0, i};
+    }
+    bool empty() const { return at_.empty(); }
+    int top() const { return at_[0].second; }
+    int64_t least() const { return at_[0].first; }
+    void add_to_top(int64_t c) {
+        std::pair<int64_t, int> x = at_[0];
+        x.first += c;
+        sink(x);
+    }
+    void pop() {
+        const std::pair<int64_t, int> x = at_.back();
+        at_.pop_back();
+        if (!at_.empty()) sink(x);
+    }
+    int64_t most() const {
+        int64_t m = 0;
+        for (const auto& e : at_) m = std::max(m, e.first);
+        return m;
+    }
+
+private:
+    void sink(const std::pair<int64_t, int>& x) {       // x takes the place of the top
+        const size_t n = at_.size();
+        size_t i = 0;
+        for (;;) {
+            size_t k = 2 * i + 1;
+            if (k >= n) break;
+            if (k + 1 < n && at_[k + 1] < at_[k]) ++k;
+            if (!(at_[k] < x)) break;
+            at_[i] = at_[k];
+            i = k;
+        }
+        at_[i] = x;
+    }
+    std::vector<std::pair<int64_t, int>> at_;
 };
 
-struct Piece { int wg, pos_begin, pos_end; };
+struct Placed { int wg, rec, pos_begin, pos_end; bool poured; };
 
-void finish_record(const CostModel& m, DiePlan& plan, const difa_work_item_t& r, const std::vector<Piece>& pieces, bool dry) {
-    const int n = (int)pieces.size();
-    plan.most_parts = std::max(plan.most_parts, n);
-    if (n > 1) {
-        // the pieces were charged piece_expected() each; put the fold at what this record's piece count makes it
-        const int64_t fold = (int64_t)m.fold * (n - 1) / n - m.fold / 2;
-        for (const Piece& pc : pieces) plan.load[(size_t)pc.wg] += fold;
-    }
-    if (dry) {
-        if (n > 1) plan.n_slots += n;
-        return;
-    }
-    const int first_slot = plan.n_slots;
-    for (const Piece& pc : pieces) {
-        difa_segment_t s = whole_segment(r);
-        s.pos_begin = pc.pos_begin;
-        s.pos_end = pc.pos_end;
-        if (n > 1) {
-            s.first_slot = first_slot;
-            s.part_slot = plan.n_slots++;
-            s.merge_idx = (int32_t)plan.merges.size();
-            s.n_parts = n;
+// One die's share of the schedule.
+struct DiePlan {
+    std::vector<Placed> placed;        // in the order they were placed; the pieces of a record stand together
+    int n_slots = 0;                   // pieces of cut records
+    int64_t makespan = 0;
+};
+
+// A die's records in order of decreasing cost, and the dealing of them.
+struct Die {
+    const CostModel& m;
+    const std::vector<difa_work_item_t>& recs;
+    const std::vector<std::pair<int64_t, int>>& order;     // (cost, index into recs)
+    int64_t total;                                          // their cost
+    int per_die, slot_budget;
+
+    // Whole records only, each to the least loaded workgroup.
+    void deal_whole(LoadHeap& heap, DiePlan& plan) const {
+        heap.reset(per_die);
+        plan.placed.clear();
+        plan.n_slots = 0;
+        for (const auto& o : order) {
+            plan.placed.push_back({heap.top(), o.second, 0, recs[(size_t)o.second].n_tiles, false});
+            heap.add_to_top(o.first);
         }
-        plan.lists[(size_t)pc.wg].push_back(s);
+        plan.makespan = heap.most();
     }
-    if (n > 1) plan.merges.push_back(difa_merge_item_t{r.bh, r.q_tile, first_slot, n});
-}
 
-void close_plan(DiePlan& plan) {
-    plan.makespan = *std::max_element(plan.load.begin(), plan.load.end());
-    plan.total = 0;
-    for (int64_t l : plan.load) plan.total += l;
-}
-
-// Records in order of decreasing cost.  A record goes whole to the least loaded workgroup (so neighbouring
-// query tiles of a head run side by side and share its K/V tiles in the die's L2) as long as that leaves the
-// workgroup room for another half of it; otherwise it is poured: laid into the room of the workgroup that is
-// being filled, cut where that room ends, the rest into the room of the workgroup that is then the least
-// loaded, and so on.  Rooms are therefore of the order of a record when long records are cut (two or three
-// pieces each, so the workgroup that folds them together at the end reads one or two slots, not ten), and
-// short records, which are not worth cutting, fill the gaps that remain.
-DiePlan deal_and_pour(const CostModel& m, const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
-                      int64_t target, int slot_budget, bool dry) {
-    DiePlan plan;
-    if (!dry) plan.lists.resize((size_t)per_die);
-    plan.load.assign((size_t)per_die, 0);
-    std::vector<int64_t>& load = plan.load;
-    auto least = [&]() { return (int)(std::min_element(load.begin(), load.end()) - load.begin()); };
-    std::vector<Piece> pieces;
-    std::vector<size_t> n_whole((size_t)per_die, 0);
-    std::vector<char> poured((size_t)per_die, 0);
-    int cur = -1;
-    auto room_of = [&](int w) { return (target - load[(size_t)w] - piece_expected(m)) / kUnit; };   // in key tiles
-    for (size_t i = 0; i < q.size(); ++i) {
-        const difa_work_item_t& r = q[i];
-        const int64_t c = cost[i];
-        const int lw = least();
-        if (load[(size_t)lw] + c + c / 2 <= target) {
-            load[(size_t)lw] += c;
-            if (!dry) plan.lists[(size_t)lw].push_back(whole_segment(r));
-            if (!poured[(size_t)lw]) ++n_whole[(size_t)lw];
-            continue;
-        }
-        pieces.clear();
-        int pos = 0;
-        while (pos < r.n_tiles) {
-            if (cur < 0 || room_of(cur) < m.min_piece) cur = least();
-            const int w = cur;
-            const int remaining = r.n_tiles - pos;
-            const int64_t room = room_of(w);
-            int take = remaining;
-            const bool may_cut = plan.n_slots + (int)pieces.size() + 2 <= slot_budget;
-            if (pos == 0 && load[(size_t)w] + c <= target) {
-                // the whole record fits
-            } else if (may_cut && room >= m.min_piece && room < remaining) {
-                take = (int)room;
-                if (remaining - take < m.min_piece) take = remaining - m.min_piece >= m.min_piece ? remaining - m.min_piece : remaining;
-            } else if (may_cut && room < m.min_piece && remaining >= 4 * m.min_piece) {
-                // no room anywhere (the target was too low): spread what is left over the least loaded
-                // workgroups in pieces of two to four times the shortest one, rather than on one of them
-                const int n = (remaining + 3 * m.min_piece - 1) / (3 * m.min_piece);
-                take = (remaining + n - 1) / n;
+    // A record goes whole to the least loaded workgroup (so neighbouring query tiles of a head run side by side and
+    // share its K/V tiles in the die's L2) as long as that leaves the workgroup room for `spare` sixteenths more of
+    // it; otherwise it is poured: laid into the room of the workgroup that is being filled, cut where that room ends,
+    // the rest into the room of the workgroup that is then the least loaded, and so on.  With spare = 8 rooms are
+    // of the order of a record when long records are cut (two or three pieces each, so the workgroup that folds them
+    // together at the end reads one or two slots, not ten), and short records fill the gaps that remain.
+    // [first, ...) are the records to deal; the heap and the plan hold what came before.  Returns false, with the plan
+    // unfinished, when the records do not go in under the target.
+    bool deal_and_pour(LoadHeap& heap, DiePlan& plan, size_t first, int64_t target, int spare) const {
+        int cur = -1;                                                // the workgroup being filled, no longer in the heap
+        int64_t cur_load = 0, most = 0;
+        int64_t slack = target * per_die - total;                    // what closed rooms and cuts may waste
+        for (size_t i = first; i < order.size(); ++i) {
+            const int rec = order[i].second;
+            const difa_work_item_t& r = recs[(size_t)rec];
+            const int64_t c = order[i].first;
+            if (!heap.empty() && heap.least() + c + c * spare / 16 <= target) {
+                plan.placed.push_back({heap.top(), rec, 0, r.n_tiles, false});
+                heap.add_to_top(c);
+                continue;
             }
-            pieces.push_back(Piece{w, pos, pos + take});
-            load[(size_t)w] += tiles_cost(m, r, pos, pos + take) + (take == r.n_tiles ? m.whole : piece_expected(m));
-            poured[(size_t)w] = 1;
-            pos += take;
+            const size_t piece_begin = plan.placed.size();
+            int64_t dearest = 0;                                     // most loaded of the workgroups that take a piece
+            int pos = 0;
+            while (pos < r.n_tiles) {
+                if (cur < 0 || target - cur_load - piece_expected(m) < (int64_t)kUnit * m.min_piece) {
+                    // (the room left is too small for a piece; a short record may still fit whole)
+                    if (cur >= 0 && pos == 0 && cur_load + c <= target) {
+                        plan.placed.push_back({cur, rec, 0, r.n_tiles, true});
+                        cur_load += c;
+                        pos = r.n_tiles;
+                        break;
+                    }
+                    if (cur >= 0) slack -= target - cur_load;
+                    if (heap.empty() || slack < 0) return false;
+                    most = std::max(most, cur_load);
+                    cur = heap.top();
+                    cur_load = heap.least();
+                    heap.pop();
+                }
+                const int remaining = r.n_tiles - pos;
+                const int64_t room = target - cur_load - piece_expected(m);
+                const int64_t rest = tiles_cost(m, r, pos, r.n_tiles);
+                int take = remaining;
+                if (pos == 0 && cur_load + c <= target) {
+                    // the whole record fits
+                } else if (rest > room) {
+                    if (plan.n_slots + (int)(plan.placed.size() - piece_begin) + 2 > slot_budget) return false;
+                    take = room > 0 ? tiles_within(m, r, pos, remaining, room) : 0;
+                    if (remaining - take < m.min_piece) take = remaining - m.min_piece;
+                    if (take < m.min_piece) {                        // (room for less than a piece of masked tiles)
+                        most = std::max(most, cur_load);
+                        slack -= target - cur_load;
+                        cur = -1;
+                        continue;
+                    }
+                }
+                plan.placed.push_back({cur, rec, pos, pos + take, true});
+                cur_load += tiles_cost(m, r, pos, pos + take) + (take == r.n_tiles ? m.whole : piece_expected(m));
+                dearest = std::max(dearest, cur_load);
+                pos += take;
+            }
+            const int n = (int)(plan.placed.size() - piece_begin);
+            if (n > 1) {
+                plan.n_slots += n;
+                slack -= (int64_t)n * piece_expected(m) - m.whole;
+                // the pieces were charged half a fold each; with many pieces each one's share comes to more
+                most = std::max(most, dearest + (int64_t)m.fold * (n - 1) / n - m.fold / 2);
+            }
         }
-        finish_record(m, plan, r, pieces, dry);
+        plan.makespan = std::max(std::max(most, cur_load), heap.most());
+        return true;
     }
-    // A poured room holds the tail of one record and the head of the next one, neighbouring query tiles of
-    // one head as a rule.  Run in the order of their first key position (the shorter one first among equals),
-    // the workgroups of the die walk through that head's K/V within a fraction of a record of each other and
-    // share the tiles in the die's L2, as they do on whole records; the pieces of a record may finish in any
-    // order, since the last one to arrive folds them.
-    if (!dry)
-        for (int w = 0; w < per_die; ++w) {
-            auto& l = plan.lists[(size_t)w];
-            std::stable_sort(l.begin() + (std::ptrdiff_t)n_whole[(size_t)w], l.end(),
-                             [](const difa_segment_t& a, const difa_segment_t& b) {
-                                 return a.pos_begin != b.pos_begin ? a.pos_begin < b.pos_begin
-                                                                   : a.pos_end - a.pos_begin < b.pos_end - b.pos_begin;
-                             });
+
+    // The best plan a few target loads give.
+    DiePlan schedule() const {
+        DiePlan best;
+        if (order.empty()) return best;
+        LoadHeap heap;
+        deal_whole(heap, best);
+        const int64_t mean = (total + per_die - 1) / per_die;
+        DiePlan begun, plan;
+        LoadHeap start;
+        for (const int spare : {8, 0}) {
+            if (best.makespan * 64 <= mean * 65) break;               // within 1.5 % of what no plan can beat
+            // Every target from the mean load on deals the first records alike: as long as the least loaded
+            // workgroup stays below the mean with the record and its spare room.
+            start.reset(per_die);
+            begun.placed.clear();
+            size_t first = 0;
+            while (first < order.size() && start.least() + order[first].first + order[first].first * spare / 16 <= mean) {
+                begun.placed.push_back({start.top(), order[first].second, 0, recs[(size_t)order[first].second].n_tiles, false});
+                start.add_to_top(order[first].first);
+                ++first;
+            }
+            // Targets from just above the mean load up; the first one that holds everything is the plan.  How far up it
+            // lies depends on how many cuts it takes: none of them costs more than `cut`, and a plan has about one for
+            // every other workgroup.
+            const int64_t cut = 2 * piece_expected(m) - m.whole;
+            for (const int64_t above : {cut / 8, cut / 3, 2 * cut / 3, cut, 3 * cut / 2}) {
+                const int64_t target = mean + above;
+                if (target >= best.makespan) break;
+                // (every record longer than the target has to be cut)
+                const int64_t longer = std::partition_point(order.begin(), order.end(), [&](const std::pair<int64_t, int>& o) {
+                    return o.first > target; }) - order.begin();
+                if (longer * cut > (target - mean) * per_die) continue;
+                heap = start;
+                plan.placed = begun.placed;
+                plan.n_slots = 0;
+                if (!deal_and_pour(heap, plan, first, target, spare)) continue;
+                if (plan.makespan < best.makespan) std::swap(best, plan);
+                break;
+            }
+            if (best.makespan * 100 <= mean * 104) break;
         }
-    close_plan(plan);
-    return plan;
-}
-
-// The records laid end to end and handed out in runs of the target cost: workgroup 0 is filled, then
-// workgroup 1, ...; a record that crosses a boundary is cut there.
-DiePlan fill_in_order(const CostModel& m, const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die,
-                      int64_t target, int slot_budget, bool dry) {
-    DiePlan plan;
-    if (!dry) plan.lists.resize((size_t)per_die);
-    plan.load.assign((size_t)per_die, 0);
-    std::vector<int64_t>& load = plan.load;
-    std::vector<Piece> pieces;
-    int w = 0;
-    for (size_t i = 0; i < q.size(); ++i) {
-        const difa_work_item_t& r = q[i];
-        pieces.clear();
-        int pos = 0;
-        if (w < per_die - 1 && load[(size_t)w] > 0 && load[(size_t)w] + cost[i] > target &&
-            (target - load[(size_t)w] - piece_expected(m)) / kUnit < m.min_piece)
-            ++w;                                                      // no room worth a piece: the next workgroup goes on
-        while (pos < r.n_tiles) {
-            const int remaining = r.n_tiles - pos;
-            const int64_t ovh = pos == 0 ? m.whole : piece_expected(m);
-            int take = remaining;
-            if (w < per_die - 1 && load[(size_t)w] + tiles_cost(m, r, pos, r.n_tiles) + ovh > target) {
-                const int64_t room = (target - load[(size_t)w] - piece_expected(m)) / kUnit;   // in key tiles
-                const bool may_cut = plan.n_slots + (int)pieces.size() + 2 <= slot_budget;
-                if (may_cut && room >= m.min_piece && remaining - room >= m.min_piece) take = (int)room;
-                else if (may_cut && room >= m.min_piece && remaining - m.min_piece >= m.min_piece) take = remaining - m.min_piece;
-                else if (load[(size_t)w] > 0 && pos == 0) { ++w; continue; }   // rather start it on the next workgroup
-            }                                                         // else: overfill
-            pieces.push_back(Piece{w, pos, pos + take});
-            load[(size_t)w] += tiles_cost(m, r, pos, pos + take) + (take == r.n_tiles ? m.whole : piece_expected(m));
-            pos += take;
-            if (pos < r.n_tiles && w < per_die - 1) ++w;              // cut: the rest starts the next workgroup
-        }
-        finish_record(m, plan, r, pieces, dry);
+        return best;
     }
-    close_plan(plan);
-    return plan;
-}
+};
 
-// The smallest target a method gets along with: too low a target leaves work over that lands on one
-// workgroup, too high a one leaves the last workgroups idle.  A few dry runs, each aiming just above the mean
-// load of the one before (the mean moves little: only the number of pieces changes it).
-template <class Run>
-int64_t settle_target(int64_t first, int per_die, Run run) {
-    int64_t target = first, best_target = first, best_span = -1;
-    for (int round = 0; round < 3; ++round) {
-        const DiePlan p = run(target, true);
-        if (best_span < 0 || p.makespan < best_span) { best_span = p.makespan; best_target = target; }
-        const int64_t mean = (p.total + per_die - 1) / per_die;
-        int64_t next;
-        if (p.makespan > target + target / 128) next = target + std::max<int64_t>(kUnit, (p.makespan - target) / 8);   // work was left over
-        else next = mean + kUnit;                                    // it all went in: aim just above the mean load
-        if (next == target || (p.makespan <= target + target / 128 && next > target)) break;
-        target = next;
-    }
-    return best_target;
-}
-
-// Whole records only, each to the least loaded workgroup: the plan to beat when records are few and a cut
-// costs a good part of a record.
-DiePlan deal_whole(const std::vector<difa_work_item_t>& q, const std::vector<int64_t>& cost, int per_die, bool dry) {
-    DiePlan plan;
-    if (!dry) plan.lists.resize((size_t)per_die);
-    plan.load.assign((size_t)per_die, 0);
-    for (size_t i = 0; i < q.size(); ++i) {
-        const int w = (int)(std::min_element(plan.load.begin(), plan.load.end()) - plan.load.begin());
-        plan.load[(size_t)w] += cost[i];
-        if (!dry) plan.lists[(size_t)w].push_back(whole_segment(q[i]));
-    }
-    close_plan(plan);
-    return plan;
-}
-
-difa_status_t schedule_build(const CostModel& m, const difa_work_item_t* items, int32_t n_items, int32_t n_wg,
+difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_item_t>& recs, int32_t n_wg,
                              int32_t n_xcd, const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                              int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out, difa_merge_item_t* merges,
                              int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out) {
-    if (n_items < 0 || (n_items > 0 && !items) || n_wg < 1 || n_xcd < 1 || n_wg % n_xcd != 0 || !wg_begin ||
-        !n_segs_out || !n_merges_out || !n_slots_out || seg_capacity < 0 || merge_capacity < 0 ||
-        (seg_capacity > 0 && !segs) || (merge_capacity > 0 && !merges))
-        return DIFA_ERR_INVALID_ARG;
-    std::vector<difa_work_item_t> recs;
-    for (int32_t i = 0; i < n_items; ++i) {
-        if (items[i].q_tile < 0) continue;
-        if (items[i].n_tiles < 1) return DIFA_ERR_INVALID_ARG;
-        recs.push_back(items[i]);
-    }
-    std::stable_sort(recs.begin(), recs.end(), [](const difa_work_item_t& a, const difa_work_item_t& b) {
-        return a.bh != b.bh ? a.bh < b.bh : a.q_tile < b.q_tile;
-    });
     // heads in order of decreasing cost, the whole sequence cut into n_xcd runs whose costs are in
     // proportion to the dies' speeds (equal when none are given)
-    struct HeadSpan { size_t first, count; int64_t cost; };
     std::vector<HeadSpan> spans;
+    std::vector<int64_t> cost(recs.size());
+    int64_t total = 0;
     for (size_t i = 0; i < recs.size();) {
-        size_t j = i;
-        int64_t cost = 0;
-        while (j < recs.size() && recs[j].bh == recs[i].bh) { cost += whole_cost(m, recs[j]); ++j; }
-        spans.push_back({i, j - i, cost});
-        i = j;
+        HeadSpan sp{i, 0, 0};
+        for (; i < recs.size() && recs[i].bh == recs[sp.first].bh; ++i) sp.cost += cost[i] = whole_cost(m, recs[i]);
+        sp.count = i - sp.first;
+        total += sp.cost;
+        spans.push_back(sp);
     }
     std::stable_sort(spans.begin(), spans.end(), [](const HeadSpan& a, const HeadSpan& b) { return a.cost > b.cost; });
-    int64_t total = 0;
-    for (const HeadSpan& sp : spans) total += sp.cost;
     const int per_die = n_wg / n_xcd;
     const int slot_capacity = 2 * n_wg;
     std::vector<double> speed((size_t)n_xcd, 1.0);         // relative speeds of the dies (their clocks differ under load)
@@ -541,8 +553,9 @@ difa_status_t schedule_build(const CostModel& m, const difa_work_item_t* items, 
         for (int x = 0; x < n_xcd; ++x) speed[(size_t)x] = die_speed[x] > 0.5 && die_speed[x] < 2.0 ? die_speed[x] : 1.0;
     std::vector<double> share(speed);                      // the part of the work each die is given, up to a common factor
     std::vector<DiePlan> plans((size_t)n_xcd), first_plans;
+    std::vector<std::vector<std::pair<int64_t, int>>> die((size_t)n_xcd);
+    std::vector<int64_t> die_cost((size_t)n_xcd);
     double first_t_max = 0.0;
-    std::vector<int64_t> cost;
     // Two rounds at most: the first hands out the work in proportion to the dies' speeds; where the plans that
     // come out of it would finish more than three hundredths apart (a die whose records had to be cut carries the
     // overhead of the cuts), the shares are corrected by that and the plans made again, and kept if they are better.
@@ -554,52 +567,27 @@ difa_status_t schedule_build(const CostModel& m, const difa_work_item_t* items, 
             for (int x = 0; x < n_xcd; ++x) upto[(size_t)x + 1] = upto[(size_t)x] + share[(size_t)x] / sum;
             upto[(size_t)n_xcd] = 2.0;
         }
-        std::vector<std::vector<difa_work_item_t>> die((size_t)n_xcd);
+        for (auto& d : die) d.clear();
+        std::fill(die_cost.begin(), die_cost.end(), 0);
         int64_t cum = 0;
         int x_at = 0;
         for (const HeadSpan& sp : spans)
-            for (size_t k = 0; k < sp.count; ++k) {
-                const difa_work_item_t& r = recs[sp.first + k];
-                const int64_t c = whole_cost(m, r);
-                const double mid = total > 0 ? (double)(2 * cum + c) / (double)(2 * total) : 0.0;
+            for (size_t k = sp.first; k < sp.first + sp.count; ++k) {
+                const double mid = total > 0 ? (double)(2 * cum + cost[k]) / (double)(2 * total) : 0.0;
                 while (x_at < n_xcd - 1 && mid >= upto[(size_t)x_at + 1]) ++x_at;
-                die[(size_t)x_at].push_back(r);
-                cum += c;
+                die[(size_t)x_at].push_back({cost[k], (int)k});
+                die_cost[(size_t)x_at] += cost[k];
+                cum += cost[k];
             }
         int slots_so_far = 0;
         for (int x = 0; x < n_xcd; ++x) {
-            std::vector<difa_work_item_t>& q = die[(size_t)x];
             // costliest records first (a query tile that holds text rows visits every key tile); the interior
             // query tiles of a head cost the same and stay neighbours
-            {
-                std::vector<std::pair<int64_t, int>> key(q.size());
-                for (size_t i = 0; i < q.size(); ++i) key[i] = {-whole_cost(m, q[i]), (int)i};
-                std::sort(key.begin(), key.end());                   // (ties keep their order: the index decides)
-                std::vector<difa_work_item_t> sorted(q.size());
-                cost.resize(q.size());
-                for (size_t i = 0; i < q.size(); ++i) { sorted[i] = q[(size_t)key[i].second]; cost[i] = -key[i].first; }
-                q.swap(sorted);
-            }
-            int64_t die_cost = 0;
-            for (size_t i = 0; i < q.size(); ++i) die_cost += cost[i];
+            std::stable_sort(die[(size_t)x].begin(), die[(size_t)x].end(),
+                             [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) { return a.first > b.first; });
             const int budget = slot_capacity - slots_so_far - 2 * per_die * (n_xcd - 1 - x);   // this die's share of the slots
-            // every workgroup is expected to take one piece
-            const int64_t first = (die_cost + (int64_t)per_die * piece_expected(m) + per_die - 1) / per_die;
-            auto deal = [&](int64_t t, bool dry) { return deal_and_pour(m, q, cost, per_die, t, budget, dry); };
-            auto fill = [&](int64_t t, bool dry) { return fill_in_order(m, q, cost, per_die, t, budget, dry); };
-            DiePlan dealt = deal(settle_target(first, per_die, deal), false);
-            // When the records are few and long compared with a workgroup's share (small layers), dealing whole
-            // records and cutting the rest leaves the workgroups uneven; filling them one after the other may
-            // then be the better plan, or not cutting at all.
-            const int64_t even = die_cost / per_die;
-            if (dealt.makespan * 20 > even * 21) {
-                DiePlan filled = fill(settle_target(first, per_die, fill), false);
-                if (filled.makespan < dealt.makespan) dealt = std::move(filled);
-                const DiePlan whole = deal_whole(q, cost, per_die, true);
-                if (whole.makespan * 50 <= dealt.makespan * 51) dealt = deal_whole(q, cost, per_die, false);
-            }
-            slots_so_far += dealt.n_slots;
-            plans[(size_t)x] = std::move(dealt);
+            plans[(size_t)x] = Die{m, recs, die[(size_t)x], die_cost[(size_t)x], per_die, budget}.schedule();
+            slots_so_far += plans[(size_t)x].n_slots;
         }
         // predicted finishing times, in cost units of a die of speed 1
         double t_min = 0.0, t_max = 0.0, t_sum = 0.0;
@@ -617,38 +605,66 @@ difa_status_t schedule_build(const CostModel& m, const difa_work_item_t* items, 
         for (int x = 0; x < n_xcd; ++x)
             share[(size_t)x] *= (t_sum / n_xcd) / ((double)plans[(size_t)x].makespan / speed[(size_t)x]);
         first_t_max = t_max;
-        first_plans = plans;
+        first_plans = std::move(plans);
+        plans.assign((size_t)n_xcd, DiePlan());
     }
-    std::vector<std::vector<difa_segment_t>> lists((size_t)n_wg);
-    std::vector<difa_merge_item_t> merge_list;
-    int n_slots = 0;
-    for (int x = 0; x < n_xcd; ++x) {
-        const DiePlan& dealt = plans[(size_t)x];
-        if (die_span) die_span[x] = dealt.makespan;
-        for (int w = 0; w < per_die; ++w)
-            for (difa_segment_t sg : dealt.lists[(size_t)w]) {
-                if (sg.part_slot >= 0) { sg.part_slot += n_slots; sg.first_slot += n_slots; sg.merge_idx += (int32_t)merge_list.size(); }
-                lists[(size_t)(w * n_xcd + x)].push_back(sg);
-            }
-        for (difa_merge_item_t cut : dealt.merges) {
-            cut.first_slot += n_slots;
-            merge_list.push_back(cut);
-        }
-        n_slots += dealt.n_slots;
+
+    // ---- the plans written out: segments grouped by workgroup (workgroup w of die x is number w * n_xcd + x)
+    int64_t n_segs = 0, n_slots = 0, n_merges = 0;
+    for (const DiePlan& p : plans) {
+        n_segs += (int64_t)p.placed.size();
+        n_slots += p.n_slots;
+        for (size_t i = 0; i < p.placed.size(); ++i)
+            n_merges += p.placed[i].pos_begin == 0 && p.placed[i].pos_end < recs[(size_t)p.placed[i].rec].n_tiles;
     }
-    int64_t n_segs = 0;
-    for (const auto& l : lists) n_segs += (int64_t)l.size();
     *n_segs_out = (int32_t)n_segs;
-    *n_merges_out = (int32_t)merge_list.size();
-    *n_slots_out = n_slots;
-    if (n_segs > seg_capacity || (int64_t)merge_list.size() > merge_capacity) return DIFA_ERR_ALLOC;
-    int32_t at = 0;
-    for (int w = 0; w < n_wg; ++w) {
-        wg_begin[w] = at;
-        for (const difa_segment_t& s : lists[(size_t)w]) segs[at++] = s;
+    *n_merges_out = (int32_t)n_merges;
+    *n_slots_out = (int32_t)n_slots;
+    if (n_segs > seg_capacity || n_merges > merge_capacity) return DIFA_ERR_ALLOC;
+    std::fill(wg_begin, wg_begin + n_wg + 1, 0);
+    for (int x = 0; x < n_xcd; ++x) {
+        if (die_span) die_span[x] = plans[(size_t)x].makespan;
+        for (const Placed& pl : plans[(size_t)x].placed) ++wg_begin[pl.wg * n_xcd + x + 1];
     }
-    wg_begin[n_wg] = at;
-    std::copy(merge_list.begin(), merge_list.end(), merges);
+    for (int w = 0; w < n_wg; ++w) wg_begin[w + 1] += wg_begin[w];
+    std::vector<int32_t> at(wg_begin, wg_begin + n_wg);              // next free place of each workgroup
+    std::vector<int32_t> poured_from((size_t)n_wg, -1);              // where its poured segments begin
+    int32_t slot = 0, merge = 0;
+    for (int x = 0; x < n_xcd; ++x) {
+        const std::vector<Placed>& placed = plans[(size_t)x].placed;
+        for (size_t i = 0; i < placed.size();) {
+            size_t j = i + 1;                                        // placed[i, j): one record
+            const difa_work_item_t& r = recs[(size_t)placed[i].rec];
+            while (j < placed.size() && placed[j].rec == placed[i].rec) ++j;
+            const int n = (int)(j - i), first_slot = slot;
+            for (; i < j; ++i) {
+                const int w = placed[i].wg * n_xcd + x;
+                if (placed[i].poured && poured_from[(size_t)w] < 0) poured_from[(size_t)w] = at[(size_t)w];
+                difa_segment_t& s = segs[at[(size_t)w]++];
+                s = whole_segment(r);
+                s.pos_begin = placed[i].pos_begin;
+                s.pos_end = placed[i].pos_end;
+                if (n > 1) {
+                    s.first_slot = first_slot;
+                    s.part_slot = slot++;
+                    s.merge_idx = merge;
+                    s.n_parts = n;
+                }
+            }
+            if (n > 1) merges[merge++] = difa_merge_item_t{r.bh, r.q_tile, first_slot, n};
+        }
+    }
+    // A poured room holds the tail of one record and the head of the next one, neighbouring query tiles of
+    // one head as a rule.  Run in the order of their first key position (the shorter one first among equals),
+    // the workgroups of the die walk through that head's K/V within a fraction of a record of each other and
+    // share the tiles in the die's L2, as they do on whole records; the pieces of a record may finish in any
+    // order, since the last one to arrive folds them.
+    for (int w = 0; w < n_wg; ++w)
+        if (poured_from[(size_t)w] >= 0)
+            std::stable_sort(segs + poured_from[(size_t)w], segs + wg_begin[w + 1], [](const difa_segment_t& a, const difa_segment_t& b) {
+                return a.pos_begin != b.pos_begin ? a.pos_begin < b.pos_begin
+                                                  : a.pos_end - a.pos_begin < b.pos_end - b.pos_begin;
+            });
     return DIFA_OK;
 }
 }  // namespace
@@ -657,25 +673,32 @@ extern "C" difa_status_t difa_schedule_build(const difa_work_item_t* items, int3
                                              int32_t n_xcd, difa_segment_t* segs, int32_t seg_capacity,
                                              int32_t* wg_begin, int32_t* n_segs_out, difa_merge_item_t* merges,
                                              int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out) {
+    if (n_items < 0 || (n_items > 0 && !items) || n_wg < 1 || n_xcd < 1 || n_wg % n_xcd != 0 || !wg_begin ||
+        !n_segs_out || !n_merges_out || !n_slots_out || seg_capacity < 0 || merge_capacity < 0 ||
+        (seg_capacity > 0 && !segs) || (merge_capacity > 0 && !merges))
+        return DIFA_ERR_INVALID_ARG;
     try {
-        return schedule_build(difa::kGenericCosts, items, n_items, n_wg, n_xcd, nullptr, nullptr, segs, seg_capacity, wg_begin, n_segs_out,
+        std::vector<difa_work_item_t> recs;
+        for (int32_t i = 0; i < n_items; ++i) {
+            if (items[i].q_tile < 0) continue;
+            if (items[i].n_tiles < 1) return DIFA_ERR_INVALID_ARG;
+            recs.push_back(items[i]);
+        }
+        std::stable_sort(recs.begin(), recs.end(), [](const difa_work_item_t& a, const difa_work_item_t& b) {
+            return a.bh != b.bh ? a.bh < b.bh : a.q_tile < b.q_tile;
+        });
+        return schedule_build(difa::kGenericCosts, recs, n_wg, n_xcd, nullptr, nullptr, segs, seg_capacity, wg_begin, n_segs_out,
                               merges, merge_capacity, n_merges_out, n_slots_out);
     } catch (const std::bad_alloc&) {
         return DIFA_ERR_ALLOC;
     }
 }
 
-// The same for the library's own calls: with the dies' relative speeds as measured on earlier launches (NULL:
-// all alike), and returning each die's predicted finishing time in the scheduler's cost units.
-difa_status_t difa::schedule_for_dies(const CostModel& m, const difa_work_item_t* items, int32_t n_items, int32_t n_wg, int32_t n_xcd,
+difa_status_t difa::schedule_for_dies(const CostModel& m, const std::vector<difa_work_item_t>& recs, int32_t n_wg, int32_t n_xcd,
                                       const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                                       int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out,
                                       difa_merge_item_t* merges, int32_t merge_capacity, int32_t* n_merges_out,
                                       int32_t* n_slots_out) {
-    try {
-        return schedule_build(m, items, n_items, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin, n_segs_out,
-                              merges, merge_capacity, n_merges_out, n_slots_out);
-    } catch (const std::bad_alloc&) {
-        return DIFA_ERR_ALLOC;
-    }
+    return schedule_build(m, recs, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin, n_segs_out,
+                          merges, merge_capacity, n_merges_out, n_slots_out);
 }
