@@ -39,7 +39,7 @@ typedef enum {
 
 enum { DIFA_HEAD_FULL = 0, DIFA_HEAD_ARROW = 1, DIFA_HEAD_CACHE = 2,
        DIFA_HEAD_ARROW_RESIDUAL = 3 /* only with difa_joint_attention_residual, see there */ };
-enum { DIFA_DTYPE_BF16 = 0, DIFA_DTYPE_F32 = 1 }; /* F32 = slow all-fp32 debug path */
+enum { DIFA_DTYPE_BF16 = 0, DIFA_DTYPE_F32 = 1 }; /* F32 = debug path: fp32 data, fp64 contractions */
 enum { DIFA_LAYOUT_BHND = 0, DIFA_LAYOUT_BNHD = 1 };
 /* Plan flags.  DIFA_FLAG_BLOCK_BAND selects the block-granular band of the paper's own kernel
  * (Sec. 3.3, Fig. 4: a block that mixes kept and discarded pairs is computed as a dense block, so
@@ -91,8 +91,7 @@ difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_plan_t** plan_
  *              sees image keys j with |i - j| <= w); ignored for other heads; may be NULL iff
  *              no head is ARROW.  w >= n_img - 1 makes the head identical to FULL.
  *   stream     hipStream_t passed as void*; NULL is the default stream.
- * The call enqueues one kernel launch on `stream` (two on the fp32 debug path when a head is cached)
- * and returns without waiting for it; host arrays may be freed on return.  Device tensors stay owned
+ * The call enqueues one kernel launch on `stream` and returns without waiting for it; host arrays may be freed on return.  Device tensors stay owned
  * by the caller and must stay valid until the stream has run the work.  Calls on one plan object
  * must not be issued from two threads at once; calls that name different streams are kept in the
  * order they were made (the later stream waits for an event on the earlier one), because they share
@@ -313,7 +312,7 @@ difa_status_t difa_plan_solve(const double* influence, const double* latency, do
  * stream; difa_plan_timing_read waits for the last bracket and returns the accumulated kernel
  * milliseconds and launch count since the last reset.  attn_ms: the call's layer kernel (on the bf16 path it
  * holds the cached-head copy as well; a bf16 layer with every head cached is one launch of the copy kernel,
- * counted here); copy_ms: the separate copy kernel of the fp32 debug path.
+ * counted here); copy_ms: 0 (kept for callers: no path has a separate copy kernel beside the layer's any more).
  */
 difa_status_t difa_plan_timing_enable(difa_plan_t* plan, int32_t enable);
 difa_status_t difa_plan_timing_read(difa_plan_t* plan, double* attn_ms, double* copy_ms,

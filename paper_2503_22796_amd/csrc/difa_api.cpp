@@ -683,6 +683,8 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             if (st != DIFA_OK) return fail(p, st, "scheduling the work list failed");
             used = lru->merges_off + (size_t)n_merges * sizeof(difa_merge_item_t);
         } else {
+            // longest records first: the hardware hands workgroups out in this order
+            std::stable_sort(p->recs.begin(), p->recs.end(), [](const difa_work_item_t& x, const difa_work_item_t& y) { return x.n_tiles > y.n_tiles; });
             lru->items_off = used;
             memcpy(hb + used, p->recs.data(), (size_t)n_items * sizeof(difa_work_item_t));
             used += (size_t)n_items * sizeof(difa_work_item_t);
@@ -712,11 +714,10 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
     const bool fast = p->desc.dtype == DIFA_DTYPE_BF16;
     const bool copies = slot->n_copy > 0 && cache != out;   // cached heads (Sec. 3.2): out[b, h] = cache[b, h]
 
-    // ---- cached heads by a copy kernel of their own: on the fp32 debug path, and for a bf16 layer that computes no
-    // head at all (the copy kernel fills the chip with many small workgroups and moves a fifth more bytes per second
+    // ---- a layer that computes no head at all: cached heads by a copy kernel of their own (it fills the chip with many small workgroups and moves a fifth more bytes per second
     // than the layer kernel's one workgroup per compute unit; it is then the call's one launch)
-    const bool copy_only = fast && copies && slot->n_items == 0;
-    if (copies && (!fast || copy_only)) {
+    const bool copy_only = copies && slot->n_items == 0;
+    if (copy_only) {
         difa::CopyArgs c{};
         c.src = cache;
         c.dst = out;
@@ -725,7 +726,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         c.batch = B; c.n_copy = slot->n_copy; c.n_tokens = N;
         c.vec_per_row = (int32_t)(D * es / 16);
         TimingPair tp{};
-        if (p->timing && (e = timing_begin(p, stream, copy_only ? 0 : 1, &tp)) != hipSuccess)
+        if (p->timing && (e = timing_begin(p, stream, 0, &tp)) != hipSuccess)
             return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
         e = difa::launch_cache_copy(c, stream);
         if (p->timing) { (void)hipEventRecord(tp.stop, stream); p->pending.push_back(tp); }
@@ -779,21 +780,27 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
                 l.sched_id = slot->sched_id;
                 memcpy(l.span, slot->die_span, sizeof l.span);
             }
-            if (copies) {
-                const int vec_per_row = (int)(D * es / 16);                 // 8 or 16: a power of two
-                int shift = 0;
-                while ((1 << shift) < vec_per_row) ++shift;
-                a.copy_src = cache;
-                a.copy_heads = (const int32_t*)slot->d_buf;
-                a.copy_stride_b = sb * (int64_t)es; a.copy_stride_h = sh * (int64_t)es; a.copy_stride_n = sn * (int64_t)es;
-                a.n_copy = slot->n_copy;
-                a.copy_vec_shift = shift;
-                a.copy_head_vecs = N << shift;
-                a.copy_chunks_per_head = (a.copy_head_vecs + difa::copy_chunk_vecs(D) - 1) / difa::copy_chunk_vecs(D);
-                const int64_t chunks = (int64_t)B * slot->n_copy * a.copy_chunks_per_head;
-                if (chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
-                a.copy_chunks = (int32_t)chunks;
-            }
+        }
+        if (copies) {
+            const int vec_per_row = (int)(D * es / 16);                     // 8, 16 or 32: a power of two
+            int shift = 0;
+            while ((1 << shift) < vec_per_row) ++shift;
+            const int64_t head_vecs = (int64_t)N << shift, chunk = fast ? difa::copy_chunk_vecs(D) : difa::kF32CopyVecs;
+            const int64_t per_head = (head_vecs + chunk - 1) / chunk, chunks = (int64_t)B * slot->n_copy * per_head;
+            if (head_vecs > INT32_MAX - chunk || chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
+            a.copy_src = cache;
+            a.copy_heads = (const int32_t*)slot->d_buf;
+            a.copy_stride_b = sb * (int64_t)es; a.copy_stride_h = sh * (int64_t)es; a.copy_stride_n = sn * (int64_t)es;
+            a.n_copy = slot->n_copy;
+            a.copy_vec_shift = shift;
+            a.copy_head_vecs = (int32_t)head_vecs;
+            a.copy_chunks_per_head = (int32_t)per_head;
+            a.copy_chunks = (int32_t)chunks;
+        }
+        if (!fast) {
+            const int64_t blocks = (int64_t)slot->n_items * (difa::kBM / difa::kF32BlockRows);
+            if (blocks + a.copy_chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many workgroups");
+            a.f32_blocks = (int32_t)blocks;
         }
         TimingPair tp{};
         if (p->timing && (e = timing_begin(p, stream, 0, &tp)) != hipSuccess)

@@ -21,13 +21,16 @@ constexpr int rows_per_wg(int head_dim) { return head_dim == 64 ? 128 : 256; }
 constexpr int wgs_per_cu(int head_dim) { return 256 / rows_per_wg(head_dim); }
 constexpr int copy_chunk_vecs(int head_dim) { return 32 * rows_per_wg(head_dim); }   // 16-byte vectors per chunk of the cached-head copy: 16 per thread
 
+constexpr int kF32BlockRows = 16;      // fp32 kernel: query rows per workgroup
+constexpr int kF32CopyVecs = 16 * 512; // ... and 16-byte vectors per chunk of its cached-head copy
+
 // Arguments common to the attention kernels.  Strides are in elements.
 struct AttnArgs {
     const void* q;
     const void* k;
     const void* v;
     void* out;
-    const difa_work_item_t* items;  // device: one record per workgroup (fp32 debug kernel)
+    const difa_work_item_t* items;  // device: one record per kBM query rows (fp32 kernel)
     const difa_segment_t* segs;     // device: segments grouped by workgroup (bf16 kernel)
     const int32_t* wg_begin;        // device: first segment of each workgroup, n_wg + 1 entries
     const difa_merge_item_t* merges;  // device: records cut into pieces
@@ -35,7 +38,7 @@ struct AttnArgs {
     float* part_ml;                 // device scratch: [slot][rows_per_wg][2] row reference (log2 domain), row sum
     int32_t* tickets;               // device, one per cut record, zero between launches: pieces finished so far
     const void* residual;           // device, shaped like out: kept differences of the residual-sharing heads (or NULL)
-    // cached heads (bf16 kernel): out[b, h] = copy_src[b, h] for the heads listed in copy_heads
+    // cached heads: out[b, h] = copy_src[b, h] for the heads listed in copy_heads
     const void* copy_src;
     const int32_t* copy_heads;      // device, n_copy entries
     int64_t copy_stride_b, copy_stride_h, copy_stride_n;   // in bytes
@@ -46,6 +49,7 @@ struct AttnArgs {
     int32_t copy_vec_shift;         // log2(16-byte vectors per token row)
     int64_t stride_b, stride_h, stride_n;
     int32_t heads, n_tokens, n_text;
+    int32_t f32_blocks;  // fp32 kernel: workgroups of the computed heads (kBM / kF32BlockRows per record); copy chunks follow
     int32_t text_begin;  // first text token: 0, or n_img when the image tokens come first
     int32_t tile_rot;    // key-tile position u of a record is tile (u + tile_rot) % n_kv_tiles
     int32_t n_kv_tiles;

@@ -2,8 +2,8 @@
 //   attn_bf16_kernel  -- the whole layer in one launch: full / arrow heads with bf16 MFMA and fp32
 //                        accumulation, then the cached heads, out[b,h] = cache[b,h] (the cache fill that
 //                        ends Alg. 1), copied by whichever workgroups have finished their attention work
-//   attn_f32_kernel   -- full / arrow heads in plain fp32 arithmetic (slow debug path)
-//   cache_copy_kernel -- cached heads of the debug path, and of a bf16 layer with every head cached
+//   attn_f32_kernel   -- the fp32 debug path: fp64 contractions on the matrix cores, fp32 exponentials; cached heads too
+//   cache_copy_kernel -- a layer with every head cached
 #include <mutex>
 #include <type_traits>
 
@@ -106,6 +106,32 @@ struct RowState {
     int lo;        // band of allowed image keys is [lo, lo + span]; text keys are always allowed
     unsigned span;
 };
+
+// One chunk of the cached-head copy: 16 vectors of 16 bytes per thread, all in flight together.
+template <int THREADS>
+__device__ __forceinline__ void copy_vectors(const AttnArgs& ca, int chunk, int tid) {
+    constexpr int PER = 16;
+    const int per_head = ca.copy_chunks_per_head, n_copy = ca.n_copy, shift = ca.copy_vec_shift;
+    const int head_vecs = ca.copy_head_vecs;
+    const int64_t row_bytes = ca.copy_stride_n;
+    const int hh = chunk / per_head, cc = chunk - hh * per_head;
+    const int bb = hh / n_copy, head = ca.copy_heads[hh - bb * n_copy];
+    const int64_t base = (int64_t)bb * ca.copy_stride_b + (int64_t)head * ca.copy_stride_h;
+    const char* __restrict__ src = (const char*)ca.copy_src + base;
+    char* __restrict__ dst = (char*)ca.out + base;
+    uintx4 val[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int vi = cc * (PER * THREADS) + u * THREADS + tid;              // vector inside the head
+        const int vr = vi < head_vecs ? vi : head_vecs - 1;                   // past the end: reread the last one, store nothing
+        val[u] = *(const uintx4*)(src + (vr >> shift) * row_bytes + (vr & ((1 << shift) - 1)) * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int vi = cc * (PER * THREADS) + u * THREADS + tid;
+        if (vi < head_vecs) *(uintx4*)(dst + (vi >> shift) * row_bytes + (vi & ((1 << shift) - 1)) * 16) = val[u];
+    }
+}
 
 template <int D, int QB>
 __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(AttnArgs a) {
@@ -975,99 +1001,200 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int n_wg, hipStream
 }
 
 // ------------------------------------------------------------------------------------------
-// fp32 debug path: one wavefront per query row, lanes stride over the allowed keys; the row is
-// evaluated exactly as defined -- maximum, exponentials, sum, weighted mean -- with fp32 data,
-// the accurate expf and fp32 value accumulation; only the score dot products run in fp64.  It shares only the work record's (batch, head, query tile) with the fast path.
+// fp32 debug path.  Scores, weighted sums and row sums in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64: products of
+// fp32 data are exact there), weights by the fp32 exponential: with logits of magnitude ~10 an fp32 dot product alone
+// costs a few 1e-6 in every weight, which is the whole error budget of this path.  It shares only the work record's
+// (batch, head, query tile) with the fast path.
+//
+// Bound by the fp64 matrix rate (72 TFLOP/s on MI355X, one of these MFMAs per SIMD every 64 clocks); converting the
+// operands and the loads straight from L2 run beside it.  A workgroup is eight wavefronts on one block of 16 query rows,
+// each taking every eighth tile of 16 keys (so that a layer of a few heads still fills the chip), combined through LDS at
+// the end.  As in the fast path scores are computed transposed, S^T = K Q^T: the accumulator layout (lane: query
+// l % 16, register i: key 4 * i + l / 16) is then the B operand layout of O^T = V^T P^T.  Which four features make up a
+// contraction step, and which feature a row of O^T is, is free as long as both operands agree; they are chosen so that a
+// lane's part of a K, V or output row is contiguous.
+// Measured on MI355X, 5 computed heads of 64 and 1101 tokens, a cached head copied by the same launch: 34 us (at the fp64
+// matrix rate alone 12; a tile takes 3400 clocks of a SIMD, 2048 of them MFMA and most of the rest fp64 conversions, and
+// 153 of the 345 blocks see every key), 6.7 ms with one wavefront per row, scalar dot products and two passes over the
+// keys.  Weighted sums on the fp32 matrix rate instead: 36 us at the same point, and a larger error (1.0e-7 of the
+// result's norm against 64 bits; 3.0e-8 as it is, 8.7e-8 before).
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) x = fmax(x, __shfl_xor(x, s, 64));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) x += __shfl_xor(x, s, 64);
-    return x;
-}
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+constexpr int kF32Rows = kF32BlockRows, kF32Keys = 16, kF32Waves = 8;
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
-    const difa_work_item_t it = a.items[blockIdx.x];
+__global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kernel(AttnArgs a) {
+    constexpr int KF = D / 4;                                // features of a K or Q row per lane
+    constexpr int VF = D / 16;                               // features of a V or output row per lane = 16-row blocks of O^T
+    const unsigned block = blockIdx.y * gridDim.x + blockIdx.x;
+    if (block >= (unsigned)a.f32_blocks) {                   // the blocks behind the computed heads' copy the cached heads
+        const unsigned chunk = block - (unsigned)a.f32_blocks;
+        if (chunk < (unsigned)a.copy_chunks) copy_vectors<64 * kF32Waves>(a, (int)chunk, (int)threadIdx.x);
+        return;
+    }
+    const difa_work_item_t it = a.items[block / (kBM / kF32Rows)];
     if (it.q_tile < 0) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int N = a.n_tokens, n_text = a.n_text;
+    const int i0 = it.q_tile * kBM + (int)(block % (kBM / kF32Rows)) * kF32Rows;
+    if (i0 >= N) return;                                     // (uniform over the workgroup)
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
     const int b = it.bh / a.heads, h = it.bh - b * a.heads;
     const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
     const float* __restrict__ qg = (const float*)a.q + base;
     const float* __restrict__ kg = (const float*)a.k + base;
     const float* __restrict__ vg = (const float*)a.v + base;
-    float* __restrict__ og = (float*)a.out + base;
 
-    for (int r = 0; r < kBM / 4; ++r) {
-        const int i = it.q_tile * kBM + wave * (kBM / 4) + r;
-        if (i >= N) break;                                   // uniform over the wavefront
-        // allowed keys: the text keys [seg0_begin, seg0_end) and the image keys [lo, hi]
-        const int tb = a.text_begin, img0 = tb == 0 ? n_text : 0, img1 = tb == 0 ? N : tb;
-        int seg0_begin, seg0_end, lo, hi;
-        if (it.window < 0 || (unsigned)(i - tb) < (unsigned)n_text) { seg0_begin = seg0_end = 0; lo = 0; hi = N - 1; }
-        else {
-            seg0_begin = tb;
-            seg0_end = tb + n_text;
-            lo = i - it.window > img0 ? i - it.window : img0;
-            hi = i + it.window < img1 - 1 ? i + it.window : img1 - 1;
+    // Keys the block visits, as two ranges [begin0, end0) and [begin1, end1): everything, or the text keys and the part of
+    // the image that some row of the block sees.
+    const int tb = a.text_begin, img0 = tb == 0 ? n_text : 0, img1 = tb == 0 ? N : tb;
+    const int i_last = i0 + kF32Rows - 1 < N - 1 ? i0 + kF32Rows - 1 : N - 1;
+    const bool banded = it.window >= 0;
+    int begin0 = 0, end0 = N, begin1 = 0, end1 = 0;
+    if (banded && i0 >= img0 && i_last < img1) {
+        begin0 = tb;
+        end0 = tb + n_text;
+        begin1 = i0 - it.window > img0 ? i0 - it.window : img0;
+        end1 = (i_last < img1 - 1 - it.window ? i_last + it.window : img1 - 1) + 1;
+    }
+    const int tiles0 = (end0 - begin0 + kF32Keys - 1) / kF32Keys, tiles = tiles0 + (end1 - begin1 + kF32Keys - 1) / kF32Keys;
+
+    // this lane's query: column c16 of S^T and O^T
+    const int i = i0 + c16 < N ? i0 + c16 : N - 1;
+    const bool text_row = !banded || (unsigned)(i - tb) < (unsigned)n_text;
+    const int lo = i - it.window, hi = i < N - 1 - it.window ? i + it.window : N - 1;
+    // The block's query rows in fp64, in the order the contraction reads them: held in registers they would leave room for
+    // one workgroup on a compute unit at head_dim 64 instead of two.
+    __shared__ double q_sm[KF][64];
+    if (wave == 0) {
+#pragma unroll
+        for (int s = 0; s < KF; s += 4) {
+            const floatx4 t4 = *(const floatx4*)(qg + (int64_t)i * a.stride_n + 4 * s + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q_sm[s + e][lane] = (double)t4[e];
         }
-        float qv[D];
+    }
+    __syncthreads();
+
+    doublex4 o[VF];
 #pragma unroll
-        for (int d = 0; d < D; d += 4) {
-            const floatx4 t4 = *(const floatx4*)(qg + (int64_t)i * a.stride_n + d);
-            qv[d] = t4[0]; qv[d + 1] = t4[1]; qv[d + 2] = t4[2]; qv[d + 3] = t4[3];
+    for (int f = 0; f < VF; ++f) o[f] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double l = 0.0, m = -1.0e30;                             // m: reference in the log2 domain, an integer: rescaling is exact
+    const double c = (double)a.scale * 1.44269504088896340736;
+
+    // Step 4 * s + e of the contraction takes features 16 * s + 4 * g + e, so that the four lanes of a key row read 64
+    // bytes of it together.  The next tile's K rows are requested when this one's scores are done, its V rows after the
+    // last use of this one's: each has the other contraction's time to arrive.  (The last tile is requested again past the
+    // end: behind a branch the compiler would have to wait for the younger loads too.)
+    floatx4 kc[KF / 4], vc[4][VF / 4];
+    auto first_key = [&](int t_any) {
+        const int t = t_any < tiles ? t_any : tiles - 1;
+        return t < tiles0 ? begin0 + t * kF32Keys : begin1 + (t - tiles0) * kF32Keys;
+    };
+    auto fetch_k = [&](int t) {
+        const int j0 = first_key(t), jk = j0 + c16 < N ? j0 + c16 : N - 1;       // (keys past the end are masked)
+        const float* kr = kg + (int64_t)jk * a.stride_n + 4 * g;
+#pragma unroll
+        for (int s = 0; s < KF / 4; ++s) kc[s] = *(const floatx4*)(kr + 16 * s);
+    };
+    auto fetch_v = [&](int t) {
+        const int j0 = first_key(t);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int jv = j0 + 4 * u + g < N ? j0 + 4 * u + g : N - 1;
+            const float* vr = vg + (int64_t)jv * a.stride_n + c16 * VF;
+#pragma unroll
+            for (int s = 0; s < VF / 4; ++s) vc[u][s] = *(const floatx4*)(vr + 4 * s);
         }
-        // Scores are accumulated in fp64: with logits of magnitude ~10 an fp32 dot product alone
-        // costs a few 1e-6 in every weight, which is the whole error budget of this path.
-        auto score = [&](int j) {
-            const float* kr = kg + (int64_t)j * a.stride_n;
-            double s = 0.0;
+    };
+    fetch_k(wave);
+    fetch_v(wave);
+    for (int t = wave; t < tiles; t += kF32Waves) {
+        const int j0 = first_key(t), j_end = t < tiles0 ? end0 : end1;
+        asm volatile("" ::: "memory");                       // (or the compiler reads the query rows once and holds them after all)
+        doublex4 s2[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};   // two chains: neither waits for itself
 #pragma unroll
-            for (int d = 0; d < D; d += 4) {
-                const floatx4 t4 = *(const floatx4*)(kr + d);
-                s = fma((double)qv[d], (double)t4[0], s); s = fma((double)qv[d + 1], (double)t4[1], s);
-                s = fma((double)qv[d + 2], (double)t4[2], s); s = fma((double)qv[d + 3], (double)t4[3], s);
-            }
-            return s * (double)a.scale;
-        };
-        // pass 1: row maximum
-        double m = -INFINITY;
-        for (int j = seg0_begin + lane; j < seg0_end; j += 64) m = fmax(m, score(j));
-        for (int j = lo + lane; j <= hi; j += 64) m = fmax(m, score(j));
-        m = wave_max(m);
-        // pass 2: weights, their sum, and the weighted sum of value rows
-        float acc[D];
+        for (int s = 0; s < KF; ++s)
+            s2[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kc[s >> 2][s & 3], q_sm[s][lane], s2[s & 1], 0, 0, 0);
+        const doublex4 sc = s2[0] + s2[1];
+        fetch_k(t + kF32Waves);
+        float top = -INFINITY;
+        double x[4];
 #pragma unroll
-        for (int d = 0; d < D; ++d) acc[d] = 0.f;
-        float l = 0.f;
-        auto accumulate = [&](int j) {
-            const float p = expf((float)(score(j) - m));
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + 4 * u + g;
+            const bool ok = (j < j_end) & (text_row | ((unsigned)(j - tb) < (unsigned)n_text) | ((j >= lo) & (j <= hi)));
+            x[u] = ok ? sc[u] * c : -INFINITY;
+            top = fmaxf(top, (float)x[u]);
+        }
+        top = fmaxf(top, __shfl_xor(top, 16, 64));
+        top = fmaxf(top, __shfl_xor(top, 32, 64));
+        const double m_new = fmax(m, ceil((double)top));
+        if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
+            const double alpha = m < -1.0e29 ? 0.0 : ldexp(1.0, (int)fmax(m - m_new, -2000.0));
+            l *= alpha;
+#pragma unroll
+            for (int f = 0; f < VF; ++f)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[f][e] *= alpha;
+            m = m_new;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double p = (double)exp2f((float)(x[u] - m));
             l += p;
-            const float* vr = vg + (int64_t)j * a.stride_n;
 #pragma unroll
-            for (int d = 0; d < D; d += 4) {
-                const floatx4 t4 = *(const floatx4*)(vr + d);
-                acc[d] = fmaf(p, t4[0], acc[d]); acc[d + 1] = fmaf(p, t4[1], acc[d + 1]);
-                acc[d + 2] = fmaf(p, t4[2], acc[d + 2]); acc[d + 3] = fmaf(p, t4[3], acc[d + 3]);
-            }
-        };
-        for (int j = seg0_begin + lane; j < seg0_end; j += 64) accumulate(j);
-        for (int j = lo + lane; j <= hi; j += 64) accumulate(j);
-        l = wave_sum(l);
-        float mine = 0.f;                                    // lane d%64 keeps feature d
+            for (int f = 0; f < VF; ++f)
+                o[f] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vc[u][f >> 2][f & 3], p, o[f], 0, 0, 0);
+        }
+        fetch_v(t + kF32Waves);
+    }
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+
+    // ---- the eight wavefronts' parts are added pairwise, upper half into lower half
+    __shared__ double part[kF32Waves / 2][4 * VF + 2][64];
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const float tot = wave_sum(acc[d]);
-            if ((d & 63) == lane) mine = tot / l;
-            if ((d & 63) == 63) {
-                const int64_t e = (int64_t)i * a.stride_n + (d - 63) + lane;
-                if (it.flags & DIFA_ITEM_ADD_RESIDUAL) mine += ((const float*)a.residual)[base + e];   // + kept difference
-                og[e] = mine;
+    for (int n = kF32Waves / 2; n >= 1; n /= 2) {
+        __syncthreads();
+        if (wave >= n && wave < 2 * n) {
+            double (*mine)[64] = part[wave - n];
+            mine[4 * VF][lane] = m;
+            mine[4 * VF + 1][lane] = l;
+#pragma unroll
+            for (int f = 0; f < VF; ++f)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mine[4 * f + e][lane] = o[f][e];
+        }
+        __syncthreads();
+        if (wave < n) {
+            double (*other)[64] = part[wave];
+            const double mo = other[4 * VF][lane], m_new = fmax(m, mo);
+            const double wm = m < -1.0e29 ? 0.0 : ldexp(1.0, (int)fmax(m - m_new, -2000.0));
+            const double wo = mo < -1.0e29 ? 0.0 : ldexp(1.0, (int)fmax(mo - m_new, -2000.0));
+            m = m_new;
+            l = l * wm + other[4 * VF + 1][lane] * wo;
+#pragma unroll
+            for (int f = 0; f < VF; ++f)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[f][e] = o[f][e] * wm + other[4 * f + e][lane] * wo;
+        }
+    }
+    if (wave == 0 && i0 + c16 < N) {
+        const double inv = 1.0 / l;
+        // register e of o[f] is feature (4 * e + g) * VF + f of the lane's query
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t at = base + (int64_t)i * a.stride_n + (4 * e + g) * VF;
+#pragma unroll
+            for (int s = 0; s < VF / 4; ++s) {
+                floatx4 w;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    double y = o[4 * s + k][e] * inv;
+                    if (it.flags & DIFA_ITEM_ADD_RESIDUAL) y += (double)((const float*)a.residual)[at + 4 * s + k];   // + kept difference
+                    w[k] = (float)y;
+                }
+                *(floatx4*)((float*)a.out + at + 4 * s) = w;
             }
         }
     }
@@ -1075,18 +1202,20 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 
 hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, int n_items, hipStream_t stream) {
     if (n_items <= 0) return hipSuccess;
+    // (a grid dimension holds fewer than 2^32 threads)
+    const int64_t blocks = (int64_t)a.f32_blocks + a.copy_chunks, in_x = blocks < (1 << 22) ? blocks : 1 << 22;
+    const dim3 grid((unsigned)in_x, (unsigned)((blocks + in_x - 1) / in_x));
     if (head_dim == 128)
-        hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(n_items), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * kF32Waves), 0, stream, a);
     else if (head_dim == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(n_items), dim3(256), 0, stream, a);
+        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * kF32Waves), 0, stream, a);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------
-// Cached heads (Sec. 3.2) by a kernel of their own: on the fp32 debug path, and for a bf16 layer that computes
-// no head at all.  A 16-byte-per-lane copy of the heads' rows; beyond 32768 workgroups a thread takes
+// Cached heads (Sec. 3.2) by a kernel of their own, for a layer that computes no head at all.  A 16-byte-per-lane copy of the heads' rows; beyond 32768 workgroups a thread takes
 // several vectors, four in flight.  HBM bound: 2 * N * D * elem bytes per (batch entry, cached head).
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void cache_copy_kernel(CopyArgs c) {
