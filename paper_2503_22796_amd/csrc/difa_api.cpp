@@ -31,6 +31,7 @@ constexpr int kRecent = 64;
 struct Slot {
     void* d_buf = nullptr;  // device: CACHE-head indices, then the schedule (or the debug path's work records)
     int32_t n_items = 0, n_copy = 0, n_merges = 0, n_slots = 0;
+    int32_t n_wg_used = 0;  // workgroups up to the last one that has a segment
     size_t wg_off = 0, segs_off = 0, merges_off = 0, items_off = 0;  // byte offsets inside the buffer
     bool valid = false;
     uint64_t stamp = 0;
@@ -682,6 +683,9 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
                                          (difa_merge_item_t*)(hb + lru->merges_off), 2 * p->n_wg, &n_merges, &n_slots);
             if (st != DIFA_OK) return fail(p, st, "scheduling the work list failed");
             used = lru->merges_off + (size_t)n_merges * sizeof(difa_merge_item_t);
+            const int32_t* begin = (const int32_t*)(hb + lru->wg_off);
+            lru->n_wg_used = p->n_wg;
+            while (lru->n_wg_used > 0 && begin[lru->n_wg_used - 1] == n_segs) --lru->n_wg_used;
         } else {
             // longest records first: the hardware hands workgroups out in this order
             std::stable_sort(p->recs.begin(), p->recs.end(), [](const difa_work_item_t& x, const difa_work_item_t& y) { return x.n_tiles > y.n_tiles; });
@@ -805,7 +809,12 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         TimingPair tp{};
         if (p->timing && (e = timing_begin(p, stream, 0, &tp)) != hipSuccess)
             return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
-        e = fast ? difa::launch_attn_bf16(a, D, p->n_wg, stream)
+        // A layer of a few records is launched on the workgroups that have any (and one for each chunk of the cached-head
+        // copy): 512 workgroups that only look for work took 2 us to start and end.  From a fraction of the grid on nothing is gained.
+        const int32_t busy = std::max(slot->n_wg_used, std::min(a.copy_chunks, p->n_wg));
+        const int32_t grid = busy <= p->n_wg / 4 ? busy : p->n_wg;
+        a.younger_from = p->n_wg / 2;
+        e = fast ? difa::launch_attn_bf16(a, D, grid, stream)
                  : difa::launch_attn_f32(a, D, slot->n_items, stream);
         if (p->timing) { (void)hipEventRecord(tp.stop, stream); p->pending.push_back(tp); }
         if (e != hipSuccess) return fail(p, DIFA_ERR_HIP, hip_msg("attention launch", e));

@@ -49,6 +49,7 @@ struct AttnArgs {
     int32_t copy_vec_shift;         // log2(16-byte vectors per token row)
     int64_t stride_b, stride_h, stride_n;
     int32_t heads, n_tokens, n_text;
+    int32_t younger_from;  // bf16 kernel: workgroups from this number on share a compute unit with an older one
     int32_t f32_blocks;  // fp32 kernel: workgroups of the computed heads (kBM / kF32BlockRows per record); copy chunks follow
     int32_t text_begin;  // first text token: 0, or n_img when the image tokens come first
     int32_t tile_rot;    // key-tile position u of a record is tile (u + tile_rot) % n_kv_tiles

@@ -331,7 +331,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     // itself the workgroup that was dispatched second runs at 2500 clocks an iteration beside 1735 of the other, and the
     // schedule, which gives both the same work, waits for it.  So the younger half of the grid takes the higher priority
     // for two iterations out of four: 2130 beside 1950.
-    const bool younger = blockIdx.x >= gridDim.x / 2;
+    const bool younger = wgs_per_cu(D) > 1 && (int)blockIdx.x >= a.younger_from;
 
     difa_segment_t seg_next{};
     int sbase = 0;                                          // ring stage of the current segment's tile 0
