@@ -31,6 +31,7 @@ constexpr int kRecent = 64;
 struct Slot {
     void* d_buf = nullptr;  // device: CACHE-head indices, then the schedule (or the debug path's work records)
     int32_t n_items = 0, n_copy = 0, n_merges = 0, n_slots = 0;
+    int32_t rows = 0, n_wg = 0;   // query rows per record, workgroups the schedule is for
     int32_t n_wg_used = 0;  // workgroups up to the last one that has a segment
     size_t wg_off = 0, segs_off = 0, merges_off = 0, items_off = 0;  // byte offsets inside the buffer
     bool valid = false;
@@ -66,10 +67,11 @@ struct TimingPair {
 struct difa_plan {
     difa_plan_desc_t desc;
     float scale;
-    int32_t bm, bn;                // query rows per work record, keys per tile
+    int32_t bn;                    // keys per tile
     int32_t band_rows;             // query rows per block of the block-granular band
     int32_t item_capacity;
-    int32_t n_wg, n_xcd;           // persistent workgroups (wgs_per_cu on every compute unit), accelerator dies
+    int32_t n_cu, n_xcd;           // compute units, accelerator dies
+    int32_t n_wg;                  // most persistent workgroups a launch has (wgs_per_cu on every compute unit)
     size_t buf_bytes, heads_bytes; // schedule buffer: cached-head list, then the schedule
     float* part_o = nullptr;       // device scratch for records cut into pieces: 2 * n_wg slots
     float* part_ml = nullptr;
@@ -83,7 +85,7 @@ struct difa_plan {
     double die_speed[kMaxDies];              // mean 1
     int speed_samples = 0, retunes = 0, reports_seen = 0;
     uint32_t launch_tag = 0, harvested_tag = 0;
-    struct Launch { uint32_t tag = 0; int64_t span[kMaxDies] = {}; int slot = -1; uint32_t sched_id = 0; };
+    struct Launch { uint32_t tag = 0; int64_t span[kMaxDies] = {}; int slot = -1, n_wg = 0; uint32_t sched_id = 0; };
     uint32_t next_sched_id = 0;
     Launch recent[kRecent];                  // the latest launches, by tag % kRecent: what each die was predicted to take
     double* rse_part = nullptr;    // device scratch of difa_head_rse: batch * heads * kRseChunks * 3 sums
@@ -191,7 +193,7 @@ void harvest_die_speeds(difa_plan* p) {
     if (tag == 0 || tag == p->harvested_tag) return;
     const difa_plan::Launch& l = p->recent[tag % kRecent];
     if (l.tag != tag) return;                                         // too long ago
-    for (int w = 0; w < p->n_wg; ++w) {
+    for (int w = 0; w < l.n_wg; ++w) {
         const unsigned long long v = t[w];
         if ((uint32_t)(v >> 32) != tag) return;                       // two launches' reports side by side: not now
         const unsigned long long ran = v & 0xffffffffull;
@@ -388,16 +390,17 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     p->scale = desc->softmax_scale > 0.f ? desc->softmax_scale : 1.0f / sqrtf((float)desc->head_dim);
     difa_tile_shape(desc->head_dim, desc->dtype, &p->band_rows, &p->bn);
     const bool bf16 = desc->dtype == DIFA_DTYPE_BF16;
-    p->bm = bf16 ? difa::rows_per_wg(desc->head_dim) : p->band_rows;
-    const int64_t q_tiles = ((int64_t)desc->max_tokens + p->bm - 1) / p->bm;
+    const int least_rows = bf16 ? difa::kRowsShort : p->band_rows;
+    const int64_t q_tiles = ((int64_t)desc->max_tokens + least_rows - 1) / least_rows;
     const int64_t cap = (int64_t)desc->batch * desc->heads * q_tiles;
     if (cap > (int64_t)1 << 24) {
         delete p;
         return fail(nullptr, DIFA_ERR_UNSUPPORTED, "batch*heads*query tiles exceeds the work-list limit");
     }
     p->item_capacity = (int32_t)cap;
-    p->n_wg = (prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1) * (bf16 ? difa::wgs_per_cu(desc->head_dim) : 1);
-    p->n_xcd = p->n_wg % kXcd == 0 ? kXcd : 1;
+    p->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
+    p->n_wg = p->n_cu * (bf16 ? difa::wgs_per_cu(difa::kRowsShort) : 1);
+    p->n_xcd = p->n_cu % kXcd == 0 ? kXcd : 1;
     p->heads_bytes = ((size_t)desc->heads * sizeof(int32_t) + 63) / 64 * 64;
     // worst case: every record whole plus two pieces per workgroup, one merge entry per workgroup
     p->buf_bytes = p->heads_bytes + ((size_t)p->n_wg + 1) * sizeof(int32_t) + 64 +
@@ -420,8 +423,9 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     if (e == hipSuccess && desc->dtype == DIFA_DTYPE_BF16) {
         what = "allocating the scratch for cut records";
         const size_t slots = 2 * (size_t)p->n_wg;
-        e = hipMalloc((void**)&p->part_o, slots * (size_t)p->bm * desc->head_dim * sizeof(float));
-        if (e == hipSuccess) e = hipMalloc((void**)&p->part_ml, slots * (size_t)p->bm * 2 * sizeof(float));
+        // (half as many slots of twice the rows where records are long)
+        e = hipMalloc((void**)&p->part_o, slots * (size_t)difa::kRowsShort * desc->head_dim * sizeof(float));
+        if (e == hipSuccess) e = hipMalloc((void**)&p->part_ml, slots * (size_t)difa::kRowsShort * 2 * sizeof(float));
         const size_t ctl_bytes = slots * sizeof(int32_t);
         if (e == hipSuccess) e = hipMalloc((void**)&p->ctl, ctl_bytes);
         if (e == hipSuccess) e = hipMemset(p->ctl, 0, ctl_bytes);      // (synchronous; the kernels leave them at zero)
@@ -556,6 +560,19 @@ extern "C" difa_status_t difa_plan_timing_read_head_rse(difa_plan_t* p, double* 
 
 namespace {
 
+// Query rows per record for a bf16 call (see kRowsShort / kRowsLong).
+int record_rows(const difa_plan* p, const int32_t* head_plan, const int32_t* window, int n_text, int n_img) {
+    if (p->desc.head_dim == 64) return difa::kRowsShort;
+    const double n = (double)n_text + n_img;
+    double pairs = 0.0;                                               // query-key pairs of the layer, about
+    for (int h = 0; h < p->desc.heads; ++h) {
+        if (head_plan[h] == DIFA_HEAD_CACHE) continue;
+        const bool full = head_plan[h] == DIFA_HEAD_FULL || window[h] >= n_img - 1;
+        pairs += full ? n * n : n_text * n + n_img * (n_text + std::min(2.0 * window[h] + 1.0, (double)n_img));
+    }
+    return pairs * p->desc.batch > difa::kLongPairsPerCu * p->n_cu ? difa::kRowsLong : difa::kRowsShort;
+}
+
 // The body of both attention entry points.  static_scratch: partial results of cut records go to the
 // library's file-scope device array instead of the plan's own buffer.
 difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k, const void* v,
@@ -664,7 +681,9 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         lru->valid = false;
         int32_t n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
         char* hb = (char*)stg.h_buf;
-        difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, p->bm, p->band_rows, p->bn,
+        lru->rows = p->desc.dtype != DIFA_DTYPE_BF16 ? p->band_rows : record_rows(p, head_plan, window, n_text, n_img);
+        lru->n_wg = p->desc.dtype != DIFA_DTYPE_BF16 ? p->n_wg : p->n_cu * difa::wgs_per_cu(lru->rows);
+        difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, lru->rows, p->band_rows, p->bn,
                                                      p->desc.flags, p->recs, (int32_t*)hb, &n_copy);
         if (st == DIFA_OK && p->recs.size() > (size_t)p->item_capacity) st = DIFA_ERR_ALLOC;    // (cannot be: sized from max_tokens)
         if (st != DIFA_OK) return fail(p, st, "work-list compilation failed");
@@ -673,18 +692,18 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         lru->wg_off = lru->segs_off = lru->merges_off = lru->items_off = used;
         if (p->desc.dtype == DIFA_DTYPE_BF16) {
             lru->wg_off = used;
-            lru->segs_off = (lru->wg_off + ((size_t)p->n_wg + 1) * sizeof(int32_t) + 63) / 64 * 64;
-            const int32_t seg_cap = n_items + 2 * p->n_wg;
+            lru->segs_off = (lru->wg_off + ((size_t)lru->n_wg + 1) * sizeof(int32_t) + 63) / 64 * 64;
+            const int32_t seg_cap = n_items + 2 * lru->n_wg;
             lru->merges_off = (lru->segs_off + (size_t)seg_cap * sizeof(difa_segment_t) + 63) / 64 * 64;
             const bool dies = p->h_times != nullptr;
-            st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, p->n_wg, p->n_xcd, dies ? lru->speed : nullptr,
+            st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, lru->n_wg, p->n_xcd, dies ? lru->speed : nullptr,
                                          dies ? lru->die_span : nullptr, (difa_segment_t*)(hb + lru->segs_off),
                                          seg_cap, (int32_t*)(hb + lru->wg_off), &n_segs,
-                                         (difa_merge_item_t*)(hb + lru->merges_off), 2 * p->n_wg, &n_merges, &n_slots);
+                                         (difa_merge_item_t*)(hb + lru->merges_off), 2 * lru->n_wg, &n_merges, &n_slots);
             if (st != DIFA_OK) return fail(p, st, "scheduling the work list failed");
             used = lru->merges_off + (size_t)n_merges * sizeof(difa_merge_item_t);
             const int32_t* begin = (const int32_t*)(hb + lru->wg_off);
-            lru->n_wg_used = p->n_wg;
+            lru->n_wg_used = lru->n_wg;
             while (lru->n_wg_used > 0 && begin[lru->n_wg_used - 1] == n_segs) --lru->n_wg_used;
         } else {
             // longest records first: the hardware hands workgroups out in this order
@@ -753,7 +772,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             // [n_slots][bm][head_dim] accumulators, then [n_slots][bm][2] row references and sums
             size_t cap = 0;
             float* base = difa::static_scratch(p->desc.device, &cap);
-            const size_t o_floats = (size_t)slot->n_slots * p->bm * D, ml_floats = (size_t)slot->n_slots * p->bm * 2;
+            const size_t o_floats = (size_t)slot->n_slots * slot->rows * D, ml_floats = (size_t)slot->n_slots * slot->rows * 2;
             if (!base)
                 return fail(p, DIFA_ERR_HIP, "the static scratch array has no address on this device (set up in difa_plan_create)");
             if ((o_floats + ml_floats) * sizeof(float) > cap) {
@@ -782,6 +801,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
                 l.tag = p->launch_tag;
                 l.slot = (int)(slot - p->slots);
                 l.sched_id = slot->sched_id;
+                l.n_wg = slot->n_wg;
                 memcpy(l.span, slot->die_span, sizeof l.span);
             }
         }
@@ -789,7 +809,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             const int vec_per_row = (int)(D * es / 16);                     // 8, 16 or 32: a power of two
             int shift = 0;
             while ((1 << shift) < vec_per_row) ++shift;
-            const int64_t head_vecs = (int64_t)N << shift, chunk = fast ? difa::copy_chunk_vecs(D) : difa::kF32CopyVecs;
+            const int64_t head_vecs = (int64_t)N << shift, chunk = fast ? difa::copy_chunk_vecs(slot->rows) : difa::kF32CopyVecs;
             const int64_t per_head = (head_vecs + chunk - 1) / chunk, chunks = (int64_t)B * slot->n_copy * per_head;
             if (head_vecs > INT32_MAX - chunk || chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
             a.copy_src = cache;
@@ -811,10 +831,10 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
         // A layer of a few records is launched on the workgroups that have any (and one for each chunk of the cached-head
         // copy): 512 workgroups that only look for work took 2 us to start and end.  From a fraction of the grid on nothing is gained.
-        const int32_t busy = std::max(slot->n_wg_used, std::min(a.copy_chunks, p->n_wg));
-        const int32_t grid = busy <= p->n_wg / 4 ? busy : p->n_wg;
-        a.younger_from = p->n_wg / 2;
-        e = fast ? difa::launch_attn_bf16(a, D, grid, stream)
+        const int32_t busy = std::max(slot->n_wg_used, std::min(a.copy_chunks, slot->n_wg));
+        const int32_t grid = busy <= slot->n_wg / 4 ? busy : slot->n_wg;
+        a.younger_from = p->n_cu;
+        e = fast ? difa::launch_attn_bf16(a, D, slot->rows, grid, stream)
                  : difa::launch_attn_f32(a, D, slot->n_items, stream);
         if (p->timing) { (void)hipEventRecord(tp.stop, stream); p->pending.push_back(tp); }
         if (e != hipSuccess) return fail(p, DIFA_ERR_HIP, hip_msg("attention launch", e));

@@ -9,17 +9,21 @@ namespace difa {
 
 constexpr int kBM = 256;  // query rows per block of the block-granular band, and per work record of the fp32 path
 constexpr int kBN = 64;   // keys per K/V tile
-// bf16 kernel: query rows per work record and workgroup (32 per wavefront), and how many such workgroups a compute unit
-// holds.  Either way a SIMD has two wavefronts.  At head_dim 128 they belong to one workgroup, whose K/V rings fill the
-// LDS.  At head_dim 64 the rings are half the size and the softmax's share of an iteration twice as large, so what counts
-// is that a wavefront has another one to hide its barriers, masks and segment ends behind: two workgroups of four
-// wavefronts that know nothing of each other.  Clocks per 256 rows x 64 keys on MI355X, one workgroup of eight against two
-// of four: 2190-2360 against 2050 in the loop; the SD3-like 512 px layers 1.13 times as fast, the 1K layer up to 1.05; at 2K
-// (where the clock gives way as the loop gets denser) the same.  64 rows per wavefront as well: 2010 clocks, 2K the same,
-// 1K 0.75 times as fast (records twice as long).
-constexpr int rows_per_wg(int head_dim) { return head_dim == 64 ? 128 : 256; }
-constexpr int wgs_per_cu(int head_dim) { return 256 / rows_per_wg(head_dim); }
-constexpr int copy_chunk_vecs(int head_dim) { return 32 * rows_per_wg(head_dim); }   // 16-byte vectors per chunk of the cached-head copy: 16 per thread
+// bf16 kernel: query rows per work record and workgroup (32 per wavefront).  Either way a SIMD has two wavefronts: they
+// belong to one workgroup of 256 rows, or to two workgroups of 128 that know nothing of each other, so that the barriers,
+// masks and record ends of one run under the other's arithmetic, records are half as long (easier to share out evenly, and a
+// band covers fewer keys outside it), and every K/V tile is written to LDS twice as often.
+// head_dim 64 (the softmax's share of an iteration is twice as large): 128 rows throughout.  Clocks per 256 rows x 64 keys on
+// MI355X 2050 against 2190-2360; SD3-like 512 px layers 1.13 times as fast, the 1K layer up to 1.05; at 2K (where the clock
+// gives way as the loop gets denser) the same.  64 rows per wavefront as well: 2010 clocks, 2K the same, 1K 0.75 times.
+// head_dim 128: the loop takes the same 2870-2940 clocks both ways, and the second copy of every tile costs 4-5 % of the
+// clock the chip holds (1.64 against 1.72 GHz on the all-full 2K layer), which long layers do not get back.  256 rows against
+// 128, by query-key pairs per compute unit: 0.9 M (FLUX-like 1K) 132 / 126 us, 8.6 M (2K mixed) 1001 / 993, 11 M (video-like)
+// 1350 / 1334, 26.8 M (2K all-full) 2928 / 3001.
+constexpr int kRowsShort = 128, kRowsLong = 256;
+constexpr double kLongPairsPerCu = 16.0e6;                      // more pairs than that per compute unit: 256 rows (head_dim 128)
+constexpr int wgs_per_cu(int rows) { return 256 / rows; }
+constexpr int copy_chunk_vecs(int rows) { return 32 * rows; }   // 16-byte vectors per chunk of the cached-head copy: 16 per thread
 
 constexpr int kF32BlockRows = 16;      // fp32 kernel: query rows per workgroup
 constexpr int kF32CopyVecs = 16 * 512; // ... and 16-byte vectors per chunk of its cached-head copy
@@ -81,7 +85,7 @@ struct RseArgs {
 };
 
 // Launchers (defined in difa_kernels.hip and difa_rse.hip).  All enqueue on `stream` and return the launch status.
-hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int n_wg, hipStream_t stream);
+hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int rows, int n_wg, hipStream_t stream);
 hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, int n_items, hipStream_t stream);
 hipError_t launch_cache_copy(const CopyArgs& a, hipStream_t stream);
 hipError_t launch_head_rse(const RseArgs& a, int dtype, hipStream_t stream);

@@ -35,15 +35,16 @@ __device__ __forceinline__ float halves_sum(float x) {
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA attention.
 //
-// A workgroup is 8 / QB wavefronts at head_dim 128 and 4 / QB at 64 (QB = 32-row blocks per wavefront; 1 in the
-// shipped build, so eight wavefronts or two times four on a compute unit, two per SIMD) and stays resident: it walks
-// the list of segments the host scheduler gave it.  A segment is a 256-row (head_dim 64: 128-row) query tile of one
-// (batch, head) together with a
+// A workgroup is BM / 32 / QB wavefronts (QB = 32-row blocks per wavefront; 1 in the shipped build, so eight
+// wavefronts, or two workgroups of four on a compute unit, two per SIMD) and stays resident: it walks
+// the list of segments the host scheduler gave it.  A segment is a BM-row query tile of one (batch, head) together with a
 // run of that record's key/value tiles (the whole run for most records; a few records are cut so
 // that every workgroup ends at the same time, and their pieces leave fp32 partial results that the
 // piece finishing last folds into its own).  Wavefront w owns rows 32*QB*w .. 32*QB*(w+1)-1 as QB 32-row blocks.
 // Key/value tiles of 64 keys are written into 4-stage LDS rings by the buffer-load-to-LDS DMA, K three
-// tiles and V two tiles ahead of their use, in the order the work record lists them (text tiles,
+// tiles and V two tiles ahead of their use (two workgroups at head_dim 128, where four stages of whole tiles would fill
+// the LDS twice over: stages of half a tile, K four and V two blocks of 32 keys ahead, a barrier for every block),
+// in the order the work record lists them (text tiles,
 // then the band tiles), so a tile with no allowed pair is never loaded (Sec. 3.1 / 3.3:
 // block-sparse band).  The first tiles and the Q rows of the next segment are requested before
 // the current segment's epilogue.
@@ -133,15 +134,16 @@ __device__ __forceinline__ void copy_vectors(const AttnArgs& ca, int chunk, int 
     }
 }
 
-template <int D, int QB>
-__global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(AttnArgs a) {
-    constexpr int BM = rows_per_wg(D);      // query rows per record
+template <int D, int BM, int QB>                // BM: query rows per record
+__global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs a) {
     constexpr int RW = 32 * QB;
     constexpr int NW = BM / RW;             // wavefronts per workgroup; each owns 32*QB query rows
     constexpr int KS = D / 16;              // MFMA k-steps of S^T = K Q^T
     constexpr int DB = D / 32;              // 32-row blocks of O^T
     constexpr int CPR = D / 8;              // 16-byte chunks per K/V row
-    constexpr int TILE = kBN * D;           // elements of one K or V tile
+    constexpr bool BLK = D == 128 && BM == 128;   // the rings hold 32-key blocks (half tiles) instead of tiles
+    constexpr int RKEYS = BLK ? kBN / 2 : kBN;    // keys per ring stage
+    constexpr int TILE = RKEYS * D;         // elements of one ring stage
     constexpr int NS = 4;                   // LDS ring depth, K and V alike: tile p lives in stage p % 4
     constexpr float kTrip = 0x1p40f;        // a block row sum beyond this sends the wavefront to the renormalising side path
     constexpr float kBump = 16.0f;          // ... where a row's reference moves if its block maximum exceeds it by 2^16
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     // view, so the wait for them is explicit (dma_wait) and sits just before the barrier that
     // publishes the tile.
     constexpr int RPI = 64 / CPR;                           // tile rows per load instruction
-    constexpr int NDMA = kBN / RPI / NW;                     // load instructions per wavefront, tensor and tile
+    constexpr int NDMA = RKEYS / RPI / NW;                     // load instructions per wavefront, tensor and tile
     const unsigned head_bytes = (unsigned)(((int64_t)(N - 1) * a.stride_n + D) * 2);
     uintx4 krsrc, vrsrc;                                    // descriptors of the head whose tiles are being loaded
     const unsigned wave_u = __builtin_amdgcn_readfirstlane(wave);
@@ -257,6 +259,24 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
         krsrc[0] = (unsigned)ka; krsrc[1] = (unsigned)(ka >> 32) & 0xffffu; krsrc[2] = head_bytes; krsrc[3] = 0x00020000u;
         vrsrc[0] = (unsigned)va; vrsrc[1] = (unsigned)(va >> 32) & 0xffffu; vrsrc[2] = head_bytes; vrsrc[3] = 0x00020000u;
         const int n = sg.pos_end - sg.pos_begin;
+        if constexpr (BLK) {                                // blocks 0..3 of K, 0 and 1 of V
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int p = sg.pos_begin + t;
+                const int tile = tile_at(p < sg.kv0_end ? p : sg.kv1_begin + (p - sg.kv0_end));
+                const unsigned tb = t < n ? (unsigned)tile * tile_bytes : 0x80000000u;
+#pragma unroll
+                for (int jb = 0; jb < 2; ++jb) {
+                    const unsigned st = (unsigned)(((sb + 2 * t + jb) & 3) * TILE * 2) + wave_lds;
+#pragma unroll
+                    for (int u = 0; u < NDMA; ++u) {
+                        dma_part(0, u, tb + jb * (tile_bytes / 2), k_lds + st);
+                        if (t == 0) dma_part(1, u, tb + jb * (tile_bytes / 2), v_lds + st);
+                    }
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             const int p = sg.pos_begin + t;
@@ -270,7 +290,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
             }
         }
     };
-    constexpr int kFirstTileLoads = 5 * NDMA;               // load instructions first_tiles issues
+    constexpr int kFirstTileLoads = (BLK ? 6 : 5) * NDMA;               // load instructions first_tiles issues
     auto query_rows = [&](const difa_segment_t& sg) __attribute__((always_inline)) {
         const int b = sg.bh / a.heads, h = sg.bh - b * a.heads;
         const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
@@ -295,12 +315,12 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     const int seg_end = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x + 1]);
     const int seg_first = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x]);
     // ---- cached heads (Sec. 3.2; the cache fill that ends Alg. 1): out[b, h] = cache[b, h], bit for bit.
-    // HBM-bound work that needs no matrix core.  It is cut into chunks of copy_chunk_vecs(D) 16-byte vectors of one
+    // HBM-bound work that needs no matrix core.  It is cut into chunks of copy_chunk_vecs(BM) 16-byte vectors of one
     // (batch entry, cached head); workgroup p takes chunks p, p + gridDim.x, ... and moves one after each of
     // its attention segments, when it waits for the next segment's first tiles anyway, so the copy is
     // spread over the launch and runs in the shadow of the other workgroups' arithmetic.
     auto copy_chunk = [&](int chunk) __attribute__((always_inline)) {
-        constexpr int PER = copy_chunk_vecs(D) / (NW * 64);          // vectors per thread and chunk, all in flight together
+        constexpr int PER = copy_chunk_vecs(BM) / (NW * 64);          // vectors per thread and chunk, all in flight together
         const AttnArgs* ca = cold_args();
         const int per_head = ca->copy_chunks_per_head, n_copy = ca->n_copy, shift = ca->copy_vec_shift;
         const int head_vecs = ca->copy_head_vecs;
@@ -315,7 +335,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
         bool live[PER];
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            int vi = cc * copy_chunk_vecs(D) + u * (NW * 64) + tid;                // vector inside the head
+            int vi = cc * copy_chunk_vecs(BM) + u * (NW * 64) + tid;                // vector inside the head
             live[u] = vi < head_vecs;
             vi = live[u] ? vi : head_vecs - 1;                            // past the end: reread the last one, store nothing
             off[u] = (unsigned)(vi >> shift) * row_bytes + (unsigned)(vi & ((1 << shift) - 1)) * 16u;
@@ -327,11 +347,11 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
             if (live[u]) *(uintx4*)(dst + off[u]) = val[u];
     };
     int next_chunk = (int)blockIdx.x;
-    // Two workgroups share a compute unit at head_dim 64, and its SIMDs serve the older wavefront first: left to
-    // itself the workgroup that was dispatched second runs at 2500 clocks an iteration beside 1735 of the other, and the
-    // schedule, which gives both the same work, waits for it.  So the younger half of the grid takes the higher priority
-    // for two iterations out of four: 2130 beside 1950.
-    const bool younger = wgs_per_cu(D) > 1 && (int)blockIdx.x >= a.younger_from;
+    // Where two workgroups share a compute unit, its SIMDs serve the older wavefront first: left to itself (head_dim 64)
+    // the workgroup that was dispatched second runs at 2500 clocks an iteration beside 1735 of the other, and the schedule,
+    // which gives both the same work, waits for it.  So the younger half of the grid takes the higher priority for two
+    // iterations out of four: 2130 beside 1950.
+    const bool younger = wgs_per_cu(BM) > 1 && (int)blockIdx.x >= a.younger_from;
 
     difa_segment_t seg_next{};
     int sbase = 0;                                          // ring stage of the current segment's tile 0
@@ -415,7 +435,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
 
     // ---- S^T = K Q^T for one 32-key block jb of a tile: s[qb], register r = key 32*jb + 8*(r/4) + 4*half + r%4
     auto qk_block = [&](int idx, int jb, floatx16 (&s)[QB]) {
-        const __bf16* kst = &Ksm[((idx + sbase) & 3) * TILE + 32 * jb * D];
+        const __bf16* kst = BLK ? &Ksm[((2 * idx + jb + sbase) & 3) * TILE] : &Ksm[((idx + sbase) & 3) * TILE + 32 * jb * D];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const bf16x8 ka = *(const bf16x8*)(kst + koff[ks]);
@@ -626,7 +646,8 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     auto half_step = [&](const floatx16 (&s_cur)[QB], floatx16 (&s_nxt)[QB], const bf16x8 (&p_prev)[QB][2],
                          bf16x8 (&p_cur)[QB][2], const __bf16* kst_nxt, const __bf16* kst_after,
                          const __bf16* vst_prev, const __bf16* vst_cur, bool with_pv, bool mask_nxt,
-                         int blk_nxt, int dma_tensor, unsigned dma_tb, unsigned dma_dst) __attribute__((always_inline)) {
+                         int blk_nxt, int dma_tensor, unsigned dma_tb, unsigned dma_dst,
+                         unsigned dma_tb2 = 0, unsigned dma_dst2 = 0) __attribute__((always_inline)) {
         float mneg[QB], lb[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) mneg[qb] = -rs[qb].m;
@@ -657,6 +678,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
             // the loads of a later tile are spread over the slots (a burst of them right after the
             // barrier stalls all wavefronts on the one memory pipe)
             if ((s & 3) == 1 && (s >> 2) < NDMA) dma_part(dma_tensor, s >> 2, dma_tb, dma_dst);
+            if (BLK && (s & 3) == 3 && (s >> 2) < NDMA) dma_part(1, s >> 2, dma_tb2, dma_dst2);
             __builtin_amdgcn_sched_barrier(0);
         }
         {
@@ -681,6 +703,7 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     qk_block(0, 0, s0);
     if (tile_masked(0)) mask_block(tile_of(0) * kBN, s0);   // (before the loop-carried flags exist)
 
+    if constexpr (BLK) __syncthreads();     // block 0 has been read by everyone: its stage takes block 4
     // Loop-carried scalars (all uniform over the wavefront), advanced once per iteration instead of
     // being recomputed from the position: ring stages of the tiles in use, mask flags, load target.
     // A wavefront issues in order and scalar work delays its next MFMA, so there is as little of it as possible.
@@ -691,23 +714,39 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     auto bump = [](int& off) { off = (off + TILE) & (NS * TILE - 1); };          // next ring stage (element offset)
     auto kptr = [&](int off, int jb) { return &Ksm[off + 32 * jb * D]; };
     auto vptr = [&](int off, int jb) { return &Vsm[off + 32 * jb * D]; };
+    const unsigned half_tile = tile_bytes / 2;
+    auto stage = [&](int blk) { return ((sbase + blk) & 3) * TILE; };                       // (BLK)
+    auto dst = [&](unsigned base, int off) { return base + (unsigned)(off * 2) + wave_lds; };
     // ring stages as element offsets: K stages of positions idx, idx+1, idx+3, V stages of idx-1, idx, idx+2
     int k_cur = (sbase & 3) * TILE, k_nxt = ((sbase + 1) & 3) * TILE, k_ld = ((sbase + 3) & 3) * TILE;
     int v_prv = k_cur, v_cur = k_cur, v_ld = ((sbase + 2) & 3) * TILE;
     bool msk_cur = pos_masked(0), msk_nxt = pos_masked(1);
-    unsigned tb_k = tile_offset(3), tb_v = tile_offset(2);  // tiles whose K / V loads the coming iteration issues
+    unsigned tb_k = tile_offset(BLK ? 2 : 3), tb_v = tile_offset(BLK ? 1 : 2);  // tiles whose K / V loads the coming iteration issues
 
     // first tile: its even block has no predecessor whose P V would be due
 #pragma unroll
-    for (int j = 0; j < AHEAD; ++j) kq[j] = k_operand(kptr(k_cur, 1), j);
+    for (int j = 0; j < AHEAD; ++j) kq[j] = k_operand(BLK ? kptr(stage(1), 0) : kptr(k_cur, 1), j);
+    if constexpr (BLK) {
+        half_step(s0, s1, pb, pa, kptr(stage(1), 0), kptr(stage(2), 0), vptr(stage(0), 0), vptr(stage(0), 0), false, msk_cur, 1,
+                  0, tb_k, dst(k_lds, stage(4)), tb_v, dst(v_lds, stage(2)));
+        mfma_results_visible();
+        __syncthreads();
+        half_step(s1, s0, pa, pb, kptr(stage(2), 0), kptr(stage(3), 0), vptr(stage(0), 0), vptr(stage(1), 0), true, msk_nxt, 2,
+                  0, tb_k + half_tile, dst(k_lds, stage(5)), tb_v + half_tile, dst(v_lds, stage(3)));
+    } else {
     half_step(s0, s1, pb, pa, kptr(k_cur, 1), kptr(k_nxt, 0), vptr(v_cur, 0), vptr(v_cur, 0), false,
               msk_cur, 1, 0, tb_k, k_lds + (unsigned)(k_ld * 2) + wave_lds);
     if (QB == 1) mfma_results_visible();    // no P V MFMA separated this block's last S^T MFMA from its first reader
     half_step(s1, s0, pa, pb, kptr(k_nxt, 0), kptr(k_nxt, 1), vptr(v_cur, 0), vptr(v_cur, 1), true,
               msk_nxt, 2, 1, tb_v, v_lds + (unsigned)(v_ld * 2) + wave_lds);
+    }
     dma_wait_older();
 
-    // Iteration idx works on tiles idx-1 (P V), idx and idx+1 (S^T), issues the loads of K tile idx+3 and
+    // With half-tile stages (BLK) half-step g reads K blocks g+1 and g+2 and V blocks g-1 and g, and issues the loads of
+    // K block g+4 into the stage of block g and of V block g+2 into that of block g-2, both read for the last time before
+    // the barrier it begins with; they are waited for at the end of half-step g+1, before the barrier of g+2.  A tile
+    // moves the ring by two stages, so there are two copies of the loop body.
+    // Otherwise: iteration idx works on tiles idx-1 (P V), idx and idx+1 (S^T), issues the loads of K tile idx+3 and
     // V tile idx+2 and, before the next barrier, waits for the loads issued one iteration earlier
     // (K tile idx+2, V tile idx+1).  K tile p is last read in the first half of iteration p, V tile p in
     // the first half of iteration p+1, so both rings are four stages deep.
@@ -719,12 +758,23 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
         constexpr int P = decltype(stage_c)::value;         // ring stage of tile idx
         constexpr int KC = P * TILE, KN = ((P + 1) & 3) * TILE, KL = ((P + 3) & 3) * TILE;
         constexpr int VP = ((P + 3) & 3) * TILE, VC = P * TILE, VL = ((P + 2) & 3) * TILE;
-        if (wgs_per_cu(D) > 1 && (P & 1) == 0 && younger) __builtin_amdgcn_s_setprio(P == 0 ? 1 : 0);
+        if (wgs_per_cu(BM) > 1 && (P & 1) == 0 && younger) __builtin_amdgcn_s_setprio(P == 0 ? 1 : 0);
         msk_cur = msk_nxt;
         msk_nxt = pos_masked(idx + 1);
         tb_v = tb_k;
-        tb_k = tile_offset(idx + 3);
+        tb_k = tile_offset(idx + (BLK ? 2 : 3));
         __syncthreads();    // the tiles waited for last are in LDS for everyone; the stages loaded next are no longer read
+        if constexpr (BLK) {
+            constexpr int S0 = P * TILE, S1 = (P + 1) * TILE, S2 = ((P + 2) & 3) * TILE, S3 = ((P + 3) & 3) * TILE;   // blocks 2 * idx ..
+            half_step(s0, s1, pb, pa, kptr(S1, 0), kptr(S2, 0), vptr(S3, 0), vptr(S0, 0), true, msk_cur, 2 * idx + 1,
+                      0, tb_k, dst(k_lds, S0), tb_v, dst(v_lds, S2));
+            dma_wait_older();
+            __syncthreads();
+            half_step(s1, s0, pa, pb, kptr(S2, 0), kptr(S3, 0), vptr(S0, 0), vptr(S1, 0), true, msk_nxt, 2 * idx + 2,
+                      0, tb_k + half_tile, dst(k_lds, S1), tb_v + half_tile, dst(v_lds, S3));
+            dma_wait_older();
+            return;
+        }
         half_step(s0, s1, pb, pa, kptr(KC, 1), kptr(KN, 0), vptr(VP, 1), vptr(VC, 0), true,
                   msk_cur, 2 * idx + 1, 0, tb_k, k_lds + (unsigned)(KL * 2) + wave_lds);
         half_step(s1, s0, pa, pb, kptr(KN, 0), kptr(KN, 1), vptr(VC, 0), vptr(VC, 1), true,
@@ -734,6 +784,18 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
     {
         int idx = 1;
         int phase = (sbase + 1) & 3;
+        if constexpr (BLK) {                // a tile takes two stages: two copies
+            phase = (sbase + 2) & 3;
+            while (idx < n_iter) {
+                if (phase == 0) {
+                    iteration(std::integral_constant<int, 0>(), idx);
+                    if (++idx >= n_iter) break;
+                }
+                iteration(std::integral_constant<int, 2>(), idx);
+                ++idx;
+                phase = 0;
+            }
+        } else
         while (idx < n_iter) {
             switch (phase) {
                 case 0:
@@ -754,18 +816,18 @@ __global__ __launch_bounds__(2 * rows_per_wg(D) / QB, 1) void attn_bf16_kernel(A
             }
             phase = 0;
         }
-        v_cur = ((sbase + n_iter - 1) & 3) * TILE;          // stage of the last tile, for its second block's P V
+        v_cur = BLK ? stage(2 * n_iter - 1) : ((sbase + n_iter - 1) & 3) * TILE;          // stage of the last tile, for its second block's P V
     }
     // The key loop is over: the K stages and all V stages but the last tile's are free.  Loads past the
     // segment's end may still be depositing zeros, and other wavefronts may still be reading: wait for
     // both, then request what the next segment needs first, so that it arrives during the epilogue.
     dma_wait_all();
     __syncthreads();
-    const int sbase_next = (sbase + n_iter) & 3;            // keeps clear of the stage the last P V still reads
+    const int sbase_next = (sbase + (BLK ? 2 : 1) * n_iter) & 3;            // keeps clear of the stage the last P V still reads
     if (seg_idx + 1 < seg_end && it.part_slot < 0) first_loads(seg_next, sbase_next);   // (a piece: after its slot stores)
     // P V of the very last block (its first operands are already in flight)
     {
-        const __bf16* vst = vptr(v_cur, 1);
+        const __bf16* vst = vptr(v_cur, BLK ? 0 : 1);
 #pragma unroll
         for (int i = 0; i < NOP; ++i) {
             if (i + AHEAD < NOP) vq[i + AHEAD] = v_operand(vst, i + AHEAD);
@@ -989,14 +1051,13 @@ float* static_scratch(int device, size_t* bytes) {
 // lowers its clock by as much as the schedule got tighter.
 constexpr int kRowBlocks = 1;
 
-hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int n_wg, hipStream_t stream) {
+hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int rows, int n_wg, hipStream_t stream) {
     if (n_wg <= 0) return hipSuccess;
-    if (head_dim == 128)
-        hipLaunchKernelGGL((attn_bf16_kernel<128, kRowBlocks>), dim3(n_wg), dim3(2 * rows_per_wg(128) / kRowBlocks), 0, stream, a);
-    else if (head_dim == 64)
-        hipLaunchKernelGGL((attn_bf16_kernel<64, kRowBlocks>), dim3(n_wg), dim3(2 * rows_per_wg(64) / kRowBlocks), 0, stream, a);
-    else
-        return hipErrorInvalidValue;
+    const dim3 grid(n_wg), threads(2 * rows / kRowBlocks);
+    if (head_dim == 128 && rows == kRowsLong) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsLong, kRowBlocks>), grid, threads, 0, stream, a);
+    else if (head_dim == 128 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsShort, kRowBlocks>), grid, threads, 0, stream, a);
+    else if (head_dim == 64 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<64, kRowsShort, kRowBlocks>), grid, threads, 0, stream, a);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

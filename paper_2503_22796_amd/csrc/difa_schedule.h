@@ -21,8 +21,8 @@ constexpr CostModel kGenericCosts{7, 36, 72, 40, 12};   // what difa_schedule_bu
 // Measured on MI355X: clock counters around every segment, regressed per workgroup on what its list held (1K and 2K
 // layers).  head_dim 128, one workgroup of eight wavefronts on a compute unit: 2950 clocks a plain iteration, 0.5-0.6
 // iterations more on a masked tile, 5.9 for starting and finishing a whole record, 6.1 for a piece (9-11 while slots were
-// laid out by rows), 2.4 for folding one other slot in.  head_dim 64, two workgroups of four wavefronts sharing the
-// compute unit: 2000 clocks, 1.4, 1-3, 3-5 and 2.7 iterations.
+// laid out by rows), 2.4 for folding one other slot in; two workgroups of four wavefronts 2900, 0.7, 5.2, 5.7 and 3.0.
+// head_dim 64, two workgroups of four wavefronts: 2000 clocks, 1.4, 1-3, 3-5 and 2.7 iterations.
 constexpr CostModel kernel_costs(int head_dim) {
     return head_dim == 64 ? CostModel{11, 12, 28, 21, 8} : CostModel{8, 26, 36, 19, 8};
 }
