@@ -464,28 +464,24 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         const unsigned ninf = 0xff800000u;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            // bit r of `gone` says that register r holds the score of a forbidden key
+            // Bit r of `gone` says that register r holds the score of a forbidden key.  Register r of a lane holds the key at
+            // offset 8*(r/4) + r%4 (+ 4*half) of the block, increasing with r, so the keys below some key are the lane's
+            // first k registers; the count k comes from that key with a handful of integer instructions.
+            auto below = [&](int key) {                                    // registers whose key is < key
+                const int e = key - j0 - 4 * half, ec = e < 0 ? 0 : (e > 32 ? 32 : e);
+                const int rem = ec & 7;
+                return (1u << (4 * (ec >> 3) + (rem < 4 ? rem : 4))) - 1u;
+            };
             unsigned gone = 0;
             if (plain) {
-                // Register r of a lane holds the key at offset 8*(r/4) + r%4 (+ 4*half) of the block, increasing
-                // with r, so the keys below the band's start are the lane's first k registers and the keys beyond
-                // its end the last ones.  The count k comes from the lane's edge with a handful of integer
-                // instructions.
-                auto below = [](int e) {                                    // registers whose key offset is < e
-                    const int ec = e < 0 ? 0 : (e > 32 ? 32 : e);
-                    const int rem = ec & 7;
-                    return 4 * (ec >> 3) + (rem < 4 ? rem : 4);
-                };
-                if (low) gone = (1u << below(rs[qb].lo - j0 - 4 * half)) - 1u;
-                if (high) gone |= ~((1u << below(rs[qb].lo + (int)rs[qb].span - j0 - 4 * half + 1)) - 1u);
+                if (low) gone = below(rs[qb].lo);
+                if (high) gone |= ~below(rs[qb].lo + (int)rs[qb].span + 1);
             } else {
-                // text keys or rows, or the tail of the sequence, in the block: one unsigned range test per segment and key
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int j = j0 + 8 * (r >> 2) + 4 * half + (r & 3);
-                    const bool ok = ((unsigned)(j - text_begin) < (unsigned)n_text) | ((unsigned)(j - rs[qb].lo) <= rs[qb].span);
-                    gone |= ok ? 0u : 1u << r;
-                }
+                // text keys or rows, or the tail of the sequence, in the block: allowed are the text keys and the row's band
+                // (spelled out key by key this path was 150 instructions, ten times in the kernel, and pushed the loop out
+                // of the instruction cache two compute units share)
+                gone = ~((below(rs[qb].lo + (int)rs[qb].span + 1) & ~below(rs[qb].lo)) |
+                         (below(text_begin + n_text) & ~below(text_begin)));
             }
             // Each score then costs a signed one-bit extract (all ones or zero) and a bit-select between the score
             // and -inf, in place.  No compare writes a lane mask that the next instruction would have to wait for
