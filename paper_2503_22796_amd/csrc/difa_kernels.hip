@@ -42,8 +42,8 @@ __device__ __forceinline__ float halves_sum(float x) {
 // that every workgroup ends at the same time, and their pieces leave fp32 partial results that the
 // piece finishing last folds into its own).  Wavefront w owns rows 32*QB*w .. 32*QB*(w+1)-1 as QB 32-row blocks.
 // Key/value tiles of 64 keys are written into 4-stage LDS rings by the buffer-load-to-LDS DMA, K three
-// tiles and V two tiles ahead of their use (two workgroups at head_dim 128, where four stages of whole tiles would fill
-// the LDS twice over: stages of half a tile, K four and V two blocks of 32 keys ahead, a barrier for every block),
+// tiles and V two tiles ahead of their use (with two workgroups on a compute unit: stages of half a tile, K four and V two
+// blocks of 32 keys ahead, a barrier for every block),
 // in the order the work record lists them (text tiles,
 // then the band tiles), so a tile with no allowed pair is never loaded (Sec. 3.1 / 3.3:
 // block-sparse band).  The first tiles and the Q rows of the next segment are requested before
@@ -141,7 +141,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     constexpr int KS = D / 16;              // MFMA k-steps of S^T = K Q^T
     constexpr int DB = D / 32;              // 32-row blocks of O^T
     constexpr int CPR = D / 8;              // 16-byte chunks per K/V row
-    constexpr bool BLK = D == 128 && BM == 128;   // the rings hold 32-key blocks (half tiles) instead of tiles
+    // Two workgroups on a compute unit: the rings hold 32-key blocks (half tiles) instead of tiles.  At head_dim 128 whole
+    // tiles would not fit twice.  At head_dim 64 they would (measured: SD3-like 512 px refresh 90.5 us against 87.0, 1K 145.6 /
+    // 142.3, 2K 1455 / 1441; the smallest call, one tile long, 8.5 / 8.9), but a ring that a tile moves by two stages
+    // needs two copies of the loop body instead of four, and two compute units share 64 KB of instruction cache.
+    constexpr bool BLK = BM == 128;
     constexpr int RKEYS = BLK ? kBN / 2 : kBN;    // keys per ring stage
     constexpr int TILE = RKEYS * D;         // elements of one ring stage
     constexpr int NS = 4;                   // LDS ring depth, K and V alike: tile p lives in stage p % 4
@@ -707,7 +711,6 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     const int m1b = it.kv0_end + (it.nm1_begin > it.kv1_begin ? it.nm1_begin - it.kv1_begin : 0) - it.pos_begin;
     const int m1e = it.kv0_end + ((it.nm1_end < it.kv1_end ? it.nm1_end : it.kv1_end) - it.kv1_begin) - it.pos_begin;
     auto pos_masked = [&](int idx) { return !(idx < m0e || (idx >= m1b && idx < m1e)); };   // [m1b, m1e) are mask-free
-    auto bump = [](int& off) { off = (off + TILE) & (NS * TILE - 1); };          // next ring stage (element offset)
     auto kptr = [&](int off, int jb) { return &Ksm[off + 32 * jb * D]; };
     auto vptr = [&](int off, int jb) { return &Vsm[off + 32 * jb * D]; };
     const unsigned half_tile = tile_bytes / 2;
@@ -715,7 +718,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     auto dst = [&](unsigned base, int off) { return base + (unsigned)(off * 2) + wave_lds; };
     // ring stages as element offsets: K stages of positions idx, idx+1, idx+3, V stages of idx-1, idx, idx+2
     int k_cur = (sbase & 3) * TILE, k_nxt = ((sbase + 1) & 3) * TILE, k_ld = ((sbase + 3) & 3) * TILE;
-    int v_prv = k_cur, v_cur = k_cur, v_ld = ((sbase + 2) & 3) * TILE;
+    int v_cur = k_cur, v_ld = ((sbase + 2) & 3) * TILE;
     bool msk_cur = pos_masked(0), msk_nxt = pos_masked(1);
     unsigned tb_k = tile_offset(BLK ? 2 : 3), tb_v = tile_offset(BLK ? 1 : 2);  // tiles whose K / V loads the coming iteration issues
 
