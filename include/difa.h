@@ -222,7 +222,7 @@ difa_status_t difa_worklist_build(int32_t batch, int32_t heads, const int32_t* h
                                   int32_t* n_copy_out);
 
 /* ------------------------------------------------------------------ host-side schedule
- * The attention kernel is persistent: it is launched with one workgroup per compute unit, and each
+ * The attention kernel is persistent: it is launched with one or two workgroups per compute unit, and each
  * workgroup walks its own list of segments.  A segment is a work record restricted to a range of the
  * positions of its visiting order (position p = the p-th key tile the record visits: the tiles of
  * the first range, then those of the second).  Most segments are whole records; to give every
