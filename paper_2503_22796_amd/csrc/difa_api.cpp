@@ -99,6 +99,7 @@ struct difa_plan {
     std::vector<difa_work_item_t> recs; // host scratch of the work-list compiler
     std::vector<int32_t> keys;          // memo keys: kSlots rows of 2 * heads + 2, then one row for the call's own
     Slot slots[kSlots];
+    int n_slots = kSlots;               // how many of them have a buffer
     Staging stagings[kStagings];
     char* d_slots = nullptr;            // the slots' device buffers and the pinned staging buffers, one allocation each
     char* h_stagings = nullptr;
@@ -391,9 +392,9 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     difa_tile_shape(desc->head_dim, desc->dtype, &p->band_rows, &p->bn);
     const bool bf16 = desc->dtype == DIFA_DTYPE_BF16;
     const int least_rows = bf16 ? difa::kRowsShort : p->band_rows;
-    const int64_t q_tiles = ((int64_t)desc->max_tokens + least_rows - 1) / least_rows;
-    const int64_t cap = (int64_t)desc->batch * desc->heads * q_tiles;
-    if (cap > (int64_t)1 << 24) {
+    auto records = [&](int rows) { return (int64_t)desc->batch * desc->heads * (((int64_t)desc->max_tokens + rows - 1) / rows); };
+    const int64_t cap = records(least_rows);
+    if (records(p->band_rows) > (int64_t)1 << 24) {
         delete p;
         return fail(nullptr, DIFA_ERR_UNSUPPORTED, "batch*heads*query tiles exceeds the work-list limit");
     }
@@ -407,6 +408,8 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
                    ((size_t)cap + 2 * (size_t)p->n_wg) * sizeof(difa_segment_t) + 64 +
                    2 * (size_t)p->n_wg * sizeof(difa_merge_item_t) + 64 + (size_t)cap * sizeof(difa_work_item_t);
     p->buf_bytes = (p->buf_bytes + 255) / 256 * 256;
+    // (up to 256 MB of schedules, and eight of them however large the layer)
+    p->n_slots = (int)std::min<size_t>(kSlots, std::max<size_t>(8, ((size_t)256 << 20) / p->buf_bytes));
     try {
         p->recs.reserve((size_t)cap);
         p->keys.assign((size_t)(kSlots + 1) * (2 * (size_t)desc->heads + 2), 0);
@@ -449,9 +452,9 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     if (e == hipSuccess) {
         what = "allocating work-list buffers";
         e = hipEventCreateWithFlags(&p->order_ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, (size_t)kSlots * p->buf_bytes);
+        if (e == hipSuccess) e = hipMalloc((void**)&p->d_slots, (size_t)p->n_slots * p->buf_bytes);
         if (e == hipSuccess) e = hipHostMalloc((void**)&p->h_stagings, (size_t)kStagings * p->buf_bytes, hipHostMallocDefault);
-        for (int s = 0; s < kSlots && e == hipSuccess; ++s) p->slots[s].d_buf = p->d_slots + (size_t)s * p->buf_bytes;
+        for (int s = 0; s < p->n_slots && e == hipSuccess; ++s) p->slots[s].d_buf = p->d_slots + (size_t)s * p->buf_bytes;
         for (int s = 0; s < kStagings && e == hipSuccess; ++s) {
             p->stagings[s].h_buf = p->h_stagings + (size_t)s * p->buf_bytes;
             e = hipEventCreateWithFlags(&p->stagings[s].copied, hipEventDisableTiming);
@@ -638,7 +641,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
     Slot* slot = nullptr;
     int victim = -1;
     double want[kMaxDies];                                            // die speeds the schedule is to be made again for
-    for (int s = 0; s < kSlots; ++s)
+    for (int s = 0; s < p->n_slots; ++s)
         if (p->slots[s].valid && memcmp(p->keys.data() + (size_t)s * key_len, key, key_len * sizeof(int32_t)) == 0) {
             slot = &p->slots[s];
             if (p->h_times && slot->n_items > 0 && slot->trial < kTrials && slot->timed >= kTrialLaunches[slot->trial] && retune_wanted(*slot, p->n_xcd, want)) {
@@ -651,7 +654,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         const bool retune = victim >= 0;
         if (!retune) {
             victim = 0;
-            for (int s = 0; s < kSlots; ++s) {
+            for (int s = 0; s < p->n_slots; ++s) {
                 if (!p->slots[s].valid) { victim = s; break; }
                 if (p->slots[s].stamp < p->slots[victim].stamp) victim = s;
             }
