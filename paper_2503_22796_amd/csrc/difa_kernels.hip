@@ -1239,7 +1239,11 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
                 for (int e = 0; e < 4; ++e) o[f][e] = o[f][e] * wm + other[4 * f + e][lane] * wo;
         }
     }
-    if (wave == 0 && i0 + c16 < N) {
+    if (wave != 0) return;
+    // The rows whose reference lies outside +-2^24 (see below) as a bit mask, the same in every lane.
+    unsigned long long exact_rows = __builtin_amdgcn_ballot_w64(!(m > -0x1p24 && m < 0x1p24));
+    exact_rows = (exact_rows | exact_rows >> 16 | exact_rows >> 32 | exact_rows >> 48) & 0xffff;
+    if (i0 + c16 < N && !(exact_rows >> c16 & 1)) {
         const double inv = 1.0 / l;
         // register e of o[f] is feature (4 * e + g) * VF + f of the lane's query
 #pragma unroll
@@ -1256,6 +1260,58 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
                 }
                 *(floatx4*)((float*)a.out + at + 4 * s) = w;
             }
+        }
+    }
+    // The loop above compares maxima in fp32 and scales a score to the log2 domain in one fp64 product: right to 4e-9 of a
+    // weight while the largest scaled score is below 2^24, wrong by more with every power of two beyond (from about 2^32 on
+    // the weights overflow or all vanish).  Nothing limits the magnitude of the inputs, so those rows are computed once more
+    // here, by one wavefront, as the operator is defined: maximum of the fp64 scores, weights from exact differences to it.
+    // (As slow as one wavefront per row is; logits of 10^7 are no attention that a model has in earnest.)
+    for (; exact_rows != 0; exact_rows &= exact_rows - 1) {
+        const int r = i0 + __builtin_ctzll(exact_rows);
+        if (r >= N) break;
+        const bool every = !banded || (unsigned)(r - tb) < (unsigned)n_text;
+        auto sees = [&](int j) {
+            return j < N && (every || (unsigned)(j - tb) < (unsigned)n_text || (j >= r - it.window && j - it.window <= r));
+        };
+        auto score = [&](int j) {
+            const float* qr = qg + (int64_t)r * a.stride_n;
+            const float* kr = kg + (int64_t)j * a.stride_n;
+            double s = 0.0;
+#pragma unroll 1
+            for (int d = 0; d < D; d += 4) {
+                const floatx4 x = *(const floatx4*)(qr + d), y = *(const floatx4*)(kr + d);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s = fma((double)x[e], (double)y[e], s);
+            }
+            return s;
+        };
+        double top = -INFINITY;
+        for (int j = lane; j < N; j += 64)
+            if (sees(j)) top = fmax(top, score(j));
+#pragma unroll
+        for (int n = 32; n >= 1; n >>= 1) top = fmax(top, __shfl_xor(top, n, 64));
+        double sum = 0.0, acc[D / 64] = {};                  // lane: features lane, lane + 64
+        for (int j0 = 0; j0 < N; j0 += 64) {
+            const bool mine = sees(j0 + lane);
+            const double p = mine ? (double)exp2f((float)((score(j0 + lane) - top) * c)) : 0.0;
+            sum += p;
+            for (unsigned long long keys = __builtin_amdgcn_ballot_w64(mine); keys != 0; keys &= keys - 1) {
+                const int u = __builtin_ctzll(keys);
+                const double pu = __shfl(p, u, 64);
+                const float* vr = vg + (int64_t)(j0 + u) * a.stride_n;
+#pragma unroll
+                for (int d = 0; d < D / 64; ++d) acc[d] = fma(pu, (double)vr[lane + 64 * d], acc[d]);
+            }
+        }
+#pragma unroll
+        for (int n = 32; n >= 1; n >>= 1) sum += __shfl_xor(sum, n, 64);
+#pragma unroll
+        for (int d = 0; d < D / 64; ++d) {
+            const int64_t at = base + (int64_t)r * a.stride_n + lane + 64 * d;
+            double y = acc[d] / sum;
+            if (it.flags & DIFA_ITEM_ADD_RESIDUAL) y += (double)((const float*)a.residual)[at];
+            ((float*)a.out)[at] = (float)y;
         }
     }
 }

@@ -38,3 +38,53 @@ def test_fp32_tile_edges(D, n_text, n_img, image_first):
             assert torch.equal(got[:, h].view(torch.int32), raw[:, h].contiguous().view(torch.int32))
         else:
             assert float((got[:, h].double() - ref[:, h]).abs().max()) <= TOL_F32, f"head {h}"
+
+
+def _run_f32(q, k, v, hp, win, n_text, n_img, scale=0.0, image_first=False):
+    from paper_2503_22796_amd import binding as B
+    dev = torch.device("cuda:0")
+    b, heads, n, d = q.shape
+    out = torch.full_like(q, float("nan")).to(dev)
+    plan = B.difa_plan_create(b, heads, d, dtype=B.DIFA_DTYPE_F32, max_tokens=n, softmax_scale=scale,
+                              flags=B.DIFA_FLAG_IMAGE_FIRST if image_first else 0)
+    try:
+        B.difa_joint_attention(plan, q.to(dev), k.to(dev), v.to(dev), out, None, hp, n_text, n_img, win)
+        torch.cuda.synchronize()
+    finally:
+        B.difa_plan_destroy(plan)
+    return out.cpu()
+
+
+def _logits(kind, D, N, seed):
+    """Q and K whose scores are of a stated magnitude.  Every entry is an integer and the softmax scale a power of two, so
+    that the scores (below 2^53) and their differences are the same numbers in any order of summation, and what is
+    compared is the softmax alone."""
+    g = torch.Generator().manual_seed(seed)
+    q, k = (torch.randint(-3, 4, (1, 2, N, D), generator=g).float() for _ in range(2))
+    if kind == "all below -1e30":                       # the small entries vanish beside 2^110: two levels of scores
+        q[..., 0], k[..., 0] = 2.0 ** 60, -2.0 ** 50
+        k[:, :, ::3, 0] = -2.0 ** 51
+    elif kind == "beyond fp32":
+        q[..., 0], k[..., 0] = 2.0 ** 75, 2.0 ** 60
+        k[:, :, ::3, 0] = 2.0 ** 59
+    else:                                               # a common part of the stated size under differences of a few units
+        q[..., 0], k[..., 0] = kind[0], kind[1]
+    return q, k
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kind", [(2.0 ** 12, 2.0 ** 11), (2.0 ** 20, 2.0 ** 20), (2.0 ** 24, -2.0 ** 24), "all below -1e30", "beyond fp32"])
+def test_fp32_logits_of_any_finite_magnitude(D, kind):
+    """Nothing limits the magnitude of finite fp32 inputs: rows whose scores are 2^20, 2^37, -2^45, all below -1e30, or beyond
+    fp32's own range.  The bar is the path's own 1e-5: relative to the scores' differences the weights are exact."""
+    from oracle import difa_oracle as O
+    n_text, n_img = 21, 250
+    hp, win = np.asarray([FULL, ARROW], np.int32), np.asarray([0, 40], np.int32)
+    q, k = _logits(kind, D, n_text + n_img, seed=17)
+    v = torch.randn(1, 2, n_text + n_img, D, generator=torch.Generator().manual_seed(18))
+    scale = 2.0 ** -5
+    print(f"f32 logits {kind} D={D}", flush=True)
+    got = _run_f32(q, k, v, hp, win, n_text, n_img, scale=scale)
+    ref, _, _ = O.joint_attention(q, k, v, None, hp, win, n_text, n_img, scale=scale)
+    assert torch.isfinite(got).all()
+    assert float((got.double() - ref).abs().max()) <= TOL_F32
