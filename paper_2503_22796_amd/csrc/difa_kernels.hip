@@ -1240,11 +1240,20 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
         }
     }
     if (wave != 0) return;
-    // The rows whose reference lies outside +-2^24 (see below) as a bit mask, the same in every lane.
-    unsigned long long exact_rows = __builtin_amdgcn_ballot_w64(!(m > -0x1p24 && m < 0x1p24));
+    const double inv = 1.0 / l;
+    double all = l;                                          // not finite if any part of it is
+#pragma unroll
+    for (int f = 0; f < VF; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) all += o[f][e];
+    unsigned high = (unsigned)(__builtin_bit_cast(unsigned long long, all) >> 32);
+    asm volatile("" : "+v"(high));                           // (the file is compiled on the assumption that there are no NaNs)
+    const bool finite = (high >> 20 & 0x7ff) != 0x7ff;
+    // The rows whose reference lies outside +-2^24 or whose result is not finite (see below) as a bit mask, the same in
+    // every lane.
+    unsigned long long exact_rows = __builtin_amdgcn_ballot_w64(!(m > -0x1p24 && m < 0x1p24) || !finite);
     exact_rows = (exact_rows | exact_rows >> 16 | exact_rows >> 32 | exact_rows >> 48) & 0xffff;
     if (i0 + c16 < N && !(exact_rows >> c16 & 1)) {
-        const double inv = 1.0 / l;
         // register e of o[f] is feature (4 * e + g) * VF + f of the lane's query
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1266,7 +1275,10 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
     // weight while the largest scaled score is below 2^24, wrong by more with every power of two beyond (from about 2^32 on
     // the weights overflow or all vanish).  Nothing limits the magnitude of the inputs, so those rows are computed once more
     // here, by one wavefront, as the operator is defined: maximum of the fp64 scores, weights from exact differences to it.
-    // (As slow as one wavefront per row is; logits of 10^7 are no attention that a model has in earnest.)
+    // And the matrix products multiply every key of a visited tile into every row, the forbidden ones with weight 0, which is
+    // not enough against an infinity or a NaN in V: a row that came out not finite is computed from its allowed keys alone, so
+    // that it stays so only if it sees such a value.
+    // (As slow as one wavefront per row is; neither logits of 10^7 nor infinities are what a model has in earnest.)
     for (; exact_rows != 0; exact_rows &= exact_rows - 1) {
         const int r = i0 + __builtin_ctzll(exact_rows);
         if (r >= N) break;

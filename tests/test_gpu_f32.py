@@ -88,3 +88,33 @@ def test_fp32_logits_of_any_finite_magnitude(D, kind):
     ref, _, _ = O.joint_attention(q, k, v, None, hp, win, n_text, n_img, scale=scale)
     assert torch.isfinite(got).all()
     assert float((got.double() - ref).abs().max()) <= TOL_F32
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("image_first", [False, True])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_fp32_a_key_that_is_not_finite_stays_with_the_rows_that_see_it(D, image_first, bad):
+    """Non-finite inputs make the rows that see them undefined and no others: a masked key takes part in the matrix products
+    of its tile with weight 0, which is not enough against an infinity in V."""
+    from oracle import difa_oracle as O
+    n_text, n_img, w = 21, 250, 19
+    N, img0 = n_text + n_img, 0 if image_first else n_text
+    hp, win = np.asarray([ARROW, ARROW, ARROW], np.int32), np.asarray([w, 0, 30], np.int32)
+    g = torch.Generator().manual_seed(23)
+    q, k, v = (torch.randn(1, 3, N, D, generator=g) for _ in range(3))
+    ref, _, _ = O.joint_attention(q, k, v, None, hp, win, n_text, n_img, image_first=image_first)
+    keys = [img0 + 3, img0 + 117, img0 + 118, img0 + n_img - 1]
+    v[:, :, keys[0], D // 2] = bad
+    v[:, :, keys[1]] = bad
+    k[:, :, keys[2], 1] = bad
+    v[:, :, keys[3], D - 1] = bad
+    print(f"f32 not finite: {bad} D={D} image_first={image_first}", flush=True)
+    got = _run_f32(q, k, v, hp, win, n_text, n_img, image_first=image_first)
+    rows = torch.arange(N)
+    image = (rows >= img0) & (rows < img0 + n_img)
+    for h in range(3):
+        blind = image & torch.stack([(rows - j).abs() > int(win[h]) for j in keys]).all(0)
+        assert int(blind.sum()) >= 20
+        assert float((got[:, h, blind].double() - ref[:, h, blind]).abs().max()) <= TOL_F32, f"head {h}"
+    rest = (got[:, 0, img0 + 3, :D // 2].double() - ref[:, 0, img0 + 3, :D // 2]).abs().max()
+    assert float(rest) <= TOL_F32                         # features of V that are finite are not touched either
