@@ -15,6 +15,8 @@
 
 #include "difa_internal.h"
 #include "difa_schedule.h"
+#include "difa_testing.h"
+#include "difa_trial.h"
 
 namespace {
 
@@ -23,9 +25,7 @@ constexpr int kSlots = 32;     // distinct (head plan, n_text, n_img) schedules 
 constexpr int kStagings = 16;  // pinned host buffers the schedules are uploaded from, used in turn
 constexpr int kXcd = 8;        // accelerator dies of an MI355X: workgroup p runs on die p % 8
 
-constexpr int kMaxDies = 16;
-constexpr int kTrials = 4;     // versions of a memoised schedule that are timed, and for how many launches each
-constexpr int kTrialLaunches[kTrials] = {3, 3, 16, 32};
+using difa::kMaxDies;
 constexpr int kRecent = 64;
 
 struct Slot {
@@ -37,18 +37,8 @@ struct Slot {
     bool valid = false;
     uint64_t stamp = 0;
     int64_t die_span[kMaxDies] = {};    // predicted finishing time of each die, in the scheduler's cost units
-    // A schedule is made for die speeds: at first those the plan object has learnt so far, then the rates at which the dies
-    // have gone through this very schedule (how fast a die goes depends on what it is given: dies with short band records
-    // clock higher than dies with full heads).  A version runs until a few launches of it have been timed (kTrialLaunches);
-    // the dies not finishing together, the next one is made from what they took, and one that turned out slower gives
-    // way to the best so far for good.
-    double speed[kMaxDies] = {};        // what the one in the buffer was made for
-    double best_speed[kMaxDies] = {};   // ... the fastest one before it
-    double best_ticks = 0.0;            // mean launch time of that one
-    int trial = 0;                      // versions timed so far; kTrials: settled
+    difa::Trial trial;                  // how it does on the dies
     uint32_t sched_id = 0;              // names this compilation (run-time reports are credited to it)
-    double ticks = 0.0, die_ticks[kMaxDies] = {};   // measured times of the launches and of their dies, summed
-    int timed = 0;
 };
 
 struct Staging {
@@ -106,6 +96,8 @@ struct difa_plan {
     int next_staging = 0;
     uint64_t clock = 0;
     std::string err;
+    int32_t forced_rows = 0;            // for tests, see difa_testing.h
+    int32_t last_slot = -1, last_grid = 0, last_reports = 0;   // ... the last attention call
     bool timing = false;
     std::vector<TimingPair> pending, pool;
     double attn_ms = 0, copy_ms = 0, rse_ms = 0;
@@ -203,15 +195,8 @@ void harvest_die_speeds(difa_plan* p) {
     p->harvested_tag = tag;
     if (l.slot >= 0 && l.slot < kSlots) {                             // the launch's own time, for its schedule's trial
         Slot& sl = p->slots[l.slot];
-        unsigned long long longest = 0;
-        for (int x = 0; x < n_xcd; ++x) longest = std::max(longest, ticks[x]);
-        if (sl.valid && sl.sched_id == l.sched_id && sl.trial < kTrials && longest > 0) {
-            if (p->reports_seen > 0) {                                // (the process's very first launch runs on a cold chip)
-                sl.ticks += (double)longest;
-                for (int x = 0; x < n_xcd; ++x) sl.die_ticks[x] += (double)ticks[x];
-                ++sl.timed;
-            }
-        }
+        // (the process's very first launch runs on a cold chip)
+        if (sl.valid && sl.sched_id == l.sched_id && p->reports_seen > 0) sl.trial.add(ticks, n_xcd);
     }
     ++p->reports_seen;
     double rate[kMaxDies], mean = 0.0;
@@ -234,38 +219,6 @@ void harvest_die_speeds(difa_plan* p) {
         for (int x = 0; x < n_xcd; ++x) g.speed[x] = p->die_speed[x];
         g.n_dies = n_xcd;
     }
-}
-
-// What the timed launches of a memoised schedule say: false if it stays (for now, or for good), true if it is to be made
-// again for the speeds in `want`.
-bool retune_wanted(Slot& s, int n_dies, double* want) {
-    const double mine = s.ticks / s.timed;
-    double mean = 0.0, rate_mean = 0.0, longest = 0.0;
-    for (int x = 0; x < n_dies; ++x) {
-        mean += s.die_ticks[x] / s.timed / n_dies;
-        longest = std::max(longest, s.die_ticks[x] / s.timed);
-    }
-    bool rates = true;                                                // every die was busy long enough to have a rate
-    for (int x = 0; x < n_dies; ++x) {
-        rates &= s.die_span[x] >= 256 && s.die_ticks[x] >= 1000.0 * s.timed;
-        want[x] = rates ? (double)s.die_span[x] * s.timed / s.die_ticks[x] : 1.0;
-        rate_mean += want[x] / n_dies;
-    }
-    for (int x = 0; x < kMaxDies; ++x)
-        want[x] = x < n_dies ? std::min(1.3, std::max(0.7, want[x] / rate_mean)) : 1.0;
-    if (s.trial > 0 && mine > s.best_ticks * 0.997) {                 // the earlier version was faster after all
-        memcpy(want, s.best_speed, sizeof s.best_speed);
-        s.trial = kTrials;
-        return true;
-    }
-    ++s.trial;
-    if (!rates || longest < mean * 1.015 || s.trial == kTrials) {     // the dies finish together, as far as that goes
-        s.trial = kTrials;
-        return false;
-    }
-    memcpy(s.best_speed, s.speed, sizeof s.speed);
-    s.best_ticks = mine;
-    return true;
 }
 
 // Puts what is about to be enqueued on `stream` behind everything this object enqueued before.
@@ -564,16 +517,17 @@ extern "C" difa_status_t difa_plan_timing_read_head_rse(difa_plan_t* p, double* 
 namespace {
 
 // Query rows per record for a bf16 call (see kRowsShort / kRowsLong).
-int record_rows(const difa_plan* p, const int32_t* head_plan, const int32_t* window, int n_text, int n_img) {
-    if (p->desc.head_dim == 64) return difa::kRowsShort;
+int record_rows(int batch, int heads, int head_dim, const int32_t* head_plan, const int32_t* window, int n_text, int n_img,
+                int n_cu) {
+    if (head_dim == 64) return difa::kRowsShort;
     const double n = (double)n_text + n_img;
     double pairs = 0.0;                                               // query-key pairs of the layer, about
-    for (int h = 0; h < p->desc.heads; ++h) {
+    for (int h = 0; h < heads; ++h) {
         if (head_plan[h] == DIFA_HEAD_CACHE) continue;
         const bool full = head_plan[h] == DIFA_HEAD_FULL || window[h] >= n_img - 1;
         pairs += full ? n * n : n_text * n + n_img * (n_text + std::min(2.0 * window[h] + 1.0, (double)n_img));
     }
-    return pairs * p->desc.batch > difa::kLongPairsPerCu * p->n_cu ? difa::kRowsLong : difa::kRowsShort;
+    return pairs * batch > difa::kLongPairsPerCu * n_cu ? difa::kRowsLong : difa::kRowsShort;
 }
 
 // The body of both attention entry points.  static_scratch: partial results of cut records go to the
@@ -644,7 +598,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
     for (int s = 0; s < p->n_slots; ++s)
         if (p->slots[s].valid && memcmp(p->keys.data() + (size_t)s * key_len, key, key_len * sizeof(int32_t)) == 0) {
             slot = &p->slots[s];
-            if (p->h_times && slot->n_items > 0 && slot->trial < kTrials && slot->timed >= kTrialLaunches[slot->trial] && retune_wanted(*slot, p->n_xcd, want)) {
+            if (p->h_times && slot->n_items > 0 && slot->trial.remake_wanted(slot->die_span, p->n_xcd, want)) {
                 victim = s;
                 slot = nullptr;
             }
@@ -662,14 +616,12 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         Slot* lru = &p->slots[victim];
         if (retune) {
             ++p->retunes;
-            memcpy(lru->speed, want, sizeof want);
+            memcpy(lru->trial.speed, want, sizeof want);
         } else {
-            for (int x = 0; x < kMaxDies; ++x) lru->speed[x] = speeds_known ? p->die_speed[x] : 1.0;
-            lru->trial = 0;
+            for (int x = 0; x < kMaxDies; ++x) lru->trial.speed[x] = speeds_known ? p->die_speed[x] : 1.0;
+            lru->trial.trial = 0;
         }
-        lru->ticks = 0.0;
-        memset(lru->die_ticks, 0, sizeof lru->die_ticks);
-        lru->timed = 0;
+        lru->trial.start_version();
         lru->sched_id = ++p->next_sched_id;
         // The device buffer may still be read by launches enqueued earlier: the copy below goes on `stream`,
         // behind all of them.  The pinned buffer it is written into on the host may still be the source of a
@@ -684,7 +636,8 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         lru->valid = false;
         int32_t n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
         char* hb = (char*)stg.h_buf;
-        lru->rows = p->desc.dtype != DIFA_DTYPE_BF16 ? p->band_rows : record_rows(p, head_plan, window, n_text, n_img);
+        lru->rows = p->desc.dtype != DIFA_DTYPE_BF16 ? p->band_rows : p->forced_rows ? p->forced_rows
+                                                               : record_rows(B, H, D, head_plan, window, n_text, n_img, p->n_cu);
         lru->n_wg = p->desc.dtype != DIFA_DTYPE_BF16 ? p->n_wg : p->n_cu * difa::wgs_per_cu(lru->rows);
         difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, lru->rows, p->band_rows, p->bn,
                                                      p->desc.flags, p->recs, (int32_t*)hb, &n_copy);
@@ -699,7 +652,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             const int32_t seg_cap = n_items + 2 * lru->n_wg;
             lru->merges_off = (lru->segs_off + (size_t)seg_cap * sizeof(difa_segment_t) + 63) / 64 * 64;
             const bool dies = p->h_times != nullptr;
-            st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, lru->n_wg, p->n_xcd, dies ? lru->speed : nullptr,
+            st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, lru->n_wg, p->n_xcd, dies ? lru->trial.speed : nullptr,
                                          dies ? lru->die_span : nullptr, (difa_segment_t*)(hb + lru->segs_off),
                                          seg_cap, (int32_t*)(hb + lru->wg_off), &n_segs,
                                          (difa_merge_item_t*)(hb + lru->merges_off), 2 * lru->n_wg, &n_merges, &n_slots);
@@ -836,6 +789,9 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         // copy): 512 workgroups that only look for work took 2 us to start and end.  From a fraction of the grid on nothing is gained.
         const int32_t busy = std::max(slot->n_wg_used, std::min(a.copy_chunks, slot->n_wg));
         const int32_t grid = busy <= slot->n_wg / 4 ? busy : slot->n_wg;
+        p->last_slot = (int32_t)(slot - p->slots);
+        p->last_grid = grid;
+        p->last_reports = a.wg_times != nullptr;
         a.younger_from = p->n_cu;
         e = fast ? difa::launch_attn_bf16(a, D, slot->rows, grid, stream)
                  : difa::launch_attn_f32(a, D, slot->n_items, stream);
@@ -922,4 +878,49 @@ extern "C" difa_status_t difa_head_rse(difa_plan_t* p, const void* y_m, const vo
     if (e != hipSuccess) return fail(p, DIFA_ERR_HIP, hip_msg("influence-metric launch", e));
     return DIFA_OK;
     });
+}
+
+// ---- views for the library's tests (difa_testing.h)
+extern "C" int32_t difa_testing_record_rows(int32_t batch, int32_t heads, int32_t head_dim, const int32_t* head_plan,
+                                            const int32_t* window, int32_t n_text, int32_t n_img, uint32_t, int32_t n_cu) {
+    return record_rows(batch, heads, head_dim, head_plan, window, n_text, n_img, n_cu);
+}
+
+extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int32_t n_versions, const double* die_ticks,
+                                   int32_t n_launches, int32_t* version, double* speeds) {
+    difa::Trial t;
+    for (double& s : t.speed) s = 1.0;
+    int v = 0;
+    for (int i = 0; i < n_launches; ++i) {
+        double want[kMaxDies];
+        if (t.remake_wanted(die_span, n_dies, want)) {
+            ++v;
+            memcpy(t.speed, want, sizeof want);
+            t.start_version();
+        }
+        version[i] = v;
+        for (int x = 0; x < n_dies; ++x) speeds[i * n_dies + x] = t.speed[x];
+        unsigned long long die[kMaxDies];
+        for (int x = 0; x < n_dies; ++x) die[x] = (unsigned long long)die_ticks[std::min(v, n_versions - 1) * n_dies + x];
+        t.add(die, n_dies);
+    }
+}
+
+extern "C" difa_status_t difa_testing_force_rows(difa_plan_t* p, int32_t rows) {
+    if (!p || (rows != 0 && rows != difa::kRowsShort && rows != difa::kRowsLong) || p->desc.dtype != DIFA_DTYPE_BF16 ||
+        (rows == difa::kRowsLong && p->desc.head_dim == 64))
+        return DIFA_ERR_INVALID_ARG;
+    p->forced_rows = rows;
+    for (Slot& s : p->slots) s.valid = false;
+    return DIFA_OK;
+}
+
+extern "C" void difa_testing_last_call(const difa_plan_t* p, int32_t* rows, int32_t* n_wg, int32_t* grid, int32_t* n_pieces,
+                                       int32_t* reports) {
+    const Slot* s = p->last_slot >= 0 ? &p->slots[p->last_slot] : nullptr;
+    *rows = s ? s->rows : 0;
+    *n_wg = s ? s->n_wg : 0;
+    *grid = p->last_grid;
+    *n_pieces = s ? s->n_slots : 0;
+    *reports = p->last_reports;
 }

@@ -14,6 +14,7 @@
 
 #include "difa.h"
 #include "difa_schedule.h"
+#include "difa_testing.h"
 
 namespace {
 
@@ -388,6 +389,7 @@ struct DiePlan {
     std::vector<Placed> placed;        // in the order they were placed; the pieces of a record stand together
     int n_slots = 0;                   // pieces of cut records
     int64_t makespan = 0;
+    int tried = 0;                     // how many times records were dealt out with cuts before this plan was settled on
 };
 
 // A die's records in order of decreasing cost, and the dealing of them.
@@ -487,6 +489,7 @@ struct Die {
     // The best plan a few target loads give.
     DiePlan schedule() const {
         DiePlan best;
+        int tried = 0;
         if (order.empty()) return best;
         LoadHeap heap;
         deal_whole(heap, best);
@@ -519,12 +522,14 @@ struct Die {
                 heap = start;
                 plan.placed = begun.placed;
                 plan.n_slots = 0;
+                ++tried;
                 if (!deal_and_pour(heap, plan, first, target, spare)) continue;
                 if (plan.makespan < best.makespan) std::swap(best, plan);
                 break;
             }
             if (best.makespan * 100 <= mean * 104) break;
         }
+        best.tried = tried;
         return best;
     }
 };
@@ -532,7 +537,7 @@ struct Die {
 difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_item_t>& recs, int32_t n_wg,
                              int32_t n_xcd, const double* die_speed, int64_t* die_span, difa_segment_t* segs,
                              int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs_out, difa_merge_item_t* merges,
-                             int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out) {
+                             int32_t merge_capacity, int32_t* n_merges_out, int32_t* n_slots_out, int32_t* tried = nullptr) {
     // heads in order of decreasing cost, the whole sequence cut into n_xcd runs whose costs are in
     // proportion to the dies' speeds (equal when none are given)
     std::vector<HeadSpan> spans;
@@ -588,6 +593,7 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
             const int budget = slot_capacity - slots_so_far - 2 * per_die * (n_xcd - 1 - x);   // this die's share of the slots
             plans[(size_t)x] = Die{m, recs, die[(size_t)x], die_cost[(size_t)x], per_die, budget}.schedule();
             slots_so_far += plans[(size_t)x].n_slots;
+            if (tried) *tried += plans[(size_t)x].tried;
         }
         // predicted finishing times, in cost units of a die of speed 1
         double t_min = 0.0, t_max = 0.0, t_sum = 0.0;
@@ -701,4 +707,38 @@ difa_status_t difa::schedule_for_dies(const CostModel& m, const std::vector<difa
                                       int32_t* n_slots_out) {
     return schedule_build(m, recs, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin, n_segs_out,
                           merges, merge_capacity, n_merges_out, n_slots_out);
+}
+
+// ---- views for the library's tests (difa_testing.h)
+extern "C" difa_status_t difa_testing_records(int32_t batch, int32_t heads, const int32_t* head_plan, const int32_t* window,
+                                              int32_t n_text, int32_t n_img, int32_t rows, int32_t head_dim, uint32_t flags,
+                                              difa_work_item_t* items, int32_t capacity, int32_t* n_items) {
+    int32_t band_rows = 0, bn = 0, n_copy = 0;
+    if (!n_items || difa_tile_shape(head_dim, DIFA_DTYPE_BF16, &band_rows, &bn) != 0) return DIFA_ERR_INVALID_ARG;
+    try {
+        std::vector<difa_work_item_t> recs;
+        const difa_status_t st = difa::worklist_for_kernel(batch, heads, head_plan, window, n_text, n_img, rows, band_rows, bn, flags,
+                                                           recs, nullptr, &n_copy);
+        if (st != DIFA_OK) return st;
+        *n_items = (int32_t)recs.size();
+        if ((int64_t)recs.size() > capacity) return capacity == 0 && !items ? DIFA_OK : DIFA_ERR_ALLOC;
+        std::copy(recs.begin(), recs.end(), items);
+        return DIFA_OK;
+    } catch (const std::bad_alloc&) {
+        return DIFA_ERR_ALLOC;
+    }
+}
+
+extern "C" difa_status_t difa_testing_schedule(const difa_work_item_t* items, int32_t n_items, int32_t head_dim, int32_t n_wg,
+                                               int32_t n_xcd, const double* die_speed, int64_t* die_span, difa_segment_t* segs,
+                                               int32_t seg_capacity, int32_t* wg_begin, int32_t* n_segs, difa_merge_item_t* merges,
+                                               int32_t merge_capacity, int32_t* n_merges, int32_t* n_slots, int32_t* tried) {
+    *tried = 0;
+    try {
+        const std::vector<difa_work_item_t> recs(items, items + n_items);
+        return schedule_build(difa::kernel_costs(head_dim), recs, n_wg, n_xcd, die_speed, die_span, segs, seg_capacity, wg_begin,
+                              n_segs, merges, merge_capacity, n_merges, n_slots, tried);
+    } catch (const std::bad_alloc&) {
+        return DIFA_ERR_ALLOC;
+    }
 }

@@ -27,17 +27,20 @@ def test_die_speeds_are_learnt_and_the_retuned_schedule_computes_the_same_layer(
         torch.cuda.synchronize()
         out = torch.empty_like(qd)
         seen_retune = retunes
-        for _ in range(14):                       # a report is picked up by the call after the launch has ended
+        settled = []
+        for _ in range(66):                       # a report is picked up by the call after the launch has ended
             out.fill_(float("nan"))
             B.difa_joint_attention(plan, qd, kd, vd, out, cd, wl.head_plan, wl.n_text, wl.n_img, wl.window)
             torch.cuda.synchronize()
             speeds, samples, retunes = B.difa_plan_die_speeds(plan)
             seen_retune = max(seen_retune, retunes)
+            settled.append(retunes)
         if n_dies > 1:
             assert samples >= 6, "no run-time reports were picked up"
             assert all(0.85 <= s <= 1.15 for s in speeds), speeds
             assert abs(sum(speeds) / n_dies - 1.0) < 0.02, speeds
-            assert retunes <= 2
+            # versions run for 3, 3, 16 and 32 launches at most, the process's first launch not counted
+            assert retunes <= 4 and len(set(settled[56:])) == 1, settled
         print(f"dies {n_dies} speeds {[round(s, 3) for s in speeds]} samples {samples} schedules made again {seen_retune}", flush=True)
         # whatever schedule the last call ran on: the same layer
         assert same_result_bf16(out.cpu(), first.cpu())

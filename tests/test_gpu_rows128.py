@@ -32,10 +32,17 @@ def test_short_records(n_text, n_img, flags):
 
 @pytest.mark.parametrize("full", [14, 16])       # 15 of 24 full heads at 16640 tokens are 16 M pairs for each of 256 compute units
 def test_both_sides_of_the_line(full):
+    from paper_2503_22796_amd import binding as B
+    import internal as I
     hp = np.asarray([FULL] * full + [CACHE] * (24 - full), np.int32)
     wl = W.Workload("line", 1, 24, 128, 256, 16384, hp, np.zeros(24, np.int32), seed=860)
     q, k, v = W.make_qkv(wl)
     cache = W.make_cache(wl)
-    out = gpu_joint_attention(q, k, v, cache, hp, wl.window, wl.n_text, wl.n_img)
+    plan = B.difa_plan_create(1, 24, 128, max_tokens=wl.N)
+    try:
+        out = gpu_joint_attention(q, k, v, cache, hp, wl.window, wl.n_text, wl.n_img, plan=plan)
+        assert I.last_call(plan)["rows"] == (128 if full == 14 else 256)
+    finally:
+        B.difa_plan_destroy(plan)
     rows = boundary_rows(wl.n_text, wl.n_img, [], extra=24, seed=full)
     check_against_oracle(out, q, k, v, cache, hp, wl.window, wl.n_text, wl.n_img, rows=rows)

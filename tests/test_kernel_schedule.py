@@ -1,0 +1,140 @@
+"""What the bf16 kernel is given: records of 128 or 256 query rows (with the block-granular band's blocks of 256 rows), their
+schedule at the kernel's own costs on 512 or 256 workgroups, and how a schedule is corrected from its launches' times."""
+import numpy as np
+import pytest
+
+import internal as I
+from paper_2503_22796_amd import binding as B
+from paper_2503_22796_amd import workloads as W
+from test_worklist import _check_schedule
+
+FULL, ARROW, CACHE = 0, 1, 2
+BN, BAND_ROWS = 64, 256
+
+
+def _kept(mode, w, n_text, n_img, image_first, block_band):
+    """Boolean [N, N]: the pairs the operator keeps."""
+    N = n_text + n_img
+    i = np.arange(N)
+    img = (i < n_img) if image_first else (i >= n_text)
+    both = img[:, None] & img[None, :]
+    if mode == FULL or w >= n_img - 1:
+        return np.ones((N, N), bool)
+    keep = ~both | (np.abs(i[:, None] - i[None, :]) <= w)
+    if block_band:
+        dense = np.zeros_like(keep)
+        for i0 in range(0, N, BAND_ROWS):
+            for j0 in range(0, N, BN):
+                if keep[i0:i0 + BAND_ROWS, j0:j0 + BN].any():
+                    dense[i0:i0 + BAND_ROWS, j0:j0 + BN] = True
+        keep = dense
+    return keep
+
+
+@pytest.mark.parametrize("rows", [128, 256])
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+@pytest.mark.parametrize("n_text,n_img", [(0, 1), (1, 127), (100, 155), (130, 126), (127, 130), (200, 600), (333, 900), (64, 0)])
+def test_records_of_the_kernel_match_brute_force(rows, flags, n_text, n_img):
+    N, image_first, block_band = n_text + n_img, bool(flags & B.DIFA_FLAG_IMAGE_FIRST), bool(flags & B.DIFA_FLAG_BLOCK_BAND)
+    hp, win = [FULL, ARROW, ARROW, CACHE, ARROW, ARROW], [0, 0, 63, 0, 64, 129]
+    items = I.records(2, hp, win, n_text, n_img, rows, 128, flags)
+    n_q, n_kv = -(-N // rows), -(-N // BN)
+    assert [(int(r["bh"]), int(r["q_tile"])) for r in items] == [(b * 6 + h, t) for b in range(2) for h in range(6) if hp[h] != CACHE
+                                                                for t in range(n_q)]
+    rot = n_img // BN if image_first and n_text > 0 and n_img > 0 else 0
+    kept = {h: _kept(hp[h], win[h], n_text, n_img, image_first, block_band) for h in range(6) if hp[h] != CACHE}
+    for r in items:
+        k = kept[int(r["bh"]) % 6][r["q_tile"] * rows:(r["q_tile"] + 1) * rows]
+        order = list(range(0, r["kv0_end"])) + list(range(r["kv1_begin"], r["kv1_end"]))
+        visited = [(u + rot) % n_kv for u in order]
+        assert len(visited) == r["n_tiles"] == len(set(visited))
+        some = {t for t in range(n_kv) if k[:, t * BN:(t + 1) * BN].any()}
+        assert some <= set(visited)
+        if block_band or image_first or int(r["window"]) < 0:
+            extra = set()
+        else:                                   # a record with text rows or a tile shared by text and image: exactly these
+            extra = set(visited) - some
+        assert set(visited) == some | extra and len(extra) <= 1
+        for u in order:
+            t = (u + rot) % n_kv
+            free = u < r["nm0_end"] if u < r["kv0_end"] else r["nm1_begin"] <= u < r["nm1_end"]
+            if free:                            # nothing to mask: every row of the record keeps every key of the tile
+                assert (t + 1) * BN <= N and k[:, t * BN:(t + 1) * BN].all()
+    # most tiles of a full head, and of a band much wider than a record, are known to be mask-free
+    for r in items:
+        if hp[int(r["bh"]) % 6] == FULL:
+            free = min(r["nm0_end"], r["kv0_end"]) + max(0, r["nm1_end"] - r["nm1_begin"])
+            assert free >= r["n_tiles"] - 1
+
+
+LAYERS = [W.flux_1k, W.flux_2k_mixed, W.flux_2k_full, W.sd3_1k, W.sd3_2k, W.video_like]
+
+
+@pytest.mark.parametrize("layer", LAYERS, ids=lambda f: f.__name__)
+@pytest.mark.parametrize("speeds", [None, [1.04, 0.97, 1.0, 1.01, 0.98, 1.03, 0.96, 1.01]])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_schedule_of_the_kernel_covers_every_position_once(layer, speeds, flags):
+    wl = layer()
+    for rows, n_wg in ((128, 512),) if wl.D == 64 else ((128, 512), (256, 256)):
+        items = I.records(wl.B, wl.head_plan, wl.window, wl.n_text, wl.n_img, rows, wl.D, flags)
+        segs, wg_begin, merges, n_slots, span, _ = I.schedule(items, wl.D, n_wg, 8, speeds)
+        _check_schedule(items, segs, wg_begin, merges, n_slots, n_wg, 8)
+        assert n_slots * rows * (wl.D + 2) * 4 <= 68157440          # fits the library's file-scope scratch
+        # dies get work in proportion to their speeds: the last one is predicted to finish within 8 % of the mean (a die's
+        # plan ends within a few percent of the load it was given, and shares more than 3 % apart are corrected once)
+        done = span / (np.asarray(speeds) if speeds else np.ones(8))
+        assert done.max() <= 1.08 * done.mean(), (wl.name, rows, done)
+
+
+@pytest.mark.parametrize("n_cut", [0, 1])
+def test_schedule_of_a_few_records(n_cut):
+    # fewer records than workgroups: one each, and a long one is cut only where that ends earlier
+    n_img = 4096 if n_cut else 200
+    items = I.records(1, [FULL, CACHE], [0, 0], 16, n_img, 128, 64)
+    segs, wg_begin, merges, n_slots, _, _ = I.schedule(items, 64, 512)
+    _check_schedule(items, segs, wg_begin, merges, n_slots, 512, 8)
+    assert (len(merges) > 0) == bool(n_cut)
+    if not n_cut:
+        assert np.diff(wg_begin).max() == 1
+
+
+# ----------------------------------------------------------------------------- a schedule's correction
+SPAN = [1000] * 8
+EVEN = [50000.0] * 8
+UNEVEN = [50000.0] * 7 + [54000.0]
+
+
+def test_a_schedule_whose_dies_finish_together_stays():
+    version, speeds = I.trial(SPAN, [EVEN], 80)
+    assert (version == 0).all() and (speeds == 1.0).all()
+
+
+def test_a_better_schedule_replaces_one_whose_dies_finish_apart():
+    version, speeds = I.trial(SPAN, [UNEVEN, EVEN], 80)
+    assert list(version[:4]) == [0, 0, 0, 1] and (version[3:] == 1).all()
+    assert speeds[3, 7] < 0.95 < 1.0 < speeds[3, 0]              # the die that finished last gets less
+    assert abs(speeds[3].mean() - 1.0) < 0.01
+
+
+def test_a_slower_schedule_gives_way_to_the_one_before_it_for_good():
+    worse = [x * 1.05 for x in UNEVEN]
+    version, speeds = I.trial(SPAN, [UNEVEN, worse, UNEVEN], 80)
+    assert list(version[3:6]) == [1, 1, 1] and (version[6:] == 2).all()
+    assert (speeds[6:] == speeds[0]).all()
+
+
+def test_no_schedule_is_made_more_than_four_times_again():
+    better = [[x * f for x in UNEVEN] for f in (1.0, 0.95, 0.9, 0.85, 0.8)]
+    version, _ = I.trial(SPAN, better, 200)
+    assert list(np.flatnonzero(np.diff(version)) + 1) == [3, 6, 22]     # after 3, 3 and 16 launches; 32 more settle it
+    better[3] = UNEVEN                                                  # ... or show that the one before was faster
+    version, speeds = I.trial(SPAN, better, 200)
+    assert list(np.flatnonzero(np.diff(version)) + 1) == [3, 6, 22, 54]
+    assert (speeds[54:] == speeds[21]).all()
+
+
+def test_dies_that_are_hardly_busy_settle_at_once():
+    version, _ = I.trial([100] * 8, [UNEVEN], 80)                # spans too short to say anything about a rate
+    assert (version == 0).all()
+    version, _ = I.trial(SPAN, [[500.0] * 7 + [900.0]], 80)
+    assert (version == 0).all()
