@@ -493,6 +493,13 @@ struct Die {
         if (order.empty()) return best;
         LoadHeap heap;
         deal_whole(heap, best);
+        // A die whose records are all too short to be cut (into two pieces of at least min_piece key tiles) has nothing to gain
+        // below, and belongs to a layer whose call is over before a search would be: 24 heads of 64 and 333 tokens are compiled
+        // in 13 us, in 140 with the search.
+        const auto can_be_cut = [&](const std::pair<int64_t, int>& o) { return recs[(size_t)o.second].n_tiles >= 2 * m.min_piece; };
+        int64_t uncut = 0;                                            // cost of the records that cannot be cut
+        for (const auto& o : order) uncut += can_be_cut(o) ? 0 : o.first;
+        if (uncut == total) return best;
         const int64_t mean = (total + per_die - 1) / per_die;
         DiePlan begun, plan;
         LoadHeap start;
@@ -512,18 +519,26 @@ struct Die {
             // lies depends on how many cuts it takes: none of them costs more than `cut`, and a plan has about one for
             // every other workgroup.
             const int64_t cut = 2 * piece_expected(m) - m.whole;
-            for (const int64_t above : {cut / 8, cut / 3, 2 * cut / 3, cut, 3 * cut / 2}) {
-                const int64_t target = mean + above;
-                if (target >= best.makespan) break;
+            const auto holds_everything = [&](int64_t target) {
                 // (every record longer than the target has to be cut)
                 const int64_t longer = std::partition_point(order.begin(), order.end(), [&](const std::pair<int64_t, int>& o) {
                     return o.first > target; }) - order.begin();
-                if (longer * cut > (target - mean) * per_die) continue;
+                if (longer * cut > (target - mean) * per_die) return false;
                 heap = start;
                 plan.placed = begun.placed;
                 plan.n_slots = 0;
                 ++tried;
-                if (!deal_and_pour(heap, plan, first, target, spare)) continue;
+                return deal_and_pour(heap, plan, first, target, spare);
+            };
+            // Where most of the work is in records that cannot be cut, rooms end with a gap as a rule and no target may hold
+            // everything: the two largest ones say so (not the largest alone: once in 500 layers a smaller one fits by luck).
+            if (2 * uncut > total && mean + 3 * cut / 2 < best.makespan && !holds_everything(mean + 3 * cut / 2) &&
+                !holds_everything(mean + cut))
+                continue;
+            for (const int64_t above : {cut / 8, cut / 3, 2 * cut / 3, cut, 3 * cut / 2}) {
+                const int64_t target = mean + above;
+                if (target >= best.makespan) break;
+                if (!holds_everything(target)) continue;
                 if (plan.makespan < best.makespan) std::swap(best, plan);
                 break;
             }

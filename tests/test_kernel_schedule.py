@@ -138,3 +138,25 @@ def test_dies_that_are_hardly_busy_settle_at_once():
     assert (version == 0).all()
     version, _ = I.trial(SPAN, [[500.0] * 7 + [900.0]], 80)
     assert (version == 0).all()
+
+
+# ----------------------------------------------------------------------------- what compiling a plan takes
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads,n_text,n_img", [(4, 16, 64), (6, 77, 400), (24, 77, 256), (24, 0, 512)])
+def test_a_layer_whose_records_cannot_be_cut_is_compiled_without_a_search(D, heads, n_text, n_img):
+    # records of fewer than 16 key tiles: a piece of a record has at least eight, so every record stays whole; such a layer's
+    # first call is shorter than a search for cuts
+    hp = [FULL] * (heads // 3) + [ARROW] * (heads - heads // 3)
+    items = I.records(1, hp, [0] * (heads // 3) + [30] * (heads - heads // 3), n_text, n_img, 128, D)
+    assert items["n_tiles"].max() < 16
+    segs, wg_begin, merges, n_slots, _, tried = I.schedule(items, D, 512)
+    _check_schedule(items, segs, wg_begin, merges, n_slots, 512, 8)
+    assert tried == 0 and n_slots == 0
+
+
+def test_a_layer_of_mostly_uncuttable_records_is_not_searched_to_the_end():
+    # narrow bands at 2K: 12 or 14 key tiles a record but for the text rows' 264; no target load holds everything, and that is
+    # found out twice for each die and rule, not four or five times
+    items = I.records(1, [ARROW] * 24, [128] * 24, 512, 16384, 128, 128)
+    *_, tried = I.schedule(items, 128, 512)
+    assert tried <= 2 * 2 * 8
