@@ -122,6 +122,10 @@ difa_status_t difa_joint_attention(difa_plan_t* plan, const void* q, const void*
  * Every call of this entry point on one GPU uses the same array, whatever the plan object or stream:
  * two such calls that overlap in time on one GPU race and produce wrong rows; the caller orders them
  * (one stream, or events).  Calls of difa_joint_attention are not affected by it.
+ * Under graph capture (either entry point): make the call once, on the stream that is captured, before capturing it, so
+ * that its schedule is resident and the graph holds the kernel launch alone (an upload recorded into the graph would read a
+ * staging buffer that later uploads overwrite).  A captured schedule is not corrected any more (see difa_plan_die_speeds)
+ * and is the last to give way to schedules of other plans; a graph must not be replayed once the plan object is gone.
  */
 difa_status_t difa_joint_attention_static(difa_plan_t* plan, const void* q, const void* k, const void* v,
                                           void* out, const void* cache, const int32_t* head_plan,

@@ -238,6 +238,28 @@ hipError_t order_behind_earlier_calls(difa_plan* p, hipStream_t stream) {
     return hipSuccess;
 }
 
+// Is what is enqueued on `stream` recorded into a graph?  (The default stream cannot be captured.)
+bool is_capturing(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!stream) return false;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
+// The slot a new schedule goes to: a free one, or the one used longest ago, those that a captured graph launches last.
+int pick_victim(const Slot* slots, int n) {
+    int victim = 0;
+    for (int s = 0; s < n; ++s) {
+        if (!slots[s].valid) return s;
+        const Slot &a = slots[s], &b = slots[victim];
+        if (a.trial.held != b.trial.held ? b.trial.held : a.stamp < b.stamp) victim = s;
+    }
+    return victim;
+}
+
 // Switches to the plan's device for the scope of a call and back afterwards.
 struct DeviceGuard {
     int prev = -1;
@@ -592,13 +614,14 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
     key[2 * H + 1] = n_img;
     harvest_die_speeds(p);
     const bool speeds_known = p->h_times && p->speed_samples >= 3;
+    const bool capturing = is_capturing(stream);
     Slot* slot = nullptr;
     int victim = -1;
     double want[kMaxDies];                                            // die speeds the schedule is to be made again for
     for (int s = 0; s < p->n_slots; ++s)
         if (p->slots[s].valid && memcmp(p->keys.data() + (size_t)s * key_len, key, key_len * sizeof(int32_t)) == 0) {
             slot = &p->slots[s];
-            if (p->h_times && slot->n_items > 0 && slot->trial.remake_wanted(slot->die_span, p->n_xcd, want)) {
+            if (slot->trial.remake_wanted(slot->die_span, p->n_xcd, want, capturing)) {
                 victim = s;
                 slot = nullptr;
             }
@@ -606,13 +629,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         }
     if (!slot) {
         const bool retune = victim >= 0;
-        if (!retune) {
-            victim = 0;
-            for (int s = 0; s < p->n_slots; ++s) {
-                if (!p->slots[s].valid) { victim = s; break; }
-                if (p->slots[s].stamp < p->slots[victim].stamp) victim = s;
-            }
-        }
+        if (!retune) victim = pick_victim(p->slots, p->n_slots);
         Slot* lru = &p->slots[victim];
         if (retune) {
             ++p->retunes;
@@ -620,6 +637,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         } else {
             for (int x = 0; x < kMaxDies; ++x) lru->trial.speed[x] = speeds_known ? p->die_speed[x] : 1.0;
             lru->trial.trial = 0;
+            lru->trial.held = capturing;
         }
         lru->trial.start_version();
         lru->sched_id = ++p->next_sched_id;
@@ -887,13 +905,13 @@ extern "C" int32_t difa_testing_record_rows(int32_t batch, int32_t heads, int32_
 }
 
 extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int32_t n_versions, const double* die_ticks,
-                                   int32_t n_launches, int32_t* version, double* speeds) {
+                                   int32_t n_launches, const int32_t* capturing, int32_t* version, double* speeds) {
     difa::Trial t;
     for (double& s : t.speed) s = 1.0;
     int v = 0;
     for (int i = 0; i < n_launches; ++i) {
         double want[kMaxDies];
-        if (t.remake_wanted(die_span, n_dies, want)) {
+        if (t.remake_wanted(die_span, n_dies, want, capturing && capturing[i])) {
             ++v;
             memcpy(t.speed, want, sizeof want);
             t.start_version();
@@ -904,6 +922,16 @@ extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int3
         for (int x = 0; x < n_dies; ++x) die[x] = (unsigned long long)die_ticks[std::min(v, n_versions - 1) * n_dies + x];
         t.add(die, n_dies);
     }
+}
+
+extern "C" int32_t difa_testing_victim(int32_t n, const int32_t* valid, const int32_t* held, const int64_t* stamp) {
+    std::vector<Slot> slots((size_t)n);
+    for (int s = 0; s < n; ++s) {
+        slots[(size_t)s].valid = valid[s] != 0;
+        slots[(size_t)s].trial.held = held[s] != 0;
+        slots[(size_t)s].stamp = (uint64_t)stamp[s];
+    }
+    return pick_victim(slots.data(), n);
 }
 
 extern "C" difa_status_t difa_testing_force_rows(difa_plan_t* p, int32_t rows) {

@@ -24,9 +24,12 @@ difa_status_t difa_testing_schedule(const difa_work_item_t* items, int32_t n_ite
 int32_t difa_testing_record_rows(int32_t batch, int32_t heads, int32_t head_dim, const int32_t* head_plan, const int32_t* window,
                                  int32_t n_text, int32_t n_img, uint32_t flags, int32_t n_cu);
 // n_launches launches of one memoised schedule, each timed by the next call.  die_ticks[v][n_dies]: what the dies take on its
-// version v (the last row for all later ones).  version[i]: the version launch i runs; speeds[i][n_dies]: what it was made for.
+// version v (the last row for all later ones).  capturing[i]: launch i is recorded into a graph (NULL: none is).  version[i]: the
+// version launch i runs; speeds[i][n_dies]: what it was made for.
 void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int32_t n_versions, const double* die_ticks, int32_t n_launches,
-                        int32_t* version, double* speeds);
+                        const int32_t* capturing, int32_t* version, double* speeds);
+// Which of n resident schedules gives way to a new one: in use or free, launched by a captured graph, time of its last use.
+int32_t difa_testing_victim(int32_t n, const int32_t* valid, const int32_t* held, const int64_t* stamp);
 
 // ---- plan objects
 // Query rows per record from the next call on: 128, 256 (head_dim 128), or 0 for the library's own choice.  The plan object

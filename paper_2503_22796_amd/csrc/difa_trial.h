@@ -23,6 +23,7 @@ struct Trial {
     int trial = 0;                      // versions timed so far; kTrials: settled
     double ticks = 0.0, die_ticks[kMaxDies] = {};   // measured times of this version's launches and of their dies, summed
     int timed = 0;
+    bool held = false;                  // a captured graph launches this schedule: its buffer is to stay as it is
 
     void start_version() {
         ticks = 0.0;
@@ -40,8 +41,12 @@ struct Trial {
     }
     // What the timed launches say: false if the schedule stays (for now, or for good), true if it is to be made again for
     // the speeds in `want`.  die_span: predicted finishing time of each die, in the scheduler's cost units.
-    bool remake_wanted(const int64_t* die_span, int n_dies, double* want) {
-        if (trial >= kTrials || timed < kTrialLaunches[trial]) return false;
+    // capturing: the launch that is about to be made is recorded into a graph.  A remake would put its upload into the graph,
+    // from a staging buffer that later uploads overwrite, and a later one would change under the graph what it launches: a
+    // schedule that has been captured is not made again.
+    bool remake_wanted(const int64_t* die_span, int n_dies, double* want, bool capturing) {
+        held |= capturing;
+        if (held || trial >= kTrials || timed < kTrialLaunches[trial]) return false;
         const double mine = ticks / timed;
         double mean = 0.0, rate_mean = 0.0, longest = 0.0;
         for (int x = 0; x < n_dies; ++x) {

@@ -10,7 +10,8 @@ _L = B.lib
 _L.difa_testing_records.argtypes = [_i32, _i32, _vp, _vp, _i32, _i32, _i32, _i32, ctypes.c_uint32, _vp, _i32, _i32p]
 _L.difa_testing_schedule.argtypes = [_vp, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _i32, _vp, _i32p, _vp, _i32, _i32p, _i32p, _i32p]
 _L.difa_testing_record_rows.argtypes = [_i32, _i32, _i32, _vp, _vp, _i32, _i32, ctypes.c_uint32, _i32]
-_L.difa_testing_trial.argtypes = [_i32, _vp, _i32, _vp, _i32, _vp, _vp]
+_L.difa_testing_trial.argtypes = [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp]
+_L.difa_testing_victim.argtypes = [_i32, _vp, _vp, _vp]
 _L.difa_testing_trial.restype = None
 _L.difa_testing_force_rows.argtypes = [_vp, _i32]
 _L.difa_testing_last_call.argtypes = [_vp] + [_i32p] * 5
@@ -55,13 +56,20 @@ def record_rows(batch, head_dim, head_plan, window, n_text, n_img, flags=0, n_cu
     return _L.difa_testing_record_rows(batch, len(hp), head_dim, hp.ctypes.data, win.ctypes.data, n_text, n_img, flags, n_cu)
 
 
-def trial(die_span, die_ticks, n_launches):
-    """(version each launch runs, speeds each launch's schedule was made for) when version v takes die_ticks[v] on the dies."""
+def trial(die_span, die_ticks, n_launches, capturing=None):
+    """(version each launch runs, speeds each launch's schedule was made for) when version v takes die_ticks[v] on the dies and
+    the launches in `capturing` are recorded into a graph."""
+    cap = _i32a([i in (capturing or ()) for i in range(n_launches)])
     span = np.ascontiguousarray(die_span, dtype=np.int64)
     ticks = np.ascontiguousarray(die_ticks, dtype=np.float64)
     version, speeds = np.zeros(n_launches, np.int32), np.zeros((n_launches, len(span)))
-    _L.difa_testing_trial(len(span), span.ctypes.data, len(ticks), ticks.ctypes.data, n_launches, version.ctypes.data, speeds.ctypes.data)
+    _L.difa_testing_trial(len(span), span.ctypes.data, len(ticks), ticks.ctypes.data, n_launches, cap.ctypes.data, version.ctypes.data, speeds.ctypes.data)
     return version, speeds
+
+
+def victim(valid, held, stamp):
+    v, h, s = _i32a(valid), _i32a(held), np.ascontiguousarray(stamp, dtype=np.int64)
+    return _L.difa_testing_victim(len(v), v.ctypes.data, h.ctypes.data, s.ctypes.data)
 
 
 def force_rows(plan, rows):

@@ -140,6 +140,22 @@ def test_dies_that_are_hardly_busy_settle_at_once():
     assert (version == 0).all()
 
 
+def test_a_schedule_that_a_captured_graph_launches_is_not_made_again():
+    # a remake due at the very launch that is captured, and one that would be due later
+    for at in (3, 2, 10):
+        version, _ = I.trial(SPAN, [UNEVEN, EVEN], 80, capturing=[at])
+        before, _ = I.trial(SPAN, [UNEVEN, EVEN], 80)
+        assert (version[:at] == before[:at]).all() and (version[at:] == version[at - 1]).all()
+
+
+def test_resident_schedules_give_way_in_order_of_use_captured_ones_last():
+    assert I.victim([1, 1, 0, 1], [0, 0, 0, 0], [4, 1, 9, 2]) == 2          # a free place
+    assert I.victim([1, 1, 1, 1], [0, 0, 0, 0], [4, 1, 9, 2]) == 1
+    assert I.victim([1, 1, 1, 1], [0, 1, 0, 0], [4, 1, 9, 2]) == 3
+    assert I.victim([1, 1, 1, 1], [1, 1, 0, 1], [4, 1, 9, 2]) == 2
+    assert I.victim([1, 1, 1, 1], [1, 1, 1, 1], [4, 1, 9, 2]) == 1          # nothing else left
+
+
 # ----------------------------------------------------------------------------- what compiling a plan takes
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("heads,n_text,n_img", [(4, 16, 64), (6, 77, 400), (24, 77, 256), (24, 0, 512)])
