@@ -767,17 +767,6 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         a.scale = p->scale;
         if (fast) {
             a.tickets = p->ctl;
-            if (p->h_times && slot->n_items > 0) {
-                if (++p->launch_tag == 0) p->launch_tag = 1;
-                a.wg_times = p->d_times;
-                a.launch_tag = p->launch_tag;
-                difa_plan::Launch& l = p->recent[p->launch_tag % kRecent];
-                l.tag = p->launch_tag;
-                l.slot = (int)(slot - p->slots);
-                l.sched_id = slot->sched_id;
-                l.n_wg = slot->n_wg;
-                memcpy(l.span, slot->die_span, sizeof l.span);
-            }
         }
         if (copies) {
             const int vec_per_row = (int)(D * es / 16);                     // 8, 16 or 32: a power of two
@@ -807,6 +796,19 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         // copy): 512 workgroups that only look for work took 2 us to start and end.  From a fraction of the grid on nothing is gained.
         const int32_t busy = std::max(slot->n_wg_used, std::min(a.copy_chunks, slot->n_wg));
         const int32_t grid = busy <= slot->n_wg / 4 ? busy : slot->n_wg;
+        // Run times are asked for where every workgroup of the schedule runs: a part of the grid says nothing about the dies, and
+        // its reports would land on those of an earlier layer that nobody has read yet.
+        if (p->h_times && grid == slot->n_wg) {
+            if (++p->launch_tag == 0) p->launch_tag = 1;
+            a.wg_times = p->d_times;
+            a.launch_tag = p->launch_tag;
+            difa_plan::Launch& l = p->recent[p->launch_tag % kRecent];
+            l.tag = p->launch_tag;
+            l.slot = (int)(slot - p->slots);
+            l.sched_id = slot->sched_id;
+            l.n_wg = slot->n_wg;
+            memcpy(l.span, slot->die_span, sizeof l.span);
+        }
         p->last_slot = (int32_t)(slot - p->slots);
         p->last_grid = grid;
         p->last_reports = a.wg_times != nullptr;

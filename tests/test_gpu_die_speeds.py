@@ -48,3 +48,27 @@ def test_die_speeds_are_learnt_and_the_retuned_schedule_computes_the_same_layer(
         check_against_oracle(out.cpu(), q, k, v, cache, wl.head_plan, wl.window, wl.n_text, wl.n_img, rows=rows)
     finally:
         B.difa_plan_destroy(plan)
+
+
+def test_reports_of_a_large_layer_survive_small_calls_behind_it():
+    """A layer of a few records is launched on a part of the grid, and its workgroups' reports say nothing; they must not land
+    on those of the large layer before it, which the next call is to read."""
+    from paper_2503_22796_amd import binding as B
+    dev = torch.device("cuda:0")
+    wl = W.flux_1k()
+    q, k, v = (t.to(dev) for t in W.make_qkv(wl))
+    cache = W.make_cache(wl).to(dev)
+    out = torch.empty_like(q)
+    small = torch.empty(1, wl.H, 80, wl.D, dtype=torch.bfloat16, device=dev)
+    plan = B.difa_plan_create(wl.B, wl.H, wl.D, max_tokens=wl.N)
+    try:
+        speeds, before, _ = B.difa_plan_die_speeds(plan)
+        for _ in range(12):
+            B.difa_joint_attention(plan, q, k, v, out, cache, wl.head_plan, wl.n_text, wl.n_img, wl.window)
+            B.difa_joint_attention(plan, q, k, v, small, None, [1] * wl.H, 16, 64, [8] * wl.H)
+            torch.cuda.synchronize()
+        _, after, _ = B.difa_plan_die_speeds(plan)
+    finally:
+        B.difa_plan_destroy(plan)
+    if len(speeds) > 1:
+        assert after >= before + 10, (before, after)
