@@ -772,17 +772,16 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             const int vec_per_row = (int)(D * es / 16);                     // 8, 16 or 32: a power of two
             int shift = 0;
             while ((1 << shift) < vec_per_row) ++shift;
-            const int64_t head_vecs = (int64_t)N << shift, chunk = fast ? difa::copy_chunk_vecs(slot->rows) : difa::kF32CopyVecs;
-            const int64_t per_head = (head_vecs + chunk - 1) / chunk, chunks = (int64_t)B * slot->n_copy * per_head;
-            if (head_vecs > INT32_MAX - chunk || chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
+            const difa::CopySplit split = difa::copy_split(N, vec_per_row, fast ? difa::copy_chunk_vecs(slot->rows) : difa::kF32CopyVecs, B, slot->n_copy);
+            if (split.chunks > INT32_MAX) return fail(p, DIFA_ERR_UNSUPPORTED, "too many cached-head chunks");
             a.copy_src = cache;
             a.copy_heads = (const int32_t*)slot->d_buf;
             a.copy_stride_b = sb * (int64_t)es; a.copy_stride_h = sh * (int64_t)es; a.copy_stride_n = sn * (int64_t)es;
             a.n_copy = slot->n_copy;
             a.copy_vec_shift = shift;
-            a.copy_head_vecs = (int32_t)head_vecs;
-            a.copy_chunks_per_head = (int32_t)per_head;
-            a.copy_chunks = (int32_t)chunks;
+            a.copy_head_vecs = split.head_vecs;
+            a.copy_chunks_per_head = (int32_t)split.per_head;
+            a.copy_chunks = (int32_t)split.chunks;
         }
         if (!fast) {
             const int64_t blocks = (int64_t)slot->n_items * (difa::kBM / difa::kF32BlockRows);
@@ -924,6 +923,12 @@ extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int3
         for (int x = 0; x < n_dies; ++x) die[x] = (unsigned long long)die_ticks[std::min(v, n_versions - 1) * n_dies + x];
         t.add(die, n_dies);
     }
+}
+
+extern "C" int32_t difa_testing_copy_chunks(int64_t n_tokens, int32_t head_dim, int32_t dtype, int32_t batch, int32_t n_copy) {
+    const int64_t chunk = dtype == DIFA_DTYPE_BF16 ? difa::copy_chunk_vecs(difa::kRowsShort) : difa::kF32CopyVecs;
+    const int64_t chunks = difa::copy_split(n_tokens, head_dim * (int64_t)elem_size(dtype) / 16, chunk, batch, n_copy).chunks;
+    return chunks > INT32_MAX ? -1 : (int32_t)chunks;
 }
 
 extern "C" int32_t difa_testing_victim(int32_t n, const int32_t* valid, const int32_t* held, const int64_t* stamp) {

@@ -28,6 +28,13 @@ constexpr int copy_chunk_vecs(int rows) { return 32 * rows; }   // 16-byte vecto
 constexpr int kF32BlockRows = 16;      // fp32 kernel: query rows per workgroup
 constexpr int kF32CopyVecs = 16 * 512; // ... and 16-byte vectors per chunk of its cached-head copy
 
+// The cached-head copy of a layer as chunks of `chunk` 16-byte vectors.
+struct CopySplit { int64_t head_vecs, per_head, chunks; };
+inline CopySplit copy_split(int64_t n_tokens, int64_t vec_per_row, int64_t chunk, int64_t batch, int64_t n_copy) {
+    const int64_t head_vecs = n_tokens * vec_per_row, per_head = (head_vecs + chunk - 1) / chunk;
+    return {head_vecs, per_head, batch * n_copy * per_head};
+}
+
 // Arguments common to the attention kernels.  Strides are in elements.
 struct AttnArgs {
     const void* q;
@@ -49,7 +56,7 @@ struct AttnArgs {
     int32_t n_copy;
     int32_t copy_chunks;            // batch * n_copy * copy_chunks_per_head; 0: nothing to copy
     int32_t copy_chunks_per_head;
-    int32_t copy_head_vecs;         // 16-byte vectors per (batch entry, head): n_tokens << copy_vec_shift
+    int64_t copy_head_vecs;         // 16-byte vectors per (batch entry, head): n_tokens << copy_vec_shift (bf16: below 2^27)
     int32_t copy_vec_shift;         // log2(16-byte vectors per token row)
     int64_t stride_b, stride_h, stride_n;
     int32_t heads, n_tokens, n_text;

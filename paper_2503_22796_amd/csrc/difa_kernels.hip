@@ -113,24 +113,26 @@ template <int THREADS>
 __device__ __forceinline__ void copy_vectors(const AttnArgs& ca, int chunk, int tid) {
     constexpr int PER = 16;
     const int per_head = ca.copy_chunks_per_head, n_copy = ca.n_copy, shift = ca.copy_vec_shift;
-    const int head_vecs = ca.copy_head_vecs;
     const int64_t row_bytes = ca.copy_stride_n;
     const int hh = chunk / per_head, cc = chunk - hh * per_head;
     const int bb = hh / n_copy, head = ca.copy_heads[hh - bb * n_copy];
-    const int64_t base = (int64_t)bb * ca.copy_stride_b + (int64_t)head * ca.copy_stride_h;
+    // a chunk is whole token rows: its first one is found in 64 bits (a head may hold 2^31 vectors and more), the rest in 32
+    const int64_t first = (int64_t)cc * (PER * THREADS), left = ca.copy_head_vecs - first;
+    const int vecs = left < PER * THREADS ? (int)left : PER * THREADS;
+    const int64_t base = (int64_t)bb * ca.copy_stride_b + (int64_t)head * ca.copy_stride_h + (first >> shift) * row_bytes;
     const char* __restrict__ src = (const char*)ca.copy_src + base;
     char* __restrict__ dst = (char*)ca.out + base;
     uintx4 val[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int vi = cc * (PER * THREADS) + u * THREADS + tid;              // vector inside the head
-        const int vr = vi < head_vecs ? vi : head_vecs - 1;                   // past the end: reread the last one, store nothing
+        const int vi = u * THREADS + tid;                                     // vector inside the chunk
+        const int vr = vi < vecs ? vi : vecs - 1;                             // past the end: reread the last one, store nothing
         val[u] = *(const uintx4*)(src + (vr >> shift) * row_bytes + (vr & ((1 << shift) - 1)) * 16);
     }
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int vi = cc * (PER * THREADS) + u * THREADS + tid;
-        if (vi < head_vecs) *(uintx4*)(dst + (vi >> shift) * row_bytes + (vi & ((1 << shift) - 1)) * 16) = val[u];
+        const int vi = u * THREADS + tid;
+        if (vi < vecs) *(uintx4*)(dst + (vi >> shift) * row_bytes + (vi & ((1 << shift) - 1)) * 16) = val[u];
     }
 }
 
@@ -327,7 +329,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         constexpr int PER = copy_chunk_vecs(BM) / (NW * 64);          // vectors per thread and chunk, all in flight together
         const AttnArgs* ca = cold_args();
         const int per_head = ca->copy_chunks_per_head, n_copy = ca->n_copy, shift = ca->copy_vec_shift;
-        const int head_vecs = ca->copy_head_vecs;
+        const int head_vecs = (int)ca->copy_head_vecs;
         const unsigned row_bytes = (unsigned)ca->copy_stride_n;     // (a head spans less than 2 GiB)
         const int hh = chunk / per_head, cc = chunk - hh * per_head;
         const int bb = hh / n_copy, head = ca->copy_heads[hh - bb * n_copy];

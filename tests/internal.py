@@ -13,6 +13,7 @@ _L.difa_testing_record_rows.argtypes = [_i32, _i32, _i32, _vp, _vp, _i32, _i32, 
 _L.difa_testing_trial.argtypes = [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp]
 _L.difa_testing_victim.argtypes = [_i32, _vp, _vp, _vp]
 _L.difa_testing_trial.restype = None
+_L.difa_testing_copy_chunks.argtypes = [ctypes.c_int64, _i32, _i32, _i32, _i32]
 _L.difa_testing_force_rows.argtypes = [_vp, _i32]
 _L.difa_testing_last_call.argtypes = [_vp] + [_i32p] * 5
 _L.difa_testing_last_call.restype = None
@@ -80,3 +81,7 @@ def last_call(plan):
     v = [_i32(0) for _ in range(5)]
     _L.difa_testing_last_call(plan, *[ctypes.byref(x) for x in v])
     return dict(zip(("rows", "n_wg", "grid", "n_pieces", "reports"), (x.value for x in v)))
+
+
+def copy_chunks(n_tokens, head_dim, dtype, batch, n_copy):
+    return _L.difa_testing_copy_chunks(n_tokens, head_dim, dtype, batch, n_copy)

@@ -176,3 +176,13 @@ def test_a_layer_of_mostly_uncuttable_records_is_not_searched_to_the_end():
     items = I.records(1, [ARROW] * 24, [128] * 24, 512, 16384, 128, 128)
     *_, tried = I.schedule(items, 128, 512)
     assert tried <= 2 * 2 * 8
+
+
+# ----------------------------------------------------------------------------- the cached-head copy
+def test_cached_heads_of_any_length_can_share_the_fp32_launch():
+    # chunks of 8192 vectors of 16 bytes; a head of 2^26 tokens of 128 floats has 2^31 vectors, one more than an int holds
+    assert I.copy_chunks(1, 64, B.DIFA_DTYPE_F32, 1, 1) == 1
+    assert I.copy_chunks(256, 128, B.DIFA_DTYPE_F32, 2, 3) == 6
+    assert I.copy_chunks(257, 128, B.DIFA_DTYPE_F32, 2, 3) == 12
+    assert I.copy_chunks(1 << 26, 128, B.DIFA_DTYPE_F32, 1, 1) == 1 << 18
+    assert I.copy_chunks((1 << 30) - 1, 128, B.DIFA_DTYPE_F32, 1, 2) == 1 << 23
