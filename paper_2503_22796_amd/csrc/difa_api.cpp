@@ -538,18 +538,29 @@ extern "C" difa_status_t difa_plan_timing_read_head_rse(difa_plan_t* p, double* 
 
 namespace {
 
-// Query rows per record for a bf16 call (see kRowsShort / kRowsLong).
+// Query rows per record for a bf16 call (the lines and what they rest on: kRowsShort / kRowsLong).
 int record_rows(int batch, int heads, int head_dim, const int32_t* head_plan, const int32_t* window, int n_text, int n_img,
-                int n_cu) {
+                uint32_t flags, int n_cu) {
     if (head_dim == 64) return difa::kRowsShort;
     const double n = (double)n_text + n_img;
-    double pairs = 0.0;                                               // query-key pairs of the layer, about
+    const bool block_band = (flags & DIFA_FLAG_BLOCK_BAND) != 0;
+    double pairs = 0.0, image_keys = 0.0, visited = 0.0, saved = 0.0; // of the layer, about
+    int computed = 0;
     for (int h = 0; h < heads; ++h) {
         if (head_plan[h] == DIFA_HEAD_CACHE) continue;
         const bool full = head_plan[h] == DIFA_HEAD_FULL || window[h] >= n_img - 1;
+        // keys that an image row's record visits
+        const auto keys = [&](int rows) { return full ? n : std::min(n, n_text + 2.0 * window[h] + rows + difa::kBN); };
         pairs += full ? n * n : n_text * n + n_img * (n_text + std::min(2.0 * window[h] + 1.0, (double)n_img));
+        image_keys += keys(difa::kRowsLong);
+        visited += n_text * n + n_img * keys(difa::kRowsLong);
+        saved += block_band ? 0.0 : n_img * (keys(difa::kRowsLong) - keys(difa::kRowsShort));
+        ++computed;
     }
-    return pairs * batch > difa::kLongPairsPerCu * n_cu ? difa::kRowsLong : difa::kRowsShort;
+    pairs *= (double)batch / n_cu;
+    if (pairs > difa::kLongPairsPerCu) return difa::kRowsLong;
+    if (pairs < difa::kShortPairsPerCu || image_keys < difa::kShortKeys * computed) return difa::kRowsShort;
+    return saved < difa::kShortSaves * visited ? difa::kRowsLong : difa::kRowsShort;
 }
 
 // The body of both attention entry points.  static_scratch: partial results of cut records go to the
@@ -655,7 +666,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         int32_t n_copy = 0, n_segs = 0, n_merges = 0, n_slots = 0;
         char* hb = (char*)stg.h_buf;
         lru->rows = p->desc.dtype != DIFA_DTYPE_BF16 ? p->band_rows : p->forced_rows ? p->forced_rows
-                                                               : record_rows(B, H, D, head_plan, window, n_text, n_img, p->n_cu);
+                                                               : record_rows(B, H, D, head_plan, window, n_text, n_img, p->desc.flags, p->n_cu);
         lru->n_wg = p->desc.dtype != DIFA_DTYPE_BF16 ? p->n_wg : p->n_cu * difa::wgs_per_cu(lru->rows);
         difa_status_t st = difa::worklist_for_kernel(B, H, head_plan, window, n_text, n_img, lru->rows, p->band_rows, p->bn,
                                                      p->desc.flags, p->recs, (int32_t*)hb, &n_copy);
@@ -901,8 +912,8 @@ extern "C" difa_status_t difa_head_rse(difa_plan_t* p, const void* y_m, const vo
 
 // ---- views for the library's tests (difa_testing.h)
 extern "C" int32_t difa_testing_record_rows(int32_t batch, int32_t heads, int32_t head_dim, const int32_t* head_plan,
-                                            const int32_t* window, int32_t n_text, int32_t n_img, uint32_t, int32_t n_cu) {
-    return record_rows(batch, heads, head_dim, head_plan, window, n_text, n_img, n_cu);
+                                            const int32_t* window, int32_t n_text, int32_t n_img, uint32_t flags, int32_t n_cu) {
+    return record_rows(batch, heads, head_dim, head_plan, window, n_text, n_img, flags, n_cu);
 }
 
 extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int32_t n_versions, const double* die_ticks,

@@ -17,11 +17,24 @@ constexpr int kBN = 64;   // keys per K/V tile
 // MI355X 2050 against 2190-2360; SD3-like 512 px layers 1.13 times as fast, the 1K layer up to 1.05; at 2K (where the clock
 // gives way as the loop gets denser) the same.  64 rows per wavefront as well: 2010 clocks, 2K the same, 1K 0.75 times.
 // head_dim 128: the loop takes the same 2870-2940 clocks both ways, and the second copy of every tile costs 4-5 % of the
-// clock the chip holds (1.64 against 1.72 GHz on the all-full 2K layer), which long layers do not get back.  256 rows against
-// 128, by query-key pairs per compute unit: 0.9 M (FLUX-like 1K) 132 / 126 us, 8.6 M (2K mixed) 1001 / 993, 11 M (video-like)
-// 1350 / 1334, 26.8 M (2K all-full) 2928 / 3001.
+// clock the chip holds (1.64 against 1.72 GHz on the all-full 2K layer).  Short records earn that back where a band covers
+// noticeably fewer keys for 128 rows than for 256, where records are few tiles long, and where the layer is too small to fill
+// the chip otherwise; with heads that see every key, or blocks of 256 rows, there is nothing to earn.  256 rows against 128, us
+// (one MI355X, 24 heads but where said; "saved": share of the key tiles that the shorter records do not visit):
+//   all full              1536 tokens 43.2 / 45.2, 4608 236 / 240, 9216 859 / 890, 13056 1739 / 1756, 16896 2846 / 2948
+//   ... of few heads      1536 tokens, 6 heads 39.7 / 27.9, 12 heads 32.9 / 33.4; 2560 tokens, 6 heads 34.5 / 35.8
+//   ... short             768 tokens 25.9 / 19.4, 300 tokens 17.0 / 12.8
+//   block-granular band   16896 tokens, w = 2048 894 / 934, 1024 603 / 605, 512 447 / 444, 128 (17 tiles a record) 376 / 324;
+//                         mixed plan 943 / 960
+//   full and w = N / 16   12 + 12 at 9216 tokens (1.0 % saved) 560 / 567, at 4608 (1.8 %) 172.6 / 175.4;
+//                         8 + 16 at 9216 (1.7 %) 462 / 457; 4 + 20 at 16896 (1.8 %) 1020 / 1011; mixed 2K (1.2 %) 1001 / 993
+//   all arrow             16896 tokens, w = 4224 (1.3 %, 14.6 M pairs a compute unit) 1477 / 1526, 2112 (2.3 %) 939 / 936,
+//                         528 (5.3 %) 498 / 468; pairs of them, w = 2048 (2.4 %, 15.8 M) 1824 / 1846, 1024 (9.5 M) 1231 / 1207
 constexpr int kRowsShort = 128, kRowsLong = 256;
-constexpr double kLongPairsPerCu = 16.0e6;                      // more pairs than that per compute unit: 256 rows (head_dim 128)
+constexpr double kLongPairsPerCu = 14.0e6;   // head_dim 128, query-key pairs per compute unit: 256 rows above this line,
+constexpr double kShortPairsPerCu = 0.13e6;  // 128 below this one; between them 128 where an image record visits fewer
+constexpr double kShortKeys = 24 * 64;       // keys than this on average, or where the shorter records save
+constexpr double kShortSaves = 0.011;        // ... this share of the visited keys and more
 constexpr int wgs_per_cu(int rows) { return 256 / rows; }
 constexpr int copy_chunk_vecs(int rows) { return 32 * rows; }   // 16-byte vectors per chunk of the cached-head copy: 16 per thread
 

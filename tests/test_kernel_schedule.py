@@ -186,3 +186,34 @@ def test_cached_heads_of_any_length_can_share_the_fp32_launch():
     assert I.copy_chunks(257, 128, B.DIFA_DTYPE_F32, 2, 3) == 12
     assert I.copy_chunks(1 << 26, 128, B.DIFA_DTYPE_F32, 1, 1) == 1 << 18
     assert I.copy_chunks((1 << 30) - 1, 128, B.DIFA_DTYPE_F32, 1, 2) == 1 << 23
+
+
+# ----------------------------------------------------------------------------- which record length
+@pytest.mark.parametrize("rows,heads,n_text,n_img,full,w,flags", [
+    (256, 24, 512, 8704, 24, 0, 0),          # every head full: nothing to save, from about 1.5 K tokens on
+    (256, 24, 77, 1459, 24, 0, 0),
+    (256, 24, 512, 12544, 24, 0, 0),
+    (128, 24, 77, 691, 24, 0, 0),            # ... but short records, or too few of them, are the better for being shorter
+    (128, 6, 77, 1459, 6, 0, 0),
+    (256, 24, 512, 16384, 0, 2048, 1),       # blocks of 256 rows are visited whole either way
+    (128, 24, 512, 16384, 0, 128, 1),
+    (256, 24, 512, 16384, 0, 4224, 0),       # bands so wide that a record's rows hardly count
+    (128, 24, 512, 16384, 0, 2112, 0),
+    (128, 24, 512, 16384, 0, 128, 0),
+    (256, 24, 512, 8704, 12, 576, 0),        # full and arrow heads: by what their records would save
+    (128, 24, 512, 8704, 4, 576, 0),
+    (128, 4, 16, 64, 2, 8, 0),               # the smallest
+])
+def test_record_length_at_head_dim_128(rows, heads, n_text, n_img, full, w, flags):
+    hp, win = [FULL] * full + [ARROW] * (heads - full), [0] * full + [w] * (heads - full)
+    assert I.record_rows(1, 128, hp, win, n_text, n_img, flags) == rows
+    assert I.record_rows(1, 64, hp, win, n_text, n_img, flags) == 128
+
+
+def test_record_length_of_the_named_layers():
+    for layer, rows in ((W.flux_1k, 128), (W.flux_2k_mixed, 128), (W.flux_2k_full, 256), (W.video_like, 128), (W.tiny, 128)):
+        wl = layer()
+        assert I.record_rows(wl.B, wl.D, wl.head_plan, wl.window, wl.n_text, wl.n_img) == rows, wl.name
+    wl = W.flux_2k_mixed()
+    assert I.record_rows(2, wl.D, wl.head_plan, wl.window, wl.n_text, wl.n_img) == 256          # 16.7 M pairs a compute unit
+    assert I.record_rows(1, wl.D, [CACHE] * 24, [0] * 24, wl.n_text, wl.n_img) == 128           # nothing computed
