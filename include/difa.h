@@ -70,8 +70,11 @@ typedef struct {
  * Sec. 3.4.2: the plan is indexed by timestep, layer and head -- one object serves one layer
  * shape and is fed that layer's per-step head plan on every call).
  *   desc      HOST pointer, read during the call only.
- *   plan_out  HOST pointer; receives the object.  The object owns small device and pinned
- *             host buffers (compiled work lists), sized from desc->max_tokens.
+ *   plan_out  HOST pointer; receives the object.  It owns, sized from desc->max_tokens: device memory for
+ *             32 compiled schedules (a denoising loop's; fewer, down to 8, where 32 would exceed 256 MB)
+ *             and pinned host memory for 16, 64 bytes for every 128 query rows of every batch entry and
+ *             head plus 74 KB each (24 heads of 16896 tokens: 8.9 MB and 4.5 MB); with bf16, 67 MB
+ *             (head_dim 128) or 35 MB of device scratch for records cut into pieces.
  * Errors: INVALID_ARG (NULL, sizes < 1, unknown flag bits), UNSUPPORTED (head_dim not 64/128,
  * unknown dtype/layout, device is not gfx950), ALLOC, HIP.  On error *plan_out is NULL.
  */

@@ -238,6 +238,22 @@ hipError_t order_behind_earlier_calls(difa_plan* p, hipStream_t stream) {
     return hipSuccess;
 }
 
+// Buffers for the schedules of layers of up to `records` records, on n_wg workgroups (0: the fp32 path, whose device buffer
+// holds the records themselves).
+struct ScheduleBuffers { size_t heads_bytes, buf_bytes; int n_slots; };
+ScheduleBuffers schedule_buffers(int heads, int64_t records, int n_wg) {
+    ScheduleBuffers b;
+    b.heads_bytes = ((size_t)heads * sizeof(int32_t) + 63) / 64 * 64;
+    // bf16, worst case: every record whole plus two pieces per workgroup, one merge entry for every two pieces
+    const size_t used = n_wg ? ((size_t)n_wg + 1) * sizeof(int32_t) + 64 + ((size_t)records + 2 * (size_t)n_wg) * sizeof(difa_segment_t) +
+                                   64 + (size_t)n_wg * sizeof(difa_merge_item_t)
+                             : (size_t)records * sizeof(difa_work_item_t);
+    b.buf_bytes = (b.heads_bytes + used + 255) / 256 * 256;
+    // (up to 256 MB of schedules, and eight of them however large the layer)
+    b.n_slots = (int)std::min<size_t>(kSlots, std::max<size_t>(8, ((size_t)256 << 20) / b.buf_bytes));
+    return b;
+}
+
 // Is what is enqueued on `stream` recorded into a graph?  (The default stream cannot be captured.)
 bool is_capturing(hipStream_t stream) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -377,14 +393,10 @@ extern "C" difa_status_t difa_plan_create(const difa_plan_desc_t* desc, difa_pla
     p->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
     p->n_wg = p->n_cu * (bf16 ? difa::wgs_per_cu(difa::kRowsShort) : 1);
     p->n_xcd = p->n_cu % kXcd == 0 ? kXcd : 1;
-    p->heads_bytes = ((size_t)desc->heads * sizeof(int32_t) + 63) / 64 * 64;
-    // worst case: every record whole plus two pieces per workgroup, one merge entry per workgroup
-    p->buf_bytes = p->heads_bytes + ((size_t)p->n_wg + 1) * sizeof(int32_t) + 64 +
-                   ((size_t)cap + 2 * (size_t)p->n_wg) * sizeof(difa_segment_t) + 64 +
-                   2 * (size_t)p->n_wg * sizeof(difa_merge_item_t) + 64 + (size_t)cap * sizeof(difa_work_item_t);
-    p->buf_bytes = (p->buf_bytes + 255) / 256 * 256;
-    // (up to 256 MB of schedules, and eight of them however large the layer)
-    p->n_slots = (int)std::min<size_t>(kSlots, std::max<size_t>(8, ((size_t)256 << 20) / p->buf_bytes));
+    const ScheduleBuffers sizes = schedule_buffers(desc->heads, cap, bf16 ? p->n_wg : 0);
+    p->heads_bytes = sizes.heads_bytes;
+    p->buf_bytes = sizes.buf_bytes;
+    p->n_slots = sizes.n_slots;
     try {
         p->recs.reserve((size_t)cap);
         p->keys.assign((size_t)(kSlots + 1) * (2 * (size_t)desc->heads + 2), 0);
@@ -684,7 +696,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             st = difa::schedule_for_dies(difa::kernel_costs(D), p->recs, lru->n_wg, p->n_xcd, dies ? lru->trial.speed : nullptr,
                                          dies ? lru->die_span : nullptr, (difa_segment_t*)(hb + lru->segs_off),
                                          seg_cap, (int32_t*)(hb + lru->wg_off), &n_segs,
-                                         (difa_merge_item_t*)(hb + lru->merges_off), 2 * lru->n_wg, &n_merges, &n_slots);
+                                         (difa_merge_item_t*)(hb + lru->merges_off), lru->n_wg, &n_merges, &n_slots);
             if (st != DIFA_OK) return fail(p, st, "scheduling the work list failed");
             used = lru->merges_off + (size_t)n_merges * sizeof(difa_merge_item_t);
             const int32_t* begin = (const int32_t*)(hb + lru->wg_off);
@@ -934,6 +946,16 @@ extern "C" void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int3
         for (int x = 0; x < n_dies; ++x) die[x] = (unsigned long long)die_ticks[std::min(v, n_versions - 1) * n_dies + x];
         t.add(die, n_dies);
     }
+}
+
+extern "C" void difa_testing_schedule_memory(int32_t batch, int32_t heads, int32_t dtype, int32_t max_tokens, int32_t n_cu,
+                                             int64_t* device_bytes, int64_t* pinned_bytes, int32_t* schedules) {
+    const int rows = dtype == DIFA_DTYPE_BF16 ? difa::kRowsShort : difa::kBM;
+    const ScheduleBuffers b = schedule_buffers(heads, (int64_t)batch * heads * (((int64_t)max_tokens + rows - 1) / rows),
+                                               dtype == DIFA_DTYPE_BF16 ? n_cu * difa::wgs_per_cu(rows) : 0);
+    *device_bytes = (int64_t)b.buf_bytes * b.n_slots;
+    *pinned_bytes = (int64_t)b.buf_bytes * kStagings;
+    *schedules = b.n_slots;
 }
 
 extern "C" int32_t difa_testing_copy_chunks(int64_t n_tokens, int32_t head_dim, int32_t dtype, int32_t batch, int32_t n_copy) {

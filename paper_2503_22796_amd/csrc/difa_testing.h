@@ -28,6 +28,9 @@ int32_t difa_testing_record_rows(int32_t batch, int32_t heads, int32_t head_dim,
 // version launch i runs; speeds[i][n_dies]: what it was made for.
 void difa_testing_trial(int32_t n_dies, const int64_t* die_span, int32_t n_versions, const double* die_ticks, int32_t n_launches,
                         const int32_t* capturing, int32_t* version, double* speeds);
+// What a plan object sets aside for schedules: device and pinned host memory, and how many stay resident.
+void difa_testing_schedule_memory(int32_t batch, int32_t heads, int32_t dtype, int32_t max_tokens, int32_t n_cu,
+                                  int64_t* device_bytes, int64_t* pinned_bytes, int32_t* schedules);
 // Chunks of the cached-head copy that shares the launch of a layer's computed heads; -1: refused.
 int32_t difa_testing_copy_chunks(int64_t n_tokens, int32_t head_dim, int32_t dtype, int32_t batch, int32_t n_copy);
 // Which of n resident schedules gives way to a new one: in use or free, launched by a captured graph, time of its last use.

@@ -14,6 +14,8 @@ _L.difa_testing_trial.argtypes = [_i32, _vp, _i32, _vp, _i32, _vp, _vp, _vp]
 _L.difa_testing_victim.argtypes = [_i32, _vp, _vp, _vp]
 _L.difa_testing_trial.restype = None
 _L.difa_testing_copy_chunks.argtypes = [ctypes.c_int64, _i32, _i32, _i32, _i32]
+_L.difa_testing_schedule_memory.argtypes = [_i32, _i32, _i32, _i32, _i32, _vp, _vp, _i32p]
+_L.difa_testing_schedule_memory.restype = None
 _L.difa_testing_force_rows.argtypes = [_vp, _i32]
 _L.difa_testing_last_call.argtypes = [_vp] + [_i32p] * 5
 _L.difa_testing_last_call.restype = None
@@ -85,3 +87,10 @@ def last_call(plan):
 
 def copy_chunks(n_tokens, head_dim, dtype, batch, n_copy):
     return _L.difa_testing_copy_chunks(n_tokens, head_dim, dtype, batch, n_copy)
+
+
+def schedule_memory(batch, heads, dtype, max_tokens, n_cu=256):
+    """(device bytes, pinned host bytes, resident schedules) of a plan object."""
+    mem, n = np.zeros(2, np.int64), _i32(0)
+    _L.difa_testing_schedule_memory(batch, heads, dtype, max_tokens, n_cu, mem[:1].ctypes.data, mem[1:].ctypes.data, ctypes.byref(n))
+    return int(mem[0]), int(mem[1]), n.value

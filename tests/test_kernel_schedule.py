@@ -178,6 +178,22 @@ def test_a_layer_of_mostly_uncuttable_records_is_not_searched_to_the_end():
     assert tried <= 2 * 2 * 8
 
 
+# ----------------------------------------------------------------------------- what a plan object sets aside
+def test_schedule_memory_of_a_plan_object():
+    # a segment is 64 bytes; at most one for every record, two for every workgroup and an entry of 16 bytes for every two of those
+    for tokens, heads in ((4608, 24), (16896, 24), (80, 4)):
+        device, pinned, n = I.schedule_memory(1, heads, B.DIFA_DTYPE_BF16, tokens)
+        most = (heads * -(-tokens // 128) + 1024) * 64 + 512 * (16 + 4)
+        assert n == 32 and most <= device / n <= most + 1024 and pinned == device // n * 16
+    # the fp32 path keeps records of 44 bytes, one for 256 rows
+    device, pinned, n = I.schedule_memory(1, 24, B.DIFA_DTYPE_F32, 4608)
+    assert n == 32 and 24 * 18 * 44 <= device / n <= 24 * 18 * 44 + 1024
+    # large layers: bounded, but eight schedules in any case
+    device, _, n = I.schedule_memory(2, 64, B.DIFA_DTYPE_BF16, 1 << 18)
+    assert 8 <= n < 32 and device <= 256 << 20
+    assert I.schedule_memory(2, 128, B.DIFA_DTYPE_BF16, 1 << 22)[2] == 8
+
+
 # ----------------------------------------------------------------------------- the cached-head copy
 def test_cached_heads_of_any_length_can_share_the_fp32_launch():
     # chunks of 8192 vectors of 16 bytes; a head of 2^26 tokens of 128 floats has 2^31 vectors, one more than an int holds
