@@ -119,9 +119,9 @@ difa_status_t difa_joint_attention(difa_plan_t* plan, const void* q, const void*
  * device array that is part of the library's code object (68 157 440 bytes per GPU, there from the
  * moment the library is loaded until the process ends) instead of the plan object's own buffer.  The
  * call makes no hipMalloc / hipFree and calls no allocating library routine.
- * Limit: a call whose schedule needs more than the array holds -- 512 pieces of 256 rows * (head_dim + 2)
- * floats at head_dim 128, 2016 of 128 rows at 64, which covers every schedule for a GPU of up to 256 compute
- * units -- fails with DIFA_ERR_UNSUPPORTED and a message naming both sizes.
+ * Limit: a call whose schedule needs more than the array holds -- pieces of (query rows of a record) *
+ * (head_dim + 2) floats: 512 of 256 rows or 1024 of 128 at head_dim 128, 2016 of 128 rows at 64, which covers
+ * every schedule for a GPU of up to 256 compute units -- fails with DIFA_ERR_UNSUPPORTED and a message naming both sizes.
  * Every call of this entry point on one GPU uses the same array, whatever the plan object or stream:
  * two such calls that overlap in time on one GPU race and produce wrong rows; the caller orders them
  * (one stream, or events).  Calls of difa_joint_attention are not affected by it.

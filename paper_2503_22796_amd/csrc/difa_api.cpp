@@ -49,7 +49,7 @@ struct Staging {
 
 struct TimingPair {
     hipEvent_t start, stop;
-    int kind;  // 0 attention, 1 copy, 2 influence metric
+    bool rse;  // the influence metric (otherwise an attention call's one launch)
 };
 
 }  // namespace
@@ -100,7 +100,7 @@ struct difa_plan {
     int32_t last_slot = -1, last_grid = 0, last_reports = 0;   // ... the last attention call
     bool timing = false;
     std::vector<TimingPair> pending, pool;
-    double attn_ms = 0, copy_ms = 0, rse_ms = 0;
+    double attn_ms = 0, rse_ms = 0;
     int64_t launches = 0, rse_launches = 0;
 };
 
@@ -295,7 +295,7 @@ struct DeviceGuard {
     }
 };
 
-hipError_t timing_begin(difa_plan* p, hipStream_t stream, int kind, TimingPair* out) {
+hipError_t timing_begin(difa_plan* p, hipStream_t stream, bool rse, TimingPair* out) {
     TimingPair tp{};
     if (!p->pool.empty()) {
         tp = p->pool.back();
@@ -306,7 +306,7 @@ hipError_t timing_begin(difa_plan* p, hipStream_t stream, int kind, TimingPair* 
         e = hipEventCreate(&tp.stop);
         if (e != hipSuccess) { (void)hipEventDestroy(tp.start); return e; }
     }
-    tp.kind = kind;
+    tp.rse = rse;
     *out = tp;
     return hipEventRecord(tp.start, stream);
 }
@@ -318,9 +318,8 @@ hipError_t timing_flush(difa_plan* p) {
         float ms = 0.f;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, tp.start, tp.stop);
         if (e == hipSuccess) {
-            if (tp.kind == 0) { p->attn_ms += ms; p->launches += 1; }
-            else if (tp.kind == 1) p->copy_ms += ms;
-            else { p->rse_ms += ms; p->rse_launches += 1; }
+            if (tp.rse) { p->rse_ms += ms; p->rse_launches += 1; }
+            else { p->attn_ms += ms; p->launches += 1; }
         } else if (first == hipSuccess) {
             first = e;
         }
@@ -511,9 +510,9 @@ extern "C" difa_status_t difa_plan_timing_read(difa_plan_t* p, double* attn_ms, 
     if (e == hipSuccess) e = timing_flush(p);
     if (e != hipSuccess) return fail(p, DIFA_ERR_HIP, hip_msg("reading kernel timing events", e));
     if (attn_ms) *attn_ms = p->attn_ms;
-    if (copy_ms) *copy_ms = p->copy_ms;
+    if (copy_ms) *copy_ms = 0.0;                                      // (no path has a separate copy kernel beside the layer's)
     if (launches) *launches = p->launches;
-    if (reset) { p->attn_ms = 0; p->copy_ms = 0; p->launches = 0; }
+    if (reset) { p->attn_ms = 0; p->launches = 0; }
     return DIFA_OK;
     });
 }
@@ -746,7 +745,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         c.batch = B; c.n_copy = slot->n_copy; c.n_tokens = N;
         c.vec_per_row = (int32_t)(D * es / 16);
         TimingPair tp{};
-        if (p->timing && (e = timing_begin(p, stream, 0, &tp)) != hipSuccess)
+        if (p->timing && (e = timing_begin(p, stream, false, &tp)) != hipSuccess)
             return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
         e = difa::launch_cache_copy(c, stream);
         if (p->timing) { (void)hipEventRecord(tp.stop, stream); p->pending.push_back(tp); }
@@ -812,7 +811,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
             a.f32_blocks = (int32_t)blocks;
         }
         TimingPair tp{};
-        if (p->timing && (e = timing_begin(p, stream, 0, &tp)) != hipSuccess)
+        if (p->timing && (e = timing_begin(p, stream, false, &tp)) != hipSuccess)
             return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
         // A layer of a few records is launched on the workgroups that have any (and one for each chunk of the cached-head
         // copy): 512 workgroups that only look for work took 2 us to start and end.  From a fraction of the grid on nothing is gained.
@@ -913,7 +912,7 @@ extern "C" difa_status_t difa_head_rse(difa_plan_t* p, const void* y_m, const vo
     e = order_behind_earlier_calls(p, stream);
     if (e != hipSuccess) return fail(p, DIFA_ERR_HIP, hip_msg("ordering the call behind earlier ones", e));
     TimingPair tp{};
-    if (p->timing && (e = timing_begin(p, stream, 2, &tp)) != hipSuccess)
+    if (p->timing && (e = timing_begin(p, stream, true, &tp)) != hipSuccess)
         return fail(p, DIFA_ERR_HIP, hip_msg("hipEventRecord", e));
     e = difa::launch_head_rse(a, p->desc.dtype, stream);
     if (p->timing) { (void)hipEventRecord(tp.stop, stream); p->pending.push_back(tp); }

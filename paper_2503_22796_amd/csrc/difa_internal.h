@@ -58,8 +58,8 @@ struct AttnArgs {
     const difa_segment_t* segs;     // device: segments grouped by workgroup (bf16 kernel)
     const int32_t* wg_begin;        // device: first segment of each workgroup, n_wg + 1 entries
     const difa_merge_item_t* merges;  // device: records cut into pieces
-    float* part_o;                  // device scratch: [slot][rows_per_wg][head_dim] unnormalised accumulators
-    float* part_ml;                 // device scratch: [slot][rows_per_wg][2] row reference (log2 domain), row sum
+    float* part_o;                  // device scratch: [slot][rows of a record][head_dim] unnormalised accumulators
+    float* part_ml;                 // device scratch: [slot][rows of a record][2] row reference (log2 domain), row sum
     int32_t* tickets;               // device, one per cut record, zero between launches: pieces finished so far
     const void* residual;           // device, shaped like out: kept differences of the residual-sharing heads (or NULL)
     // cached heads: out[b, h] = copy_src[b, h] for the heads listed in copy_heads

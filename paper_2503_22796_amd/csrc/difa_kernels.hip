@@ -316,7 +316,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         query_rows(sg);
     };
 
-    // Persistent workgroup: one per compute unit, walking the segments the host scheduled for it.
+    // Persistent workgroup: one or two per compute unit, walking the segments the host scheduled for it.
     // The record of the following segment is fetched while the current one runs.
     const int seg_end = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x + 1]);
     const int seg_first = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x]);
@@ -353,10 +353,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             if (live[u]) *(uintx4*)(dst + off[u]) = val[u];
     };
     int next_chunk = (int)blockIdx.x;
-    // Where two workgroups share a compute unit, its SIMDs serve the older wavefront first: left to itself (head_dim 64)
-    // the workgroup that was dispatched second runs at 2500 clocks an iteration beside 1735 of the other, and the schedule,
-    // which gives both the same work, waits for it.  So the younger half of the grid takes the higher priority for two
-    // iterations out of four: 2130 beside 1950.
+    // Where two workgroups share a compute unit, its SIMDs serve the older wavefront first: left to itself (head_dim 64) the
+    // workgroup that was dispatched second ran at 2500 clocks an iteration beside 1735 of the other, and the schedule, which
+    // gives both the same work, waits for it.  So the younger half of the grid runs every other iteration at the higher
+    // priority.  With and without: SD3-like 2K layer 1443 / 1475 us, 1K 141.6 / 144.0, 512 px 28.6 / 29.7; head_dim 128 the same
+    // either way.  (A segment leaves the priority as its last iteration had it: lowering it after the key loop changes nothing.)
     const bool younger = wgs_per_cu(BM) > 1 && (int)blockIdx.x >= a.younger_from;
 
     difa_segment_t seg_next{};
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         mfma_results_visible();
     };
     // Element mask of one 32-key block whose first key is j0.  The host marks a tile as masked when any
-    // of the workgroup's 256 rows has a forbidden key in it; for the rows of one wavefront most such
+    // of the record's rows has a forbidden key in it; for the rows of one wavefront most such
     // blocks lie entirely inside the band, or are cut by one band edge only.  That is decided here from
     // scalars, so that the common cases cost nothing or two plain integer instructions per score.
     const int row_first = it.q_tile * BM + (int)wave_u * RW;              // this wavefront's rows (uniform)
@@ -1014,7 +1015,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 // ------------------------------------------------------------------------------------------
 // Scratch of difa_joint_attention_static, the entry point for callers that must not allocate: the
 // partial results of cut records (what part_o / part_ml point at) live in this file-scope array
-// instead of a buffer the plan object allocated.  512 pieces of 256 rows at head_dim 128:
+// instead of a buffer the plan object allocated.  512 pieces of 256 rows, or 1024 of 128, at head_dim 128:
 // 512 * 256 * (128 + 2) floats = 68 157 440 bytes, held by every GPU the library runs on until the
 // process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the device
 // address is looked up once per device and is what the kernels receive as an argument.

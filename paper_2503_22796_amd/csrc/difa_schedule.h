@@ -23,6 +23,11 @@ constexpr CostModel kGenericCosts{7, 36, 72, 40, 12};   // what difa_schedule_bu
 // iterations more on a masked tile, 5.9 for starting and finishing a whole record, 6.1 for a piece (9-11 while slots were
 // laid out by rows), 2.4 for folding one other slot in; two workgroups of four wavefronts 2900, 0.7, 5.2, 5.7 and 3.0.
 // head_dim 64, two workgroups of four wavefronts: 2000 clocks, 1.4, 1-3, 3-5 and 2.7 iterations.
+// At head_dim 128 records and pieces are charged less than that (3.3 and 4.5 iterations, 2.4 a fold) and masked tiles more
+// (1.0): what a schedule depends on is their difference and the tiles, and a schedule is corrected from its own launches
+// besides (difa_trial.h).  Charging {6, 43, 46, 22, 8}, the measured ones, instead: FLUX-like 1K layer 128.8 us (129.1 as it
+// is), 2K mixed 993 (1000), all full 2892 (2900), video-like 1312 (1328), w = 128 at 1K 94.0 (94.8), runs of one side differing
+// by as much; one set does for both record lengths for the same reason.
 constexpr CostModel kernel_costs(int head_dim) {
     return head_dim == 64 ? CostModel{11, 12, 28, 21, 8} : CostModel{8, 26, 36, 19, 8};
 }
