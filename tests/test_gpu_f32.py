@@ -118,3 +118,35 @@ def test_fp32_a_key_that_is_not_finite_stays_with_the_rows_that_see_it(D, image_
         assert float((got[:, h, blind].double() - ref[:, h, blind]).abs().max()) <= TOL_F32, f"head {h}"
     rest = (got[:, 0, img0 + 3, :D // 2].double() - ref[:, 0, img0 + 3, :D // 2]).abs().max()
     assert float(rest) <= TOL_F32                         # features of V that are finite are not touched either
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_fp32_tensors_need_no_more_than_element_alignment(D):
+    """Tensors that begin one float into an allocation: the kernel reads and writes four floats at a time."""
+    from oracle import difa_oracle as O
+    from paper_2503_22796_amd import binding as B
+    dev = torch.device("cuda:0")
+    hp, win = np.asarray([FULL, ARROW, CACHE], np.int32), np.asarray([0, 12, 0], np.int32)
+    wl = W.Workload("f32a", 1, 3, D, 21, 150, hp, win, seed=930)
+    q, k, v = W.make_qkv(wl, dtype=torch.float32)
+    cache = W.make_cache(wl, dtype=torch.float32)
+
+    def shifted(t):
+        buf = torch.full((t.numel() + 1,), float("nan"), device=dev)
+        view = buf[1:].view(t.shape)
+        view.copy_(t.to(dev))
+        return buf, view
+
+    (_, qd), (_, kd), (_, vd), (_, cd), (whole, out) = (shifted(t) for t in (q, k, v, cache, torch.zeros_like(q)))
+    print(f"f32 element alignment D={D}", flush=True)
+    plan = B.difa_plan_create(1, 3, D, dtype=B.DIFA_DTYPE_F32, max_tokens=wl.N)
+    try:
+        B.difa_joint_attention(plan, qd, kd, vd, out, cd, hp, wl.n_text, wl.n_img, win)
+        torch.cuda.synchronize()
+    finally:
+        B.difa_plan_destroy(plan)
+    assert bool(torch.isnan(whole[0]))                    # nothing is written before the tensor
+    got = out.cpu()
+    ref, raw, _ = O.joint_attention(q, k, v, cache, hp, win, wl.n_text, wl.n_img)
+    assert float((got[:, :2].double() - ref[:, :2]).abs().max()) <= TOL_F32
+    assert torch.equal(got[:, 2].view(torch.int32), raw[:, 2].contiguous().view(torch.int32))
