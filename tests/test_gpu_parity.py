@@ -196,7 +196,7 @@ def test_plan_reuse_many_plans_and_a_side_stream():
     try:
         rng = np.random.Generator(np.random.PCG64(5))
         cases = []
-        for it in range(12):                      # more distinct plans than the memo keeps
+        for it in range(40):                      # more distinct plans than the 32 the memo keeps
             hp = rng.integers(0, 3, size=H).astype(np.int32)
             win = rng.integers(0, 300, size=H).astype(np.int32)
             cases.append((hp, win))

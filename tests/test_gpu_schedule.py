@@ -67,7 +67,7 @@ def test_flux_2k_schedule_three_steps_two_layers():
 
 def test_flux_2k_schedule_all_28_steps_of_four_layers():
     """The 57-layer x 28-step schedule on four of its layers, every step: each layer's plan object sees 28
-    distinct plans (more than it keeps resident, so work lists are evicted and recompiled at the 2K size).
+    distinct plans, fewer than the 32 it keeps resident: every one is compiled once, at the 2K size.
     Every call: each cached head bit-identical to the layer's previous output.  Twelve sampled (layer, step)
     pairs, the last step among them: computed heads against the oracle on sampled rows.  A head that stays
     cached for three steps or more in a row still carries, bit for bit, the output of the step that last
@@ -152,8 +152,9 @@ def test_flux_2k_schedule_all_28_steps_of_four_layers():
 
 
 def test_small_schedule_many_plans_per_layer():
-    # more distinct plans per layer than the plan object memoises, an odd token count, head_dim 64
-    H, layers, steps = 6, 3, 11
+    # more distinct plans per layer than the 32 the plan object keeps resident, so that schedules give way to others; an odd
+    # token count, head_dim 64
+    H, layers, steps = 6, 3, 36
     base = W.Workload("small_schedule", 2, H, 64, 37, 484, np.zeros(H, np.int32), np.zeros(H, np.int32), seed=77)
     rng = np.random.Generator(np.random.PCG64(78))
     hp = np.zeros((layers, steps, H), np.int32)
@@ -162,5 +163,6 @@ def test_small_schedule_many_plans_per_layer():
         for t in range(1, steps):
             hp[l, t] = rng.integers(0, 3, size=H)
             win[l, t] = np.where(hp[l, t] == ARROW, rng.integers(0, 500, size=H), 0)
+        assert len({(tuple(hp[l, t]), tuple(win[l, t])) for t in range(steps)}) > 32
     worst = run_schedule(base, layers, steps, hp, win, list(range(base.N)))
     print(f"small schedule: max_abs_err={worst:.3e}", flush=True)
