@@ -128,7 +128,9 @@ difa_status_t difa_joint_attention(difa_plan_t* plan, const void* q, const void*
  * Under graph capture (either entry point): make the call once, on the stream that is captured, before capturing it, so
  * that its schedule is resident and the graph holds the kernel launch alone (an upload recorded into the graph would read a
  * staging buffer that later uploads overwrite).  A captured schedule is not corrected any more (see difa_plan_die_speeds)
- * and is the last to give way to schedules of other plans; a graph must not be replayed once the plan object is gone.
+ * and is the last to give way to schedules of other plans.  A graph whose schedule has given way all the same (more
+ * captured plans than the object keeps schedules) writes nothing for that layer, cached heads included, when it is
+ * replayed; a graph must not be replayed once the plan object is gone.
  */
 difa_status_t difa_joint_attention_static(difa_plan_t* plan, const void* q, const void* k, const void* v,
                                           void* out, const void* cache, const int32_t* head_plan,

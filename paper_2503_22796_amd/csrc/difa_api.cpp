@@ -245,7 +245,7 @@ ScheduleBuffers schedule_buffers(int heads, int64_t records, int n_wg) {
     ScheduleBuffers b;
     b.heads_bytes = ((size_t)heads * sizeof(int32_t) + 63) / 64 * 64;
     // bf16, worst case: every record whole plus two pieces per workgroup, one merge entry for every two pieces
-    const size_t used = n_wg ? ((size_t)n_wg + 1) * sizeof(int32_t) + 64 + ((size_t)records + 2 * (size_t)n_wg) * sizeof(difa_segment_t) +
+    const size_t used = n_wg ? ((size_t)n_wg + 2) * sizeof(int32_t) + 64 + ((size_t)records + 2 * (size_t)n_wg) * sizeof(difa_segment_t) +
                                    64 + (size_t)n_wg * sizeof(difa_merge_item_t)
                              : (size_t)records * sizeof(difa_work_item_t);
     b.buf_bytes = (b.heads_bytes + used + 255) / 256 * 256;
@@ -687,7 +687,9 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         size_t used = p->heads_bytes;
         lru->wg_off = lru->segs_off = lru->merges_off = lru->items_off = used;
         if (p->desc.dtype == DIFA_DTYPE_BF16) {
-            lru->wg_off = used;
+            // (the schedule's number is in the same place whatever the schedule)
+            *(int32_t*)(hb + used) = (int32_t)lru->sched_id;
+            lru->wg_off = used + sizeof(int32_t);
             lru->segs_off = (lru->wg_off + ((size_t)lru->n_wg + 1) * sizeof(int32_t) + 63) / 64 * 64;
             const int32_t seg_cap = n_items + 2 * lru->n_wg;
             lru->merges_off = (lru->segs_off + (size_t)seg_cap * sizeof(difa_segment_t) + 63) / 64 * 64;
@@ -789,6 +791,7 @@ difa_status_t joint_attention_impl(difa_plan_t* p, const void* q, const void* k,
         a.scale = p->scale;
         if (fast) {
             a.tickets = p->ctl;
+            a.sched_id = (int32_t)slot->sched_id;
         }
         if (copies) {
             const int vec_per_row = (int)(D * es / 16);                     // 8, 16 or 32: a power of two

@@ -56,7 +56,7 @@ struct AttnArgs {
     void* out;
     const difa_work_item_t* items;  // device: one record per kBM query rows (fp32 kernel)
     const difa_segment_t* segs;     // device: segments grouped by workgroup (bf16 kernel)
-    const int32_t* wg_begin;        // device: first segment of each workgroup, n_wg + 1 entries
+    const int32_t* wg_begin;        // device: first segment of each workgroup, n_wg + 1 entries; sched_id stands in front of them
     const difa_merge_item_t* merges;  // device: records cut into pieces
     float* part_o;                  // device scratch: [slot][rows of a record][head_dim] unnormalised accumulators
     float* part_ml;                 // device scratch: [slot][rows of a record][2] row reference (log2 domain), row sum
@@ -83,6 +83,7 @@ struct AttnArgs {
     // constant-rate 100 MHz counter) in wg_times[p] when it ends (host memory mapped into the device; NULL: off)
     unsigned long long* wg_times;
     uint32_t launch_tag;
+    int32_t sched_id;               // bf16 kernel: the schedule the launch was made for
 };
 
 struct CopyArgs {

@@ -318,8 +318,12 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 
     // Persistent workgroup: one or two per compute unit, walking the segments the host scheduled for it.
     // The record of the following segment is fetched while the current one runs.
-    const int seg_end = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x + 1]);
+    // A launch replayed from a graph may find that its schedule has given way to another, for the other record length even: the
+    // segments would name scratch slots beyond the end, and half of a record's pieces would leave their ticket standing.  It has
+    // nothing to do then.  (All three words are read together; a return up front put a memory latency before every launch: 0.8 us.)
+    const bool mine = __builtin_amdgcn_readfirstlane(a.wg_begin[-1]) == a.sched_id;
     const int seg_first = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x]);
+    const int seg_listed = __builtin_amdgcn_readfirstlane(a.wg_begin[blockIdx.x + 1]), seg_end = mine ? seg_listed : seg_first;
     // ---- cached heads (Sec. 3.2; the cache fill that ends Alg. 1): out[b, h] = cache[b, h], bit for bit.
     // HBM-bound work that needs no matrix core.  It is cut into chunks of copy_chunk_vecs(BM) 16-byte vectors of one
     // (batch entry, cached head); workgroup p takes chunks p, p + gridDim.x, ... and moves one after each of
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         for (int u = 0; u < PER; ++u)
             if (live[u]) *(uintx4*)(dst + off[u]) = val[u];
     };
-    int next_chunk = (int)blockIdx.x;
+    int next_chunk = mine ? (int)blockIdx.x : 0x7fffffff;
     // Where two workgroups share a compute unit, its SIMDs serve the older wavefront first: left to itself (head_dim 64) the
     // workgroup that was dispatched second ran at 2500 clocks an iteration beside 1735 of the other, and the schedule, which
     // gives both the same work, waits for it.  So the younger half of the grid runs every other iteration at the higher
