@@ -532,8 +532,9 @@ struct Die {
             };
             // Where most of the work is in records that cannot be cut, rooms end with a gap as a rule and no target may hold
             // everything: the two largest ones say so (not the largest alone: once in 500 layers a smaller one fits by luck).
-            if (2 * uncut > total && mean + 3 * cut / 2 < best.makespan && !holds_everything(mean + 3 * cut / 2) &&
-                !holds_everything(mean + cut))
+            // With a record or two for each workgroup the whole search costs less than asking.
+            if (order.size() > 2 * (size_t)per_die && 2 * uncut > total && mean + 3 * cut / 2 < best.makespan &&
+                !holds_everything(mean + 3 * cut / 2) && !holds_everything(mean + cut))
                 continue;
             for (const int64_t above : {cut / 8, cut / 3, 2 * cut / 3, cut, 3 * cut / 2}) {
                 const int64_t target = mean + above;
