@@ -103,7 +103,7 @@ typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 
 struct RowState {
     float m;       // reference maximum (log2 domain) the weights are expressed against
-    float l;       // running sum of this lane's half of the keys
+    float l;       // running sum of the weights
     int lo;        // band of allowed image keys is [lo, lo + span]; text keys are always allowed
     unsigned span;
 };
@@ -420,6 +420,16 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         rs[qb].l = 0.f;
     }
 
+    // A operand of the row sums.  P as it stands (lane l: query l % 32, keys of half l / 32) read as the B operand of a
+    // 16x16x32 product has query l % 16 + 16 * (l / 16 % 2) in column l % 16 and key slots 8 * (l / 16) .. + 7: row m of A
+    // has ones in the slots of the lane groups whose parity is that of m / 4, so that every lane receives, in all four
+    // registers, the sum over both halves' keys of its own query's weights.
+    bf16x8 row_ones;
+    {
+        const int lane = l32 + 32 * half;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) row_ones[e] = (__bf16)(((lane >> 4) ^ (lane >> 2)) & 1 ? 0.f : 1.f);
+    }
     floatx16 o[DB][QB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -520,7 +530,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // whatever is not behind an MFMA delays the next one; the steady state spends nothing on a running
     // maximum).
     //   piece s: scores 2*(s&7), 2*(s&7)+1 of row block s>>3 -> two weights 2^(score*c - reference) as
-    //   bf16 B operands, added to the block's row sum
+    //   bf16 B operands
     // The reference of a row is NOT the running maximum: it is set from the first block that holds an
     // allowed key and afterwards moves only when a weight outgrows 2^kTrip.  That is detected after
     // the fact, from the block's row sum, and repaired on a rare side path (renormalise() below), so
@@ -537,28 +547,17 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         pin(x[0]);
         pin(x[1]);
     };
-    // (the row-sum update of a pair trails its conversion by one slot: a dot product issued right after
-    // the conversion it reads costs a wait state, as does a conversion right after its exponential)
-    auto softmax_b = [&](int s, float (&x)[2], float (&lb)[QB], bf16x8 (&pw)[QB][2], unsigned& held) __attribute__((always_inline)) {
+    auto softmax_b = [&](int s, float (&x)[2], bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
         const int qb = s >> 3, r = 2 * (s & 7);
-        bf16x2 ones;
-        ones[0] = (__bf16)1.0f;
-        ones[1] = (__bf16)1.0f;
         floatx2 pf;
         pf[0] = x[0];
         pf[1] = __builtin_amdgcn_exp2f(x[1]);
-        if (s > 0) {                                                  // the weights that entered P V are the ones summed
-            const int qp = (s - 1) >> 3;
-            lb[qp] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, held), ones, ((s - 1) & 7) ? lb[qp] : 0.f, false);
-            pin(lb[qp]);
-        }
         bf16x2 pr = __builtin_convertvector(pf, bf16x2);
         unsigned bits = __builtin_bit_cast(unsigned, pr);
         asm volatile("" : "+v"(bits));
         pr = __builtin_bit_cast(bf16x2, bits);
         pw[qb][r >> 3][r & 7] = pr[0];
         pw[qb][r >> 3][(r & 7) + 1] = pr[1];
-        held = bits;
     };
     // Rare side path, uniform over the wavefront: some row of block g produced a weight beyond 2^kTrip
     // (always the case for the first block, whose rows still carry the initial reference).  Every row
@@ -566,7 +565,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // reference; the block's weights and row sums are recomputed, the running sums and O are scaled.
     // The accumulators live in accumulation registers and are scaled in place there; the waits cover
     // MFMA results still in flight.
-    auto renormalise = [&](const floatx16 (&sc)[QB], float (&mneg)[QB], float (&lb)[QB], bf16x8 (&pw)[QB][2], bool rescale_o) __attribute__((always_inline)) {
+    auto renormalise = [&](const floatx16 (&sc)[QB], float (&lb)[QB], bf16x8 (&pw)[QB][2], bool rescale_o) __attribute__((always_inline)) {
         float alpha[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -579,7 +578,6 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             alpha[qb] = __builtin_amdgcn_exp2f(m_old - m_new);
             rs[qb].m = m_new;
             rs[qb].l *= alpha[qb];
-            mneg[qb] = -m_new;
             lb[qb] = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
@@ -587,13 +585,14 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
                 ones[0] = (__bf16)1.0f;
                 ones[1] = (__bf16)1.0f;
                 floatx2 pf;
-                pf[0] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r], c, mneg[qb]));
-                pf[1] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r + 1], c, mneg[qb]));
+                pf[0] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r], c, -m_new));
+                pf[1] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r + 1], c, -m_new));
                 const bf16x2 pr = __builtin_convertvector(pf, bf16x2);
                 pw[qb][r >> 3][r & 7] = pr[0];
                 pw[qb][r >> 3][(r & 7) + 1] = pr[1];
                 lb[qb] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lb[qb], false);
             }
+            lb[qb] = halves_sum(lb[qb]);
         }
         if (!rescale_o) return;     // nothing has been accumulated yet
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
@@ -650,15 +649,39 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     bf16x8 pa[QB][2], pb[QB][2];              // weights of the even / odd block in flight
     bf16x8 kq[NOP], vq[NOP];                // LDS operands (entry j = operand j of the stream)
 
+    // Row sums of a block's weights (the rounded ones, which are what P V multiplies), by the matrix core: two 16x16x32
+    // products beside the 16 (head_dim 64: 8) of S^T and P V.  v_dot2_f32_bf16, which adds a pair in one vector instruction, runs in
+    // the matrix pipe and stalls it: an MFMA with one of them behind it takes 49 clocks of its SIMD where four v_fma cost one
+    // (33 instead of 32), and the softmax's mix per MFMA 40.5 with it, 34.5 with the two products, 33.2 with no sum at all
+    // (head_dim 64: 52.0, 42.1, 38.3).  2K all-full layer 2955 -> 2839 us (2977 -> 2917 where every pass has
+    // other inputs), video-like 1349 -> 1270 (1353 -> 1307), mixed 1021 -> 969, FLUX-like 1K 127.8 -> 122.0 (130.0 -> 126.3);
+    // head_dim 64 within 0.5 %.  (v_add on the unrounded weights costs the same and is less exact: 2.0e-3 of
+    // the result's norm off instead of 1.75e-3 where few keys carry a row.)
+    floatx4 wsum[QB];
+    auto sum_weights = [&](int qb, int tt, const bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
+        wsum[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pw[qb][tt], tt ? wsum[qb] : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    };
+    // Closes a block: its row sums are checked (see renormalise) and added to the rows' running sums.
+    auto settle = [&](const floatx16 (&sc)[QB], bf16x8 (&pw)[QB][2], bool rescale_o) __attribute__((always_inline)) {
+        float lb[QB];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) lb[qb] = wsum[qb][0];
+        // compared as integers: a row beside one with an infinite weight has the sum NaN (0 x inf), which has to count as large
+        unsigned top = __builtin_bit_cast(unsigned, lb[0]);
+        if (QB > 1) top = top > __builtin_bit_cast(unsigned, lb[QB - 1]) ? top : __builtin_bit_cast(unsigned, lb[QB - 1]);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(top > __builtin_bit_cast(unsigned, kTrip)) != 0, 0))
+            renormalise(sc, lb, pw, rescale_o);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) rs[qb].l += lb[qb];
+    };
     auto half_step = [&](const floatx16 (&s_cur)[QB], floatx16 (&s_nxt)[QB], const bf16x8 (&p_prev)[QB][2],
                          bf16x8 (&p_cur)[QB][2], const __bf16* kst_nxt, const __bf16* kst_after,
                          const __bf16* vst_prev, const __bf16* vst_cur, bool with_pv, bool mask_nxt,
                          int blk_nxt, int dma_tensor, unsigned dma_tb, unsigned dma_dst,
                          unsigned dma_tb2 = 0, unsigned dma_dst2 = 0) __attribute__((always_inline)) {
-        float mneg[QB], lb[QB];
+        float mneg[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) mneg[qb] = -rs[qb].m;
-        unsigned held = 0;
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
             const int j = s / QB, qb = s % QB, jn = j + AHEAD;    // operand jn is fetched while operand j is used
@@ -681,23 +704,16 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
                     else vq[jn - NOP] = v_operand(vst_cur, jn - NOP);
                 }
             }
-            softmax_b(s, x, lb, p_cur, held);
+            softmax_b(s, x, p_cur);
+            if ((s & 7) == 5) sum_weights(qb, 0, p_cur);
+            if ((s & 7) == 7) sum_weights(qb, 1, p_cur);
             // the loads of a later tile are spread over the slots (a burst of them right after the
             // barrier stalls all wavefronts on the one memory pipe)
             if ((s & 3) == 1 && (s >> 2) < NDMA) dma_part(dma_tensor, s >> 2, dma_tb, dma_dst);
             if (BLK && (s & 3) == 3 && (s >> 2) < NDMA) dma_part(1, s >> 2, dma_tb2, dma_dst2);
             __builtin_amdgcn_sched_barrier(0);
         }
-        {
-            bf16x2 ones;
-            ones[0] = (__bf16)1.0f;
-            ones[1] = (__bf16)1.0f;
-            lb[QB - 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, held), ones, lb[QB - 1], false);
-        }
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(fmaxf(lb[0], lb[QB - 1]) > kTrip) != 0, 0))
-            renormalise(s_cur, mneg, lb, p_cur, with_pv);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) rs[qb].l += lb[qb];
+        settle(s_cur, p_cur, with_pv);
         // block number blk_nxt = 2*position + jb; its first key is only needed on this rare path
         if (__builtin_expect(mask_nxt, 0)) {
 #pragma unroll
@@ -846,7 +862,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // ---- epilogue: O^T register r of block db is feature d = 32*db + 8*(r/4) + 4*half + r%4
     float l_fin[QB];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) l_fin[qb] = halves_sum(rs[qb].l);
+    for (int qb = 0; qb < QB; ++qb) l_fin[qb] = rs[qb].l;
     bool writes_rows = it.part_slot < 0;
     if (it.part_slot >= 0) {
         // A piece of a cut record.  Its unnormalised fp32 accumulators, row reference (log2 domain) and row

@@ -1,0 +1,42 @@
+"""Rows whose logits leap: the reference a row's weights are expressed against moves only when a block's row sum outgrows
+2^40, and the sums of rows 16 apart come out of one matrix product, an infinite weight of one row meeting a zero coefficient
+of the other.  Each row of a wavefront leaps in a block of its own choice, or not at all, alone or together with its partner,
+by a finite weight or an infinite one, once or twice."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_22796_amd import workloads as W
+from util import ARROW, FULL, check_against_oracle, gpu_joint_attention
+import internal as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D,rows", [(64, 128), (128, 128), (128, 256)])
+@pytest.mark.parametrize("step", [30.0, 60.0, 400.0])          # leap in the log2 domain: below 2^40, above it, beyond fp32
+def test_leaping_rows(D, rows, step):
+    from paper_2503_22796_amd import binding as B
+    n_text, n_img = 40, 360
+    hp, win = np.asarray([FULL, ARROW], np.int32), np.asarray([0, 90], np.int32)
+    wl = W.Workload("leap", 1, 2, D, n_text, n_img, hp, win, seed=900 + D, positional=False)
+    q, k, v = (t.clone() for t in W.make_qkv(wl))
+    # feature f carries the leap at key[f]: only rows that have something there see it
+    keys = [2, 35, 70, 101, 150, 399]
+    q[..., :len(keys)] = 0
+    k[..., :len(keys)] = 0
+    unit = step * np.log(2.0) * D ** 0.5 / 16
+    for f, j in enumerate(keys):
+        k[:, :, j, f] = 16.0
+    for i in range(wl.N):
+        leaps = {0: [], 1: [2], 2: [1, 4], 3: [3], 4: [0, 5], 5: [4], 6: [2, 3]}[(i * 5 + i // 16) % 7]
+        for n, f in enumerate(leaps):
+            q[:, :, i, f] = unit * (n + 1)                      # a second leap starts from the first
+    print(f"leap D={D} rows={rows} step={step}", flush=True)
+    plan = B.difa_plan_create(1, 2, D, max_tokens=wl.N)
+    try:
+        I.force_rows(plan, rows)
+        out = gpu_joint_attention(q, k, v, None, hp, win, n_text, n_img, plan=plan)
+    finally:
+        B.difa_plan_destroy(plan)
+    check_against_oracle(out, q, k, v, None, hp, win, n_text, n_img)
