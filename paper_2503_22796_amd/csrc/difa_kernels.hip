@@ -422,13 +422,14 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 
     // A operand of the row sums.  P as it stands (lane l: query l % 32, keys of half l / 32) read as the B operand of a
     // 16x16x32 product has query l % 16 + 16 * (l / 16 % 2) in column l % 16 and key slots 8 * (l / 16) .. + 7: row m of A
-    // has ones in the slots of the lane groups whose parity is that of m / 4, so that every lane receives, in all four
-    // registers, the sum over both halves' keys of its own query's weights.
+    // has ones in the slots of the lane groups whose parity is that of m / 4, so that every lane receives, in
+    // register 0, the sum over both halves' keys of its own query's weights.  (Only every fourth row is there, the one register
+    // 0 comes from: with ones in the other rows as well the products take more power, 1-1.5 % of the clock.)
     bf16x8 row_ones;
     {
         const int lane = l32 + 32 * half;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) row_ones[e] = (__bf16)(((lane >> 4) ^ (lane >> 2)) & 1 ? 0.f : 1.f);
+        for (int e = 0; e < 8; ++e) row_ones[e] = (__bf16)((((lane >> 4) ^ (lane >> 2)) & 1) || (lane & 3) ? 0.f : 1.f);
     }
     floatx16 o[DB][QB];
 #pragma unroll
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // whatever is not behind an MFMA delays the next one; the steady state spends nothing on a running
     // maximum).
     //   piece s: scores 2*(s&7), 2*(s&7)+1 of row block s>>3 -> two weights 2^(score*c - reference) as
-    //   bf16 B operands
+    //   bf16 B operands (convert)
     // The reference of a row is NOT the running maximum: it is set from the first block that holds an
     // allowed key and afterwards moves only when a weight outgrows 2^kTrip.  That is detected after
     // the fact, from the block's row sum, and repaired on a rare side path (renormalise() below), so
@@ -547,11 +548,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         pin(x[0]);
         pin(x[1]);
     };
-    auto softmax_b = [&](int s, float (&x)[2], bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
+    auto convert = [&](int s, const float (&x)[2], bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
         const int qb = s >> 3, r = 2 * (s & 7);
         floatx2 pf;
         pf[0] = x[0];
-        pf[1] = __builtin_amdgcn_exp2f(x[1]);
+        pf[1] = x[1];
         bf16x2 pr = __builtin_convertvector(pf, bf16x2);
         unsigned bits = __builtin_bit_cast(unsigned, pr);
         asm volatile("" : "+v"(bits));
@@ -643,6 +644,13 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     constexpr int NMF = QB * NOP;           // MFMAs per stream per half-step
     constexpr int NSLOT = 8 * QB;           // slots per half-step: one per pair of scores of a lane
     constexpr int AHEAD = 3;                // operands in flight per stream
+    // head_dim 64 has half as many MFMAs as slots would take: S^T in the first four slots, P V in the last four (both in the
+    // first four: 7 % more clocks), and a pair of weights is converted one slot after its exponentials, whose result the
+    // conversion may not read in the very next instruction (at head_dim 128 the same costs 2 %: the MFMAs set the pace there and a
+    // slot gets longer by the conversion).  With both SD3-like 1K 141.9 -> 139.3 us, 2K 1426 -> 1406, 512 px refresh 85.2 -> 84.1.
+    constexpr int PV0 = NSLOT - NMF;        // slot of the first P V MFMA
+    constexpr int kLag = D == 64 ? 1 : 0;
+    static_assert(QB == 1 || kLag == 0, "a pair's slot and the next one belong to the same row block");
     static_assert(NOP == 8 || NOP == 4, "slot layout assumes head_dim 128 or 64");
     floatx16 s0[QB], s1[QB];                  // scores of the even / odd block in flight
     bf16x8 pa[QB][2], pb[QB][2];              // weights of the even / odd block in flight
@@ -683,13 +691,13 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
                          const __bf16* vst_prev, const __bf16* vst_cur, bool with_pv, bool mask_nxt,
                          int blk_nxt, int dma_tensor, unsigned dma_tb, unsigned dma_dst,
                          unsigned dma_tb2 = 0, unsigned dma_dst2 = 0) __attribute__((always_inline)) {
-        float mneg[QB];
+        float mneg[QB], xs[2][2];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) mneg[qb] = -rs[qb].m;
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
             const int j = s / QB, qb = s % QB, jn = j + AHEAD;    // operand jn is fetched while operand j is used
-            float x[2];
+            float (&x)[2] = xs[s & 1];
             if (s < NMF) {
                 if (j == 0) mfma_s_first(s_nxt[qb], kq[j], qf[qb][j]);
                 else mfma_s_acc(s_nxt[qb], kq[j], qf[qb][j]);
@@ -700,16 +708,20 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             }
             softmax_a(s, s_cur, mneg, x);
             __builtin_amdgcn_sched_barrier(0);
-            if (s < NMF) {
+            if (s >= PV0 && s < PV0 + NMF) {
+                const int i = j - PV0, in = i + AHEAD;
                 if (with_pv)
-                    o[j >> 1][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[j], p_prev[qb][j & 1], o[j >> 1][qb], 0, 0, 0);
+                    o[i >> 1][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[i], p_prev[qb][i & 1], o[i >> 1][qb], 0, 0, 0);
                 if (qb == 0) {
-                    if (jn < NOP) { if (with_pv) vq[jn] = v_operand(vst_prev, jn); }
-                    else vq[jn - NOP] = v_operand(vst_cur, jn - NOP);
+                    if (in < NOP) { if (with_pv) vq[in] = v_operand(vst_prev, in); }
+                    else vq[in - NOP] = v_operand(vst_cur, in - NOP);
                 }
             }
-            softmax_b(s, x, p_cur);
-            if ((s & 7) == 5) sum_weights(qb, 0, p_cur);
+            x[1] = __builtin_amdgcn_exp2f(x[1]);
+            pin(x[1]);
+            if (s >= kLag) convert(s - kLag, xs[(s - kLag) & 1], p_cur);
+            if ((s & 7) == 5 + kLag) sum_weights(qb, 0, p_cur);
+            if (kLag && s == NSLOT - 1) convert(s, x, p_cur);
             if ((s & 7) == 7) sum_weights(qb, 1, p_cur);
             // the loads of a later tile are spread over the slots (a burst of them right after the
             // barrier stalls all wavefronts on the one memory pipe)
