@@ -1115,23 +1115,25 @@ hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int rows, int n_wg,
 // costs a few 1e-6 in every weight, which is the whole error budget of this path.  It shares only the work record's
 // (batch, head, query tile) with the fast path.
 //
-// Bound by the fp64 matrix rate (72 TFLOP/s on MI355X, one of these MFMAs per SIMD every 64 clocks); converting the
-// operands and the loads straight from L2 run beside it.  A workgroup is eight wavefronts on one block of 16 query rows,
-// each taking every eighth tile of 16 keys (so that a layer of a few heads still fills the chip), combined through LDS at
+// Bound by the fp64 matrix rate (72 TFLOP/s on MI355X, one of these MFMAs per SIMD every 64 clocks) and by the vector
+// instructions, none of which runs beside it; the loads come straight from L2.  A workgroup is eight wavefronts on one block
+// of 16 query rows, each taking every eighth tile of 16 keys (so that a layer of a few heads still fills the chip), combined through LDS at
 // the end.  As in the fast path scores are computed transposed, S^T = K Q^T: the accumulator layout (lane: query
 // l % 16, register i: key 4 * i + l / 16) is then the B operand layout of O^T = V^T P^T.  Which four features make up a
 // contraction step, and which feature a row of O^T is, is free as long as both operands agree; they are chosen so that a
 // lane's part of a K, V or output row is contiguous.
-// Measured on MI355X, 5 computed heads of 64 and 1101 tokens, a cached head copied by the same launch: 34 us (at the fp64
-// matrix rate alone 12; a tile takes 3400 clocks of a SIMD, 2048 of them MFMA and most of the rest fp64 conversions, and
-// 153 of the 345 blocks see every key), 6.7 ms with one wavefront per row, scalar dot products and two passes over the
-// keys.  Weighted sums on the fp32 matrix rate instead: 36 us at the same point, and a larger error (1.0e-7 of the
-// result's norm against 64 bits; 3.0e-8 as it is, 8.7e-8 before).
+// Measured on MI355X, 5 computed heads of 64 and 1101 tokens, a cached head copied by the same launch: 31.2 us, 34.7 with 270
+// instead of 60 vector instructions a tile beside its 32 MFMAs (addresses, masks and maxima of every tile, a library
+// exponential, conversions one by one); 12 at the fp64 matrix rate alone: 153 of the 345 blocks see every key, and 60 % of the
+// compute units carry them.  6.7 ms with one wavefront per row, scalar dot products and two passes over the
+// keys.  Weighted sums on the fp32 matrix rate instead: 36 us against 34, and a larger error (1.0e-7 of the
+// result's norm against 64 bits; 3.0e-8 as it is, 8.7e-8 with scalar sums).
 // ------------------------------------------------------------------------------------------
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int kF32Rows = kF32BlockRows, kF32Keys = 16, kF32Waves = 8;
 
-template <int D>
+// WIDE: 16 token rows span 2 GiB or more (hundreds of thousands of heads in [token, head, feature] order).
+template <int D, bool WIDE>
 __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kernel(AttnArgs a) {
     constexpr int KF = D / 4;                                // features of a K or Q row per lane
     constexpr int VF = D / 16;                               // features of a V or output row per lane = 16-row blocks of O^T
@@ -1146,7 +1148,7 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
     const int N = a.n_tokens, n_text = a.n_text;
     const int i0 = it.q_tile * kBM + (int)(block % (kBM / kF32Rows)) * kF32Rows;
     if (i0 >= N) return;                                     // (uniform over the workgroup)
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, c16 = lane & 15, g = lane >> 4;
     const int b = it.bh / a.heads, h = it.bh - b * a.heads;
     const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
     const float* __restrict__ qg = (const float*)a.q + base;
@@ -1189,32 +1191,68 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
     for (int f = 0; f < VF; ++f) o[f] = doublex4{0.0, 0.0, 0.0, 0.0};
     double l = 0.0, m = -1.0e30;                             // m: reference in the log2 domain, an integer: rescaling is exact
     const double c = (double)a.scale * 1.44269504088896340736;
+    const float c32 = (float)c;
 
     // Step 4 * s + e of the contraction takes features 16 * s + 4 * g + e, so that the four lanes of a key row read 64
-    // bytes of it together.  The next tile's K rows are requested when this one's scores are done, its V rows after the
+    // bytes of it together.  The next tile's K rows are requested when this one's are converted, its V rows after the
     // last use of this one's: each has the other contraction's time to arrive.  (The last tile is requested again past the
-    // end: behind a branch the compiler would have to wait for the younger loads too.)
+    // end: behind a branch the compiler would have to wait for the younger loads too.)  A lane's place in a tile does not change;
+    // where the tile lies is a buffer descriptor of its own, which ends with the sequence: rows past that read as zero.
     floatx4 kc[KF / 4], vc[4][VF / 4];
+    const int row_bytes = WIDE ? 0 : (int)a.stride_n * 4;
+    const int at_k = c16 * row_bytes + 16 * g;
+    int at_v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) at_v[u] = (4 * u + g) * row_bytes + 4 * VF * c16;
     auto first_key = [&](int t_any) {
         const int t = t_any < tiles ? t_any : tiles - 1;
         return t < tiles0 ? begin0 + t * kF32Keys : begin1 + (t - tiles0) * kF32Keys;
     };
+    auto tile_rows = [&](const float* head, int t) {
+        const int j0 = first_key(t), rows = N - j0 < kF32Keys ? N - j0 : kF32Keys;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)(head + (int64_t)j0 * a.stride_n), 0, (rows - 1) * row_bytes + 4 * D, 0x00020000);
+    };
     auto fetch_k = [&](int t) {
-        const int j0 = first_key(t), jk = j0 + c16 < N ? j0 + c16 : N - 1;       // (keys past the end are masked)
-        const float* kr = kg + (int64_t)jk * a.stride_n + 4 * g;
+        if constexpr (WIDE) {
+            const int j = first_key(t) + c16;
+            const float* kr = kg + (int64_t)(j < N ? j : N - 1) * a.stride_n + 4 * g;
 #pragma unroll
-        for (int s = 0; s < KF / 4; ++s) kc[s] = *(const floatx4*)(kr + 16 * s);
+            for (int s = 0; s < KF / 4; ++s) kc[s] = *(const floatx4*)(kr + 16 * s);
+            return;
+        }
+        const __amdgpu_buffer_rsrc_t r = tile_rows(kg, t);
+#pragma unroll
+        for (int s = 0; s < KF / 4; ++s) kc[s] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, at_k + 64 * s, 0, 0));
     };
     auto fetch_v = [&](int t) {
-        const int j0 = first_key(t);
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int jv = j0 + 4 * u + g < N ? j0 + 4 * u + g : N - 1;
-            const float* vr = vg + (int64_t)jv * a.stride_n + c16 * VF;
+            for (int u = 0; u < 4; ++u) {
+                const int j = first_key(t) + 4 * u + g;
+                const float* vr = vg + (int64_t)(j < N ? j : N - 1) * a.stride_n + c16 * VF;
 #pragma unroll
-            for (int s = 0; s < VF / 4; ++s) vc[u][s] = *(const floatx4*)(vr + 4 * s);
+                for (int s = 0; s < VF / 4; ++s) vc[u][s] = *(const floatx4*)(vr + 4 * s);
+            }
+            return;
         }
+        const __amdgpu_buffer_rsrc_t r = tile_rows(vg, t);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int s = 0; s < VF / 4; ++s) vc[u][s] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(r, at_v[u] + 16 * s, 0, 0));
     };
+    // An fp64 MFMA and every vector instruction of the SIMD exclude each other, and changing over costs 12 clocks besides (one
+    // MFMA 64 clocks, with one conversion behind it 77, with two 80, with eight plain integer instructions 86): as few vector
+    // instructions as possible, and conversions in groups, not one before each MFMA.
+    constexpr int kGroup = 8;
+    auto convert = [](const floatx4 (&x)[2], double (&y)[kGroup]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) y[i] = (double)x[i >> 2][i & 3];
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) asm volatile("" : "+v"(y[i]));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const bool split = banded && i0 >= img0 && i_last < img1;   // text keys and band as two ranges
     fetch_k(wave);
     fetch_v(wave);
     for (int t = wave; t < tiles; t += kF32Waves) {
@@ -1222,23 +1260,34 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
         asm volatile("" ::: "memory");                       // (or the compiler reads the query rows once and holds them after all)
         doublex4 s2[2] = {doublex4{0.0, 0.0, 0.0, 0.0}, doublex4{0.0, 0.0, 0.0, 0.0}};   // two chains: neither waits for itself
 #pragma unroll
-        for (int s = 0; s < KF; ++s)
-            s2[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kc[s >> 2][s & 3], q_sm[s][lane], s2[s & 1], 0, 0, 0);
-        const doublex4 sc = s2[0] + s2[1];
-        fetch_k(t + kF32Waves);
-        float top = -INFINITY;
-        double x[4];
+        for (int h8 = 0; h8 < KF / kGroup; ++h8) {
+            const floatx4 kx[2] = {kc[2 * h8], kc[2 * h8 + 1]};
+            double kd[kGroup];
+            convert(kx, kd);
+            if (h8 == KF / kGroup - 1) fetch_k(t + kF32Waves);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = j0 + 4 * u + g;
-            const bool ok = (j < j_end) & (text_row | ((unsigned)(j - tb) < (unsigned)n_text) | ((j >= lo) & (j <= hi)));
-            x[u] = ok ? sc[u] * c : -INFINITY;
-            top = fmaxf(top, (float)x[u]);
+            for (int e = 0; e < kGroup; ++e)
+                s2[e & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[e], q_sm[kGroup * h8 + e][lane], s2[e & 1], 0, 0, 0);
         }
-        top = fmaxf(top, __shfl_xor(top, 16, 64));
-        top = fmaxf(top, __shfl_xor(top, 32, 64));
-        const double m_new = fmax(m, ceil((double)top));
-        if (__builtin_amdgcn_ballot_w64(m_new > m) != 0) {
+        doublex4 sc = s2[0] + s2[1];
+        // Does every row of the block see every key of the tile?  (the same for the whole wavefront; most tiles)
+        const bool every_pair = j0 + kF32Keys <= j_end &&
+                                (!banded || (split && (t < tiles0 || (j0 >= i_last - it.window && j0 + kF32Keys - 1 <= i0 + it.window))));
+        if (!every_pair) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = j0 + 4 * u + g;
+                const bool ok = (j < j_end) & (text_row | ((unsigned)(j - tb) < (unsigned)n_text) | ((j >= lo) & (j <= hi)));
+                sc[u] = ok ? sc[u] : -INFINITY;
+            }
+        }
+        // The reference is the maximum so far, rounded up to a whole power of two (which one exactly does not matter: moving it
+        // is exact).  Only where some row has outgrown it do the four lanes of a row exchange their maxima.
+        const float top = fmaxf(fmaxf((float)sc[0], (float)sc[1]), fmaxf((float)sc[2], (float)sc[3])) * c32;
+        if (__builtin_amdgcn_ballot_w64((double)top > m) != 0) {
+            float row_top = fmaxf(top, __shfl_xor(top, 16, 64));
+            row_top = fmaxf(row_top, __shfl_xor(row_top, 32, 64));
+            const double m_new = fmax(m, ceil((double)row_top));
             const double alpha = m < -1.0e29 ? 0.0 : ldexp(1.0, (int)fmax(m - m_new, -2000.0));
             l *= alpha;
 #pragma unroll
@@ -1247,15 +1296,25 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_f32_kern
                 for (int e = 0; e < 4; ++e) o[f][e] *= alpha;
             m = m_new;
         }
+        double p[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const double p = (double)exp2f((float)(x[u] - m));
-            l += p;
-#pragma unroll
-            for (int f = 0; f < VF; ++f)
-                o[f] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vc[u][f >> 2][f & 3], p, o[f], 0, 0, 0);
+            p[u] = (double)__builtin_amdgcn_exp2f((float)fma(sc[u], c, -m));
+            l += p[u];
         }
-        fetch_v(t + kF32Waves);
+#pragma unroll
+        for (int h8 = 0; h8 < 4 * VF / kGroup; ++h8) {
+            const floatx4* vx = &vc[0][0] + 2 * h8;
+            const floatx4 v2[2] = {vx[0], vx[1]};
+            double vd[kGroup];
+            convert(v2, vd);
+            if (h8 == 4 * VF / kGroup - 1) fetch_v(t + kF32Waves);
+#pragma unroll
+            for (int e = 0; e < kGroup; ++e) {
+                const int u = (kGroup * h8 + e) / VF, f = (kGroup * h8 + e) % VF;
+                o[f] = __builtin_amdgcn_mfma_f64_16x16x4f64(vd[e], p[u], o[f], 0, 0, 0);
+            }
+        }
     }
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
@@ -1382,12 +1441,13 @@ hipError_t launch_attn_f32(const AttnArgs& a, int head_dim, int n_items, hipStre
     // (a grid dimension holds fewer than 2^32 threads)
     const int64_t blocks = (int64_t)a.f32_blocks + a.copy_chunks, in_x = blocks < (1 << 22) ? blocks : 1 << 22;
     const dim3 grid((unsigned)in_x, (unsigned)((blocks + in_x - 1) / in_x));
-    if (head_dim == 128)
-        hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * kF32Waves), 0, stream, a);
-    else if (head_dim == 64)
-        hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * kF32Waves), 0, stream, a);
-    else
-        return hipErrorInvalidValue;
+    const bool wide = a.stride_n >= ((int64_t)1 << 31) / (4 * kF32Keys);
+    const dim3 threads(64 * kF32Waves);
+    if (head_dim == 128 && !wide) hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, threads, 0, stream, a);
+    else if (head_dim == 128) hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, threads, 0, stream, a);
+    else if (head_dim == 64 && !wide) hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, threads, 0, stream, a);
+    else if (head_dim == 64) hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, threads, 0, stream, a);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -150,3 +150,25 @@ def test_fp32_tensors_need_no_more_than_element_alignment(D):
     ref, raw, _ = O.joint_attention(q, k, v, cache, hp, win, wl.n_text, wl.n_img)
     assert float((got[:, :2].double() - ref[:, :2]).abs().max()) <= TOL_F32
     assert torch.equal(got[:, 2].view(torch.int32), raw[:, 2].contiguous().view(torch.int32))
+
+
+@pytest.mark.parametrize("n_tokens", [2, 18])
+def test_token_rows_of_hundreds_of_megabytes(n_tokens):
+    # 2^19 heads of 64 in [batch, token, head, feature] order: 16 token rows span 2 GiB, more than a 32-bit byte offset reaches
+    from paper_2503_22796_amd import binding as B
+    heads, D, dev = 1 << 19, 64, torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_tokens)
+    q, k, v = (torch.randn((1, n_tokens, heads, D), device=dev, generator=g) for _ in range(3))
+    out = torch.full_like(q, float("nan"))
+    plan = B.difa_plan_create(1, heads, D, dtype=B.DIFA_DTYPE_F32, layout=B.DIFA_LAYOUT_BNHD, max_tokens=n_tokens)
+    try:
+        B.difa_joint_attention(plan, q, k, v, out, None, np.zeros(heads, np.int32), 0, n_tokens, np.zeros(heads, np.int32))
+        torch.cuda.synchronize()
+    finally:
+        B.difa_plan_destroy(plan)
+    for h0 in (0, 12345, heads - 64):                            # 64 heads at a time, in fp64 on the host
+        qh, kh, vh = (t[0, :, h0:h0 + 64].transpose(0, 1).cpu().double().contiguous() for t in (q, k, v))
+        ref = torch.matmul(torch.softmax(torch.matmul(qh, kh.transpose(1, 2).contiguous()) / 8.0, dim=2), vh)
+        got = out[0, :, h0:h0 + 64].transpose(0, 1).cpu().double()
+        assert float((got - ref).abs().max()) <= TOL_F32
