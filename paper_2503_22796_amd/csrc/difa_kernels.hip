@@ -94,8 +94,9 @@ __device__ __forceinline__ void mfma_s_acc(floatx16& d, const bf16x8& k, const b
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(k), "a"(q));
 }
 __device__ __forceinline__ void mfma_results_visible() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-// (the same wait, tied to the registers it is for: no read of them can be moved ahead of it)
-__device__ __forceinline__ void mfma_results_visible(floatx16& d) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(d) :: "memory"); }
+// No wait, only the order: for results of an MFMA that a younger MFMA's result has already been read behind.  (The matrix
+// pipe works in order.)
+__device__ __forceinline__ void settled_results(floatx16& d) { asm volatile("" : "+v"(d) :: "memory"); }
 
 // Cache-policy operand of the buffer load/store builtins: device scope ("sc1").
 constexpr int kDeviceCoherent = 16;
@@ -471,22 +472,25 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     };
     // Element mask of one 32-key block whose first key is j0.  The host marks a tile as masked when any
     // of the record's rows has a forbidden key in it; for the rows of one wavefront most such
-    // blocks lie entirely inside the band, or are cut by one band edge only.  That is decided here from
-    // scalars, so that the common cases cost nothing or two plain integer instructions per score.
-    const int row_first = it.q_tile * BM + (int)wave_u * RW;              // this wavefront's rows (uniform)
+    // blocks lie entirely inside the band.  Which first keys those are is two intervals of the segment: blocks of text keys, and
+    // for a wavefront of image rows the blocks that all its bands cover (of other rows: everything before the end).
+    const int row_first = it.q_tile * BM + (int)wave_u * RW < N ? it.q_tile * BM + (int)wave_u * RW : N - 1;   // this wavefront's rows
     const int row_last = row_first + RW - 1 < N - 1 ? row_first + RW - 1 : N - 1;
+    int free0 = 0, free_last = N - 32;                                     // a full head, or rows that are all text
+    if (it.window >= 0 && row_last >= img0 && row_first < img1) {
+        free0 = row_last - it.window > img0 ? row_last - it.window : img0;
+        free_last = row_first + it.window < img1 - 1 ? row_first + it.window - 31 : img1 - 32;
+        if (row_first < img0 || row_last >= img1) free_last = -1;         // rows of both kinds
+    }
+    const bool some_free = free_last >= free0, some_text = n_text >= 32;
+    const int free_from = some_free ? free0 : -1, text_from = some_text ? text_begin : -1;   // (-1: no block begins there)
+    const unsigned free_span = some_free ? (unsigned)(free_last - free0) : 0u, text_span = some_text ? (unsigned)(n_text - 32) : 0u;
     auto mask_block = [&](int j0, floatx16 (&s)[QB]) {
-        const bool plain = j0 >= img0 && j0 + 31 < img1 && row_first >= img0 && row_last < img1 && it.window >= 0;
-        // image rows, image keys, no tail: row i allows keys [i - w, i + w]
-        const bool low = row_last - it.window > j0;                        // some row's band starts after j0
-        const bool high = row_first + it.window < j0 + 31;                 // some row's band ends before the block does
-        if (plain && !low && !high) return;
-        // a wavefront of text rows, or a block of text keys, inside the sequence: nothing to mask either
-        if (j0 + 31 < N && (row_last < img0 || row_first >= img1 || j0 + 31 < img0 || j0 >= img1)) return;
+        if ((unsigned)(j0 - free_from) <= free_span || (unsigned)(j0 - text_from) <= text_span) return;
         const unsigned ninf = 0xff800000u;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            // Bit r of `gone` says that register r holds the score of a forbidden key.  Register r of a lane holds the key at
+            // Bit r of `keep` says that register r holds the score of an allowed key.  Register r of a lane holds the key at
             // offset 8*(r/4) + r%4 (+ 4*half) of the block, increasing with r, so the keys below some key are the lane's
             // first k registers; the count k comes from that key with a handful of integer instructions.
             auto below = [&](int key) {                                    // registers whose key is < key
@@ -494,17 +498,10 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
                 const int rem = ec & 7;
                 return (1u << (4 * (ec >> 3) + (rem < 4 ? rem : 4))) - 1u;
             };
-            unsigned gone = 0;
-            if (plain) {
-                if (low) gone = below(rs[qb].lo);
-                if (high) gone |= ~below(rs[qb].lo + (int)rs[qb].span + 1);
-            } else {
-                // text keys or rows, or the tail of the sequence, in the block: allowed are the text keys and the row's band
-                // (spelled out key by key this path was 150 instructions, ten times in the kernel, and pushed the loop out
-                // of the instruction cache two compute units share)
-                gone = ~((below(rs[qb].lo + (int)rs[qb].span + 1) & ~below(rs[qb].lo)) |
-                         (below(text_begin + n_text) & ~below(text_begin)));
-            }
+            unsigned keep = below(rs[qb].lo + (int)rs[qb].span + 1) & ~below(rs[qb].lo);
+            // text keys in the block (spelled out key by key this was 150 instructions, ten times in the kernel, and pushed the
+            // loop out of the instruction cache two compute units share)
+            if (j0 < img0 || j0 + 31 >= img1) keep |= below(text_begin + n_text) & ~below(text_begin);
             // Each score then costs a signed one-bit extract (all ones or zero) and a bit-select between the score
             // and -inf, in place.  No compare writes a lane mask that the next instruction would have to wait for
             // (a compare and a select that reads its result cost 20 clocks a pair on this chip, four ordinary
@@ -517,11 +514,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 #pragma unroll
             for (int r = 0; r < 16; ++r) x[r] = s[qb][r];
             unsigned t0, t1;
-            asm volatile("v_bfe_i32 %16, %18, 0, 1\n\tv_bfe_i32 %17, %18, 1, 1\n\tv_bfi_b32 %0, %16, %19, %0\n\tv_bfi_b32 %1, %17, %19, %1\n\tv_bfe_i32 %16, %18, 2, 1\n\tv_bfe_i32 %17, %18, 3, 1\n\tv_bfi_b32 %2, %16, %19, %2\n\tv_bfi_b32 %3, %17, %19, %3\n\tv_bfe_i32 %16, %18, 4, 1\n\tv_bfe_i32 %17, %18, 5, 1\n\tv_bfi_b32 %4, %16, %19, %4\n\tv_bfi_b32 %5, %17, %19, %5\n\tv_bfe_i32 %16, %18, 6, 1\n\tv_bfe_i32 %17, %18, 7, 1\n\tv_bfi_b32 %6, %16, %19, %6\n\tv_bfi_b32 %7, %17, %19, %7\n\tv_bfe_i32 %16, %18, 8, 1\n\tv_bfe_i32 %17, %18, 9, 1\n\tv_bfi_b32 %8, %16, %19, %8\n\tv_bfi_b32 %9, %17, %19, %9\n\tv_bfe_i32 %16, %18, 10, 1\n\tv_bfe_i32 %17, %18, 11, 1\n\tv_bfi_b32 %10, %16, %19, %10\n\tv_bfi_b32 %11, %17, %19, %11\n\tv_bfe_i32 %16, %18, 12, 1\n\tv_bfe_i32 %17, %18, 13, 1\n\tv_bfi_b32 %12, %16, %19, %12\n\tv_bfi_b32 %13, %17, %19, %13\n\tv_bfe_i32 %16, %18, 14, 1\n\tv_bfe_i32 %17, %18, 15, 1\n\tv_bfi_b32 %14, %16, %19, %14\n\tv_bfi_b32 %15, %17, %19, %15"
+            asm volatile("v_bfe_i32 %16, %18, 0, 1\n\tv_bfe_i32 %17, %18, 1, 1\n\tv_bfi_b32 %0, %16, %0, %19\n\tv_bfi_b32 %1, %17, %1, %19\n\tv_bfe_i32 %16, %18, 2, 1\n\tv_bfe_i32 %17, %18, 3, 1\n\tv_bfi_b32 %2, %16, %2, %19\n\tv_bfi_b32 %3, %17, %3, %19\n\tv_bfe_i32 %16, %18, 4, 1\n\tv_bfe_i32 %17, %18, 5, 1\n\tv_bfi_b32 %4, %16, %4, %19\n\tv_bfi_b32 %5, %17, %5, %19\n\tv_bfe_i32 %16, %18, 6, 1\n\tv_bfe_i32 %17, %18, 7, 1\n\tv_bfi_b32 %6, %16, %6, %19\n\tv_bfi_b32 %7, %17, %7, %19\n\tv_bfe_i32 %16, %18, 8, 1\n\tv_bfe_i32 %17, %18, 9, 1\n\tv_bfi_b32 %8, %16, %8, %19\n\tv_bfi_b32 %9, %17, %9, %19\n\tv_bfe_i32 %16, %18, 10, 1\n\tv_bfe_i32 %17, %18, 11, 1\n\tv_bfi_b32 %10, %16, %10, %19\n\tv_bfi_b32 %11, %17, %11, %19\n\tv_bfe_i32 %16, %18, 12, 1\n\tv_bfe_i32 %17, %18, 13, 1\n\tv_bfi_b32 %12, %16, %12, %19\n\tv_bfi_b32 %13, %17, %13, %19\n\tv_bfe_i32 %16, %18, 14, 1\n\tv_bfe_i32 %17, %18, 15, 1\n\tv_bfi_b32 %14, %16, %14, %19\n\tv_bfi_b32 %15, %17, %15, %19"
                          : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]),
                            "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15]),
                            "=&v"(t0), "=&v"(t1)
-                         : "v"(gone), "v"(ninf));
+                         : "v"(keep), "v"(ninf));
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[qb][r] = x[r];
         }
@@ -672,7 +669,10 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     auto settle = [&](const floatx16 (&sc)[QB], bf16x8 (&pw)[QB][2], bool first) __attribute__((always_inline)) {
         float lb[QB];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) lb[qb] = wsum[qb][0];
+        for (int qb = 0; qb < QB; ++qb) {
+            lb[qb] = wsum[qb][0];
+            pin(lb[qb]);                    // (read here, whatever follows)
+        }
         if (first) {                        // (the weights are at most 1)
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) rs[qb].l = lb[qb];
@@ -730,10 +730,13 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             __builtin_amdgcn_sched_barrier(0);
         }
         settle(s_cur, p_cur, !with_pv);
-        // block number blk_nxt = 2*position + jb; its first key is only needed on this rare path
+        // block number blk_nxt = 2*position + jb; its first key is only needed on this rare path.  (settle() has read the row sums,
+        // which the matrix pipe makes after the last S^T MFMA: the scores are there.  Another 32 wait states here, scalar
+        // decisions about each edge of the band and a branch for each cost the SD3-like 512 px refresh 85.5 us instead of 82,
+        // the 1K layer 138.3 instead of 134.5.)
         if (__builtin_expect(mask_nxt, 0)) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) mfma_results_visible(s_nxt[qb]);
+            for (int qb = 0; qb < QB; ++qb) settled_results(s_nxt[qb]);
             mask_block(tile_of(blk_nxt >> 1) * kBN + 32 * (blk_nxt & 1), s_nxt);
         }
     };
