@@ -572,15 +572,15 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
     std::vector<double> speed((size_t)n_xcd, 1.0);         // relative speeds of the dies (their clocks differ under load)
     if (die_speed)
         for (int x = 0; x < n_xcd; ++x) speed[(size_t)x] = die_speed[x] > 0.5 && die_speed[x] < 2.0 ? die_speed[x] : 1.0;
-    std::vector<double> share(speed);                      // the part of the work each die is given, up to a common factor
-    std::vector<DiePlan> plans((size_t)n_xcd), first_plans;
     std::vector<std::vector<std::pair<int64_t, int>>> die((size_t)n_xcd);
     std::vector<int64_t> die_cost((size_t)n_xcd);
-    double first_t_max = 0.0;
-    // Two rounds at most: the first hands out the work in proportion to the dies' speeds; where the plans that
-    // come out of it would finish more than three hundredths apart (a die whose records had to be cut carries the
-    // overhead of the cuts), the shares are corrected by that and the plans made again, and kept if they are better.
-    for (int round = 0; round < 2; ++round) {
+    // The dies' plans for given shares of the work (up to a common factor), and the predicted finishing times of the first, the
+    // last and all of them together, in cost units of a die of speed 1.
+    struct Plans {
+        std::vector<DiePlan> die;
+        double t_min = 0.0, t_max = 0.0, t_sum = 0.0;
+    };
+    const auto plans_for = [&](const std::vector<double>& share) {
         std::vector<double> upto((size_t)n_xcd + 1, 0.0);  // cumulative share of the work that dies 0 .. x-1 take
         {
             double sum = 0.0;
@@ -600,6 +600,8 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
                 die_cost[(size_t)x_at] += cost[k];
                 cum += cost[k];
             }
+        Plans p;
+        p.die.resize((size_t)n_xcd);
         int slots_so_far = 0;
         for (int x = 0; x < n_xcd; ++x) {
             // costliest records first (a query tile that holds text rows visits every key tile); the interior
@@ -607,29 +609,37 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
             std::stable_sort(die[(size_t)x].begin(), die[(size_t)x].end(),
                              [](const std::pair<int64_t, int>& a, const std::pair<int64_t, int>& b) { return a.first > b.first; });
             const int budget = slot_capacity - slots_so_far - 2 * per_die * (n_xcd - 1 - x);   // this die's share of the slots
-            plans[(size_t)x] = Die{m, recs, die[(size_t)x], die_cost[(size_t)x], per_die, budget}.schedule();
-            slots_so_far += plans[(size_t)x].n_slots;
-            if (tried) *tried += plans[(size_t)x].tried;
+            p.die[(size_t)x] = Die{m, recs, die[(size_t)x], die_cost[(size_t)x], per_die, budget}.schedule();
+            slots_so_far += p.die[(size_t)x].n_slots;
+            if (tried) *tried += p.die[(size_t)x].tried;
+            const double t = (double)p.die[(size_t)x].makespan / speed[(size_t)x];
+            p.t_min = x == 0 ? t : std::min(p.t_min, t);
+            p.t_max = std::max(p.t_max, t);
+            p.t_sum += t;
         }
-        // predicted finishing times, in cost units of a die of speed 1
-        double t_min = 0.0, t_max = 0.0, t_sum = 0.0;
-        for (int x = 0; x < n_xcd; ++x) {
-            const double t = (double)plans[(size_t)x].makespan / speed[(size_t)x];
-            t_min = x == 0 ? t : std::min(t_min, t);
-            t_max = std::max(t_max, t);
-            t_sum += t;
-        }
-        if (round == 1) {
-            if (t_max >= first_t_max) plans.swap(first_plans);       // the correction did not help: keep the first plans
-            break;
-        }
-        if (t_sum <= 0.0 || t_min <= 0.0 || (t_max - t_min) * n_xcd <= 0.03 * t_sum) break;
+        return p;
+    };
+    const auto apart = [&](const Plans& p) { return p.t_min > 0.0 && (p.t_max - p.t_min) * n_xcd > 0.03 * p.t_sum; };
+    // First the work is handed out in proportion to the dies' speeds; where the plans that come out of it would finish more
+    // than three hundredths apart (a die whose records had to be cut carries the overhead of the cuts), the shares are corrected
+    // by that and the plans made again, and kept if they are better.
+    Plans best = plans_for(speed);
+    if (apart(best)) {
+        std::vector<double> share(speed);
         for (int x = 0; x < n_xcd; ++x)
-            share[(size_t)x] *= (t_sum / n_xcd) / ((double)plans[(size_t)x].makespan / speed[(size_t)x]);
-        first_t_max = t_max;
-        first_plans = std::move(plans);
-        plans.assign((size_t)n_xcd, DiePlan());
+            share[(size_t)x] *= (best.t_sum / n_xcd) / ((double)best.die[(size_t)x].makespan / speed[(size_t)x]);
+        Plans next = plans_for(share);
+        if (next.t_max < best.t_max) best = std::move(next);
     }
+    // With a record or two for each workgroup a share a few hundredths larger can be one record more than the die has
+    // workgroups, and the layer takes as long as two: equal shares then.  (512 records of 1024 keys at head_dim 128, one for each
+    // workgroup: 39 us, and 51 in those processes whose measured die speeds gave some die 65 of them; 4096 keys: 122 us, 131-142 with
+    // records cut to avoid that; head_dim 64 72.7 and 80.)
+    if (die_speed && recs.size() <= 2 * (size_t)n_wg && apart(best)) {
+        Plans next = plans_for(std::vector<double>((size_t)n_xcd, 1.0));
+        if (next.t_max < best.t_max) best = std::move(next);
+    }
+    std::vector<DiePlan>& plans = best.die;
 
     // ---- the plans written out: segments grouped by workgroup (workgroup w of die x is number w * n_xcd + x)
     int64_t n_segs = 0, n_slots = 0, n_merges = 0;

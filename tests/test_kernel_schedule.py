@@ -233,3 +233,14 @@ def test_record_length_of_the_named_layers():
     wl = W.flux_2k_mixed()
     assert I.record_rows(2, wl.D, wl.head_plan, wl.window, wl.n_text, wl.n_img) == 256          # 16.7 M pairs a compute unit
     assert I.record_rows(1, wl.D, [CACHE] * 24, [0] * 24, wl.n_text, wl.n_img) == 128           # nothing computed
+
+
+@pytest.mark.parametrize("heads,speeds", [(64, [1.03, 0.97, 1.02, 0.98, 1.0, 1.0, 1.01, 0.99]), (60, [1.1, 0.9, 1.05, 0.95, 1.0, 1.0, 1.0, 1.0])])
+def test_speeds_of_dies_do_not_give_one_more_records_than_workgroups(heads, speeds):
+    # 512 (or 480) equal records on 512 workgroups: in proportion to the speeds some die would get 65 for its 64 workgroups and
+    # take as long as two records
+    items = I.records(1, [FULL] * heads, [0] * heads, 0, 1024, 128, 128)
+    segs, wg_begin, merges, n_slots, span, _ = I.schedule(items, 128, 512, 8, speeds)
+    _check_schedule(items, segs, wg_begin, merges, n_slots, 512, 8)
+    one = I.schedule(items, 128, 512)[4].max()
+    assert (span / np.asarray(speeds)).max() <= 1.12 * one
