@@ -623,20 +623,18 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
     // First the work is handed out in proportion to the dies' speeds; where the plans that come out of it would finish more
     // than three hundredths apart (a die whose records had to be cut carries the overhead of the cuts), the shares are corrected
     // by that and the plans made again, and kept if they are better.
+    // A layer with no more records than workgroups is another matter: there a share a few hundredths larger can be one record more
+    // than the die has workgroups, which takes as long as two, or has records cut to avoid that, and equal shares are the
+    // correction.  (512 records of 1024 keys at head_dim 128, one for each workgroup: 39 us, and 51 in those processes whose measured
+    // die speeds gave some die 65 of them; 4096 keys: 122 us, 131-142 with records cut; head_dim 64 72.7 and 80.)
     Plans best = plans_for(speed);
     if (apart(best)) {
-        std::vector<double> share(speed);
-        for (int x = 0; x < n_xcd; ++x)
-            share[(size_t)x] *= (best.t_sum / n_xcd) / ((double)best.die[(size_t)x].makespan / speed[(size_t)x]);
+        const bool uneven = *std::max_element(speed.begin(), speed.end()) > *std::min_element(speed.begin(), speed.end());
+        std::vector<double> share((size_t)n_xcd, 1.0);
+        if (!uneven || recs.size() > (size_t)n_wg)
+            for (int x = 0; x < n_xcd; ++x)
+                share[(size_t)x] = speed[(size_t)x] * (best.t_sum / n_xcd) / ((double)best.die[(size_t)x].makespan / speed[(size_t)x]);
         Plans next = plans_for(share);
-        if (next.t_max < best.t_max) best = std::move(next);
-    }
-    // With a record or two for each workgroup a share a few hundredths larger can be one record more than the die has
-    // workgroups, and the layer takes as long as two: equal shares then.  (512 records of 1024 keys at head_dim 128, one for each
-    // workgroup: 39 us, and 51 in those processes whose measured die speeds gave some die 65 of them; 4096 keys: 122 us, 131-142 with
-    // records cut to avoid that; head_dim 64 72.7 and 80.)
-    if (die_speed && recs.size() <= 2 * (size_t)n_wg && apart(best)) {
-        Plans next = plans_for(std::vector<double>((size_t)n_xcd, 1.0));
         if (next.t_max < best.t_max) best = std::move(next);
     }
     std::vector<DiePlan>& plans = best.die;
