@@ -16,20 +16,21 @@ constexpr int kBN = 64;   // keys per K/V tile
 // head_dim 64 (the softmax's share of an iteration is twice as large): 128 rows throughout.  Clocks per 256 rows x 64 keys on
 // MI355X 2050 against 2190-2360; SD3-like 512 px layers 1.13 times as fast, the 1K layer up to 1.05; at 2K (where the clock
 // gives way as the loop gets denser) the same.  64 rows per wavefront as well: 2010 clocks, 2K the same, 1K 0.75 times.
-// head_dim 128: the loop takes the same 2870-2940 clocks both ways, and the second copy of every tile costs 4-5 % of the
-// clock the chip holds (1.64 against 1.72 GHz on the all-full 2K layer).  Short records earn that back where a band covers
-// noticeably fewer keys for 128 rows than for 256, where records are few tiles long, and where the layer is too small to fill
-// the chip otherwise; with heads that see every key, or blocks of 256 rows, there is nothing to earn.  256 rows against 128, us
+// head_dim 128: the loop takes 2350-2450 clocks with records of 128 rows and 2650 with 256, and the second copy of every tile costs
+// the power that those clocks save (the chip holds less than 1.7 GHz on such layers; all-full 2K 2800 us with 256 rows, 2885 with
+// 128).  Short records earn it back where a band covers noticeably fewer keys for 128 rows than for 256, where records are few tiles
+// long, and where the layer is too small to fill the chip otherwise; with heads that see every key, or blocks of 256 rows, there is
+// nothing to earn.  256 rows against 128, us
 // (one MI355X, 24 heads but where said; "saved": share of the key tiles that the shorter records do not visit):
-//   all full              1536 tokens 43.2 / 45.2, 4608 236 / 240, 9216 859 / 890, 13056 1739 / 1756, 16896 2846 / 2948
-//   ... of few heads      1536 tokens, 6 heads 39.7 / 27.9, 12 heads 32.9 / 33.4; 2560 tokens, 6 heads 34.5 / 35.8
-//   ... short             768 tokens 25.9 / 19.4, 300 tokens 17.0 / 12.8
-//   block-granular band   16896 tokens, w = 2048 894 / 934, 1024 603 / 605, 512 447 / 444, 128 (17 tiles a record) 376 / 324;
-//                         mixed plan 943 / 960
-//   full and w = N / 16   12 + 12 at 9216 tokens (1.0 % saved) 560 / 567, at 4608 (1.8 %) 172.6 / 175.4;
-//                         8 + 16 at 9216 (1.7 %) 462 / 457; 4 + 20 at 16896 (1.8 %) 1020 / 1011; mixed 2K (1.2 %) 1001 / 993
-//   all arrow             16896 tokens, w = 4224 (1.3 %, 14.6 M pairs a compute unit) 1477 / 1526, 2112 (2.3 %) 939 / 936,
-//                         528 (5.3 %) 498 / 468; pairs of them, w = 2048 (2.4 %, 15.8 M) 1824 / 1846, 1024 (9.5 M) 1231 / 1207
+//   all full              1536 tokens 40.4 / 41.3, 4608 229 / 231, 9216 844 / 860, 13056 1668 / 1702, 16896 2799 / 2885
+//   ... of few heads      1536 tokens, 6 heads 37.0 / 25.9, 12 heads 32.5 / 30.9; 2560 tokens, 6 heads 35.5 / 34.7, 12 heads 49.3 / 48.0
+//   ... short             768 tokens 24.2 / 17.9, 300 tokens 16.2 / 11.5
+//   block-granular band   16896 tokens, w = 2048 845 / 858, 1024 567 / 570, 512 424 / 420, 128 (17 tiles a record) 311 / 306;
+//                         mixed plan 913 / 920
+//   full and w = N / 16   12 + 12 at 9216 tokens (1.0 % saved) 546 / 547, at 4608 (1.8 %) 169.5 / 167.2;
+//                         8 + 16 at 9216 (1.7 %) 454 / 440; 4 + 20 at 16896 (1.8 %) 991 / 959; mixed 2K (1.2 %) 958 / 964
+//   all arrow             16896 tokens, w = 4224 (1.3 %, 14.6 M pairs a compute unit) 1404 / 1408, 2112 (2.3 %) 883 / 858,
+//                         528 (5.3 %) 458 / 424; pairs of them, w = 2048 (2.4 %, 15.8 M) 1728 / 1748, 1024 (9.5 M) 1166 / 1157
 constexpr int kRowsShort = 128, kRowsLong = 256;
 constexpr double kLongPairsPerCu = 14.0e6;   // head_dim 128, query-key pairs per compute unit: 256 rows above this line,
 constexpr double kShortPairsPerCu = 0.13e6;  // 128 below this one; between them 128 where an image record visits fewer

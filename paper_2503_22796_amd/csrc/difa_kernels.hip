@@ -57,7 +57,7 @@ __device__ __forceinline__ float halves_sum(float x) {
 //
 // Scores are produced transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: a lane then holds
 // 16 keys of ONE query (column = lane % 32), so the softmax row statistics are per-lane scalars
-// and need one exchange between the wavefront halves.  The same register layout is exactly the
+// (a maximum needs one exchange between the wavefront halves, the sums come from the matrix core).  The same register layout is exactly the
 // B operand of O^T = V^T P^T, so P never goes through LDS.  V stays row-major [key][feature] in
 // LDS and its transposed operand comes from ds_read_b64_tr_b16.
 //
@@ -359,10 +359,10 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     };
     int next_chunk = mine ? (int)blockIdx.x : 0x7fffffff;
     // Where two workgroups share a compute unit, its SIMDs serve the older wavefront first: left to itself (head_dim 64) the
-    // workgroup that was dispatched second ran at 2500 clocks an iteration beside 1735 of the other, and the schedule, which
-    // gives both the same work, waits for it.  So the younger half of the grid runs every other iteration at the higher
-    // priority.  With and without: SD3-like 2K layer 1443 / 1475 us, 1K 141.6 / 144.0, 512 px 28.6 / 29.7; head_dim 128 the same
-    // either way.  (A segment leaves the priority as its last iteration had it: lowering it after the key loop changes nothing.)
+    // workgroup that was dispatched second ran at 2500 clocks an iteration beside 1735 of the other (before the row sums moved to
+    // the matrix core), and the schedule, which gives both the same work, waits for it.  So the younger half of the grid runs every other
+    // iteration at the higher priority.  With and without: SD3-like 2K layer 1365 / 1391 us, 1K 132.3 / 136.5; every half-step instead 1377 and 135.8; head_dim
+    // 128 the same either way.  (A segment leaves the priority as its last iteration had it: lowering it after the key loop changes nothing.)
     const bool younger = wgs_per_cu(BM) > 1 && (int)blockIdx.x >= a.younger_from;
 
     difa_segment_t seg_next{};

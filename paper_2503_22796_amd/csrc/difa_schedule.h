@@ -28,6 +28,8 @@ constexpr CostModel kGenericCosts{7, 36, 72, 40, 12};   // what difa_schedule_bu
 // besides (difa_trial.h).  Charging {6, 43, 46, 22, 8}, the measured ones, instead: FLUX-like 1K layer 128.8 us (129.1 as it
 // is), 2K mixed 993 (1000), all full 2892 (2900), video-like 1312 (1328), w = 128 at 1K 94.0 (94.8), runs of one side differing
 // by as much; one set does for both record lengths for the same reason.
+// (An iteration is shorter by now, 2350-2650 and 1700-1850 clocks, and records, pieces and folds are more of them: 5.5-7, 5-8 and
+// 2.3-2.9 at head_dim 128, 5-6, 5-6 and 2 at 64.  {10, 36, 42, 16, 8} and {8, 44, 50, 20, 8} changed no layer by more than 0.5 %.)
 constexpr CostModel kernel_costs(int head_dim) {
     return head_dim == 64 ? CostModel{11, 12, 28, 21, 8} : CostModel{8, 26, 36, 19, 8};
 }
