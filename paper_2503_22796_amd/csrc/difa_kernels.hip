@@ -557,6 +557,21 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         pw[qb][r >> 3][r & 7] = pr[0];
         pw[qb][r >> 3][(r & 7) + 1] = pr[1];
     };
+    // Sum of a row's weights in a block from that row's lanes alone (rare paths: see sum_weights for the others).
+    auto own_sum = [&](const bf16x8 (&pw)[2]) __attribute__((always_inline)) {
+        bf16x2 ones;
+        ones[0] = (__bf16)1.0f;
+        ones[1] = (__bf16)1.0f;
+        float sum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            bf16x2 pr;
+            pr[0] = pw[r >> 3][r & 7];
+            pr[1] = pw[r >> 3][(r & 7) + 1];
+            sum = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, sum, false);
+        }
+        return halves_sum(sum);
+    };
     // Rare side path, uniform over the wavefront: some row of block g produced a weight beyond 2^kTrip
     // (also a row's first block with an allowed key, if that is not the segment's first).  Every row
     // whose block maximum exceeds its reference by more than 2^kBump takes that maximum as its new
@@ -576,21 +591,16 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             alpha[qb] = __builtin_amdgcn_exp2f(m_old - m_new);
             rs[qb].m = m_new;
             rs[qb].l *= alpha[qb];
-            lb[qb] = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
-                bf16x2 ones;
-                ones[0] = (__bf16)1.0f;
-                ones[1] = (__bf16)1.0f;
                 floatx2 pf;
                 pf[0] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r], c, -m_new));
                 pf[1] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r + 1], c, -m_new));
                 const bf16x2 pr = __builtin_convertvector(pf, bf16x2);
                 pw[qb][r >> 3][r & 7] = pr[0];
                 pw[qb][r >> 3][(r & 7) + 1] = pr[1];
-                lb[qb] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, lb[qb], false);
             }
-            lb[qb] = halves_sum(lb[qb]);
+            lb[qb] = own_sum(pw[qb]);
         }
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
@@ -673,16 +683,19 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             lb[qb] = wsum[qb][0];
             pin(lb[qb]);                    // (read here, whatever follows)
         }
-        if (first) {                        // (the weights are at most 1)
+        // compared as integers: a row beside one with an infinite weight has the sum NaN (0 x inf), which has to count as large
+        unsigned top = __builtin_bit_cast(unsigned, lb[0]);
+        if (QB > 1) top = top > __builtin_bit_cast(unsigned, lb[QB - 1]) ? top : __builtin_bit_cast(unsigned, lb[QB - 1]);
+        const bool large = __builtin_amdgcn_ballot_w64(top > __builtin_bit_cast(unsigned, kTrip)) != 0;
+        if (first) {                        // the weights are at most 1, or NaN: a row of Q that is not finite, which stays with its own row
+            if (__builtin_expect(large, 0))
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) lb[qb] = own_sum(pw[qb]);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) rs[qb].l = lb[qb];
             return;
         }
-        // compared as integers: a row beside one with an infinite weight has the sum NaN (0 x inf), which has to count as large
-        unsigned top = __builtin_bit_cast(unsigned, lb[0]);
-        if (QB > 1) top = top > __builtin_bit_cast(unsigned, lb[QB - 1]) ? top : __builtin_bit_cast(unsigned, lb[QB - 1]);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(top > __builtin_bit_cast(unsigned, kTrip)) != 0, 0))
-            renormalise(sc, lb, pw);
+        if (__builtin_expect(large, 0)) renormalise(sc, lb, pw);
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) rs[qb].l += lb[qb];
     };

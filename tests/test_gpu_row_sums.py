@@ -1,7 +1,7 @@
 """Rows whose logits leap: the reference a row's weights are expressed against moves only when a block's row sum outgrows
 2^40, and the sums of rows 16 apart come out of one matrix product, an infinite weight of one row meeting a zero coefficient
 of the other.  Each row of a wavefront leaps in a block of its own choice, or not at all, alone or together with its partner,
-by a finite weight or an infinite one, once or twice."""
+by a finite weight or an infinite one, once or twice.  A row of Q that is not finite makes its own output so and no other."""
 import numpy as np
 import pytest
 import torch
@@ -39,4 +39,28 @@ def test_leaping_rows(D, rows, step):
         out = gpu_joint_attention(q, k, v, None, hp, win, n_text, n_img, plan=plan)
     finally:
         B.difa_plan_destroy(plan)
+    check_against_oracle(out, q, k, v, None, hp, win, n_text, n_img)
+
+
+@pytest.mark.parametrize("D,rows", [(64, 128), (128, 128), (128, 256)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_query_rows_that_are_not_finite_stay_alone(D, rows, value):
+    from paper_2503_22796_amd import binding as B
+    n_text, n_img = 40, 360
+    hp, win = np.asarray([FULL, ARROW], np.int32), np.asarray([0, 90], np.int32)
+    wl = W.Workload("alone", 1, 2, D, n_text, n_img, hp, win, seed=950 + D, positional=False)
+    q, k, v = W.make_qkv(wl)
+    bad = [0, 21, 39, 50, 130, 255, 399]                        # text and image rows of either half of 32, none 16 from another
+    broken = q.clone()
+    broken[:, :, bad, 3] = value
+    print(f"not finite D={D} rows={rows} value={value}", flush=True)
+    plan = B.difa_plan_create(1, 2, D, max_tokens=wl.N)
+    try:
+        I.force_rows(plan, rows)
+        clean = gpu_joint_attention(q, k, v, None, hp, win, n_text, n_img, plan=plan)
+        out = gpu_joint_attention(broken, k, v, None, hp, win, n_text, n_img, plan=plan)
+    finally:
+        B.difa_plan_destroy(plan)
+    assert not bool(torch.isfinite(out[:, :, bad].float()).any())
+    out[:, :, bad] = clean[:, :, bad]
     check_against_oracle(out, q, k, v, None, hp, win, n_text, n_img)
