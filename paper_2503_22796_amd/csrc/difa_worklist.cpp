@@ -623,35 +623,28 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
     // First the work is handed out in proportion to the dies' speeds; where the plans that come out of it would finish more
     // than three hundredths apart (a die whose records had to be cut carries the overhead of the cuts), the shares are corrected
     // by that and the plans made again, and kept if they are better.
-    // A layer with no more records than workgroups is another matter: there a share a few hundredths larger can be one record more
-    // than the die has workgroups, which takes as long as two, or has records cut to avoid that, and equal shares are the
-    // correction.  (512 records of 1024 keys at head_dim 128, one for each workgroup: 39 us, and 51 in those processes whose measured
-    // die speeds gave some die 65 of them; 4096 keys: 122 us, 131-142 with records cut; head_dim 64 72.7 and 80.)
-    // Each way is tried after the other only where the last die is still predicted to end a tenth behind the mean, so that first
-    // calls seldom wait for a third set of plans.
-    Plans best = plans_for(speed);
-    std::vector<double> best_share(speed);
-    const bool uneven = *std::max_element(speed.begin(), speed.end()) > *std::min_element(speed.begin(), speed.end());
-    const auto late = [&](double by) { return best.t_max * n_xcd > (1.0 + by) * best.t_sum; };   // the last die, behind the mean
-    const auto try_shares = [&](const std::vector<double>& share) {
-        Plans next = plans_for(share);
-        if (next.t_max >= best.t_max) return;
-        best = std::move(next);
-        best_share = share;
-    };
-    const auto try_corrected = [&]() {
-        std::vector<double> share(best_share);
+    // Where the last die is still predicted to end well behind the mean, equal shares are tried as well, and corrected in their turn.
+    // A layer with no more records than workgroups needs them most: there a share a few hundredths larger can be one record more
+    // than the die has workgroups, which takes as long as two, or has records cut to avoid that. (512 records of 1024 keys at
+    // head_dim 128, one for each workgroup: 39 us, and 51 in those processes whose measured die speeds gave some die 65 of them; 4096
+    // keys: 122 us, 131-142 with records cut; head_dim 64 72.7 and 80.)  No way rules out another, the earliest end is kept: equal
+    // shares instead of the correction, whichever came first, end up to three times as late (6 heads, 3658 tokens).
+    const Plans first = plans_for(speed);
+    Plans best = first;
+    const auto keep_better = [&](Plans next) { if (next.t_max < best.t_max) best = std::move(next); };
+    const auto corrected = [&](const Plans& p, std::vector<double> share) {
         for (int x = 0; x < n_xcd; ++x)
-            share[(size_t)x] *= (best.t_sum / n_xcd) / ((double)best.die[(size_t)x].makespan / speed[(size_t)x]);
-        try_shares(share);
+            share[(size_t)x] *= (p.t_sum / n_xcd) / ((double)p.die[(size_t)x].makespan / speed[(size_t)x]);
+        return plans_for(share);
     };
-    const std::vector<double> equal((size_t)n_xcd, 1.0);
-    if (uneven && recs.size() <= (size_t)n_wg) {
-        if (late(0.02)) try_shares(equal);
-        if (apart(best) && late(0.1)) try_corrected();
-    } else {
-        if (apart(best)) try_corrected();
-        if (uneven && late(0.1)) try_shares(equal);
+    const auto late = [&](double by) { return best.t_max * n_xcd > (1.0 + by) * best.t_sum; };   // the last die, behind the mean
+    const bool uneven = *std::max_element(speed.begin(), speed.end()) > *std::min_element(speed.begin(), speed.end());
+    if (apart(first)) keep_better(corrected(first, speed));
+    if (uneven && late(recs.size() <= (size_t)n_wg ? 0.02 : 0.1)) {
+        const std::vector<double> equal((size_t)n_xcd, 1.0);
+        const Plans even = plans_for(equal);
+        keep_better(even);
+        if (apart(even) && late(0.1)) keep_better(corrected(even, equal));
     }
     std::vector<DiePlan>& plans = best.die;
 
