@@ -35,12 +35,11 @@ __device__ __forceinline__ float halves_sum(float x) {
 // ------------------------------------------------------------------------------------------
 // bf16 MFMA attention.
 //
-// A workgroup is BM / 32 / QB wavefronts (QB = 32-row blocks per wavefront; 1 in the shipped build, so eight
-// wavefronts, or two workgroups of four on a compute unit, two per SIMD) and stays resident: it walks
+// A workgroup is BM / 32 wavefronts (eight, or two workgroups of four on a compute unit: two per SIMD) and stays resident: it walks
 // the list of segments the host scheduler gave it.  A segment is a BM-row query tile of one (batch, head) together with a
 // run of that record's key/value tiles (the whole run for most records; a few records are cut so
 // that every workgroup ends at the same time, and their pieces leave fp32 partial results that the
-// piece finishing last folds into its own).  Wavefront w owns rows 32*QB*w .. 32*QB*(w+1)-1 as QB 32-row blocks.
+// piece finishing last folds into its own).  Wavefront w owns rows 32*w .. 32*w+31.
 // Key/value tiles of 64 keys are written into 4-stage LDS rings by the buffer-load-to-LDS DMA, K three
 // tiles and V two tiles ahead of their use (with two workgroups on a compute unit: stages of half a tile, K four and V two
 // blocks of 32 keys ahead, a barrier for every block),
@@ -49,11 +48,13 @@ __device__ __forceinline__ float halves_sum(float x) {
 // block-sparse band).  The first tiles and the Q rows of the next segment are requested before
 // the current segment's epilogue.
 //
-// Rows per wavefront: with 64 rows (QB = 2) every 16-byte-per-lane LDS operand read feeds two MFMAs,
-// but the whole register file goes to one wavefront per SIMD, and a single wavefront does not overlap
+// Rows per wavefront: with 64 rows every 16-byte-per-lane LDS operand read would feed two MFMAs,
+// but the whole register file would go to one wavefront per SIMD, and a single wavefront does not overlap
 // its own vector arithmetic with its own MFMAs: measured, the clocks of the two simply add.  With 32
-// rows (QB = 1) a wavefront fits in half the register file, two share a SIMD, and one's softmax runs
-// under the other's MFMAs; LDS (twice the operand reads) is busy about a third of the time.
+// rows a wavefront fits in half the register file, two share a SIMD, and one's softmax runs
+// under the other's MFMAs; LDS (twice the operand reads) is busy about a third of the time.  (Before the row sums moved to the
+// matrix core 32 rows took 16 % fewer clocks a key tile than 64 and 5-19 % less time in the 1K layers, head_dim 64 and narrow windows; at
+// the long 2K layers the same time, where the chip runs at its power limit.)
 //
 // Scores are produced transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: a lane then holds
 // 16 keys of ONE query (column = lane % 32), so the softmax row statistics are per-lane scalars
@@ -62,7 +63,7 @@ __device__ __forceinline__ float halves_sum(float x) {
 // LDS and its transposed operand comes from ds_read_b64_tr_b16.
 //
 // Software pipeline inside a wavefront: a wavefront issues in order, so the loop body is laid
-// out by hand as 8 * QB slots per 32-key half-step, each slot one MFMA (S^T of the next block, or
+// out by hand as 8 slots per 32-key half-step, each slot one MFMA (S^T of the next block, or
 // P V of the previous one) followed by the few vector instructions of the softmax of the block
 // in between, an LDS operand read or a DMA request; the vector work runs while the matrix core
 // is busy with the slot's MFMA.
@@ -137,10 +138,10 @@ __device__ __forceinline__ void copy_vectors(const AttnArgs& ca, int chunk, int 
     }
 }
 
-template <int D, int BM, int QB>                // BM: query rows per record
-__global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs a) {
-    constexpr int RW = 32 * QB;
-    constexpr int NW = BM / RW;             // wavefronts per workgroup; each owns 32*QB query rows
+template <int D, int BM>                        // BM: query rows per record
+__global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
+    constexpr int RW = 32;                  // query rows of a wavefront
+    constexpr int NW = BM / RW;             // wavefronts per workgroup
     constexpr int KS = D / 16;              // MFMA k-steps of S^T = K Q^T
     constexpr int DB = D / 32;              // 32-row blocks of O^T
     constexpr int CPR = D / 8;              // 16-byte chunks per K/V row
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // segment's tile p goes to stage (sb + p) % 4) and its query rows in the Q operand registers.
     // Requested ahead of time: for the first segment at once, for every other one by its predecessor,
     // between the end of its own key loop and its epilogue.
-    bf16x8 qf[QB][KS];
+    bf16x8 qf[KS];
     auto first_tiles = [&](const difa_segment_t& sg, int sb) __attribute__((always_inline)) {
         const int b = sg.bh / a.heads, h = sg.bh - b * a.heads;
         const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
@@ -302,15 +303,12 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         const int b = sg.bh / a.heads, h = sg.bh - b * a.heads;
         const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
         const __bf16* qg = (const __bf16*)a.q + base;
+        const int i_r = sg.q_tile * BM + wave * RW + l32;
+        const int i = i_r < N ? i_r : N - 1;            // rows past the end recompute row N-1
+        // B operand of S^T = K Q^T: column = query l32, k-slots 8*half..8*half+7 of each 16-wide step
+        const __bf16* qrow = qg + (int64_t)i * a.stride_n + 8 * half;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const int i_r = sg.q_tile * BM + wave * RW + 32 * qb + l32;
-            const int i = i_r < N ? i_r : N - 1;            // rows past the end recompute row N-1
-            // B operand of S^T = K Q^T: column = query l32, k-slots 8*half..8*half+7 of each 16-wide step
-            const __bf16* qrow = qg + (int64_t)i * a.stride_n + 8 * half;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *(const bf16x8*)(qrow + 16 * ks);
-        }
+        for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(qrow + 16 * ks);
     };
     auto first_loads = [&](const difa_segment_t& sg, int sb) __attribute__((always_inline)) {
         first_tiles(sg, sb);
@@ -405,20 +403,17 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     __bf16* __restrict__ og = (__bf16*)a.out + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
     const int row0 = it.q_tile * BM + wave * RW;           // first query row of this wavefront
 
-    // ---- per-lane query rows (two: one per 32-row block) and their allowed key ranges
-    RowState rs[QB];
-    int i_raw[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        i_raw[qb] = row0 + 32 * qb + l32;
-        const int i = i_raw[qb] < N ? i_raw[qb] : N - 1;
+    // ---- per-lane query row and its allowed key range
+    RowState rs;
+    const int i_raw = row0 + l32, i_row = i_raw < N ? i_raw : N - 1;
+    {
         int lo, hi;
-        if (it.window < 0 || (unsigned)(i - text_begin) < (unsigned)n_text) { lo = 0; hi = N - 1; }
-        else { lo = i - it.window; hi = i + it.window < N - 1 ? i + it.window : N - 1; }
-        rs[qb].lo = lo;
-        rs[qb].span = (unsigned)(hi - lo);                  // key j is in the band iff (unsigned)(j-lo) <= span
-        rs[qb].m = -1.0e30f;                                // finite: exp2(-inf - m) must be 0, not NaN
-        rs[qb].l = 0.f;
+        if (it.window < 0 || (unsigned)(i_row - text_begin) < (unsigned)n_text) { lo = 0; hi = N - 1; }
+        else { lo = i_row - it.window; hi = i_row + it.window < N - 1 ? i_row + it.window : N - 1; }
+        rs.lo = lo;
+        rs.span = (unsigned)(hi - lo);                      // key j is in the band iff (unsigned)(j-lo) <= span
+        rs.m = -1.0e30f;                                    // finite: exp2(-inf - m) must be 0, not NaN
+        rs.l = 0.f;
     }
 
     // A operand of the row sums.  P as it stands (lane l: query l % 32, keys of half l / 32) read as the B operand of a
@@ -432,13 +427,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 #pragma unroll
         for (int e = 0; e < 8; ++e) row_ones[e] = (__bf16)((((lane >> 4) ^ (lane >> 2)) & 1) || (lane & 3) ? 0.f : 1.f);
     }
-    floatx16 o[DB][QB];
+    floatx16 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[db][qb][r] = 0.f;
+        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
 
     // The segment covers positions [pos_begin, pos_end) of the record's visiting order; idx counts from
     // the segment's first position.
@@ -456,17 +449,14 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         return idx < n_iter ? (unsigned)tile_of(idx) * tile_bytes : 0x80000000u;
     };
 
-    // ---- S^T = K Q^T for one 32-key block jb of a tile: s[qb], register r = key 32*jb + 8*(r/4) + 4*half + r%4
-    auto qk_block = [&](int idx, int jb, floatx16 (&s)[QB]) {
+    // ---- S^T = K Q^T for one 32-key block jb of a tile: s, register r = key 32*jb + 8*(r/4) + 4*half + r%4
+    auto qk_block = [&](int idx, int jb, floatx16& s) {
         const __bf16* kst = BLK ? &Ksm[((2 * idx + jb + sbase) & 3) * TILE] : &Ksm[((idx + sbase) & 3) * TILE + 32 * jb * D];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const bf16x8 ka = *(const bf16x8*)(kst + koff[ks]);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if (ks == 0) mfma_s_first(s[qb], ka, qf[qb][ks]);
-                else mfma_s_acc(s[qb], ka, qf[qb][ks]);
-            }
+            if (ks == 0) mfma_s_first(s, ka, qf[ks]);
+            else mfma_s_acc(s, ka, qf[ks]);
         }
         mfma_results_visible();
     };
@@ -485,43 +475,40 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     const bool some_free = free_last >= free0, some_text = n_text >= 32;
     const int free_from = some_free ? free0 : -1, text_from = some_text ? text_begin : -1;   // (-1: no block begins there)
     const unsigned free_span = some_free ? (unsigned)(free_last - free0) : 0u, text_span = some_text ? (unsigned)(n_text - 32) : 0u;
-    auto mask_block = [&](int j0, floatx16 (&s)[QB]) {
+    auto mask_block = [&](int j0, floatx16& s) {
         if ((unsigned)(j0 - free_from) <= free_span || (unsigned)(j0 - text_from) <= text_span) return;
         const unsigned ninf = 0xff800000u;
+        // Bit r of `keep` says that register r holds the score of an allowed key.  Register r of a lane holds the key at
+        // offset 8*(r/4) + r%4 (+ 4*half) of the block, increasing with r, so the keys below some key are the lane's
+        // first k registers; the count k comes from that key with a handful of integer instructions.
+        auto below = [&](int key) {                                    // registers whose key is < key
+            const int e = key - j0 - 4 * half, ec = e < 0 ? 0 : (e > 32 ? 32 : e);
+            const int rem = ec & 7;
+            return (1u << (4 * (ec >> 3) + (rem < 4 ? rem : 4))) - 1u;
+        };
+        unsigned keep = below(rs.lo + (int)rs.span + 1) & ~below(rs.lo);
+        // text keys in the block (spelled out key by key this was 150 instructions, ten times in the kernel, and pushed the
+        // loop out of the instruction cache two compute units share)
+        if (j0 < img0 || j0 + 31 >= img1) keep |= below(text_begin + n_text) & ~below(text_begin);
+        // Each score then costs a signed one-bit extract (all ones or zero) and a bit-select between the score
+        // and -inf, in place.  No compare writes a lane mask that the next instruction would have to wait for
+        // (a compare and a select that reads its result cost 20 clocks a pair on this chip, four ordinary
+        // instructions 16), and the sixteen registers are not rebuilt elsewhere (a select per score into a
+        // fresh set of registers makes the compiler copy all sixteen over and back on every path through
+        // here, the one that changes nothing included).
+        // (one statement for the block's sixteen scores, written out so that the compiler neither turns
+        // the bit-select back into a compare and a select nor pads every score with a wait state)
+        float x[16];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            // Bit r of `keep` says that register r holds the score of an allowed key.  Register r of a lane holds the key at
-            // offset 8*(r/4) + r%4 (+ 4*half) of the block, increasing with r, so the keys below some key are the lane's
-            // first k registers; the count k comes from that key with a handful of integer instructions.
-            auto below = [&](int key) {                                    // registers whose key is < key
-                const int e = key - j0 - 4 * half, ec = e < 0 ? 0 : (e > 32 ? 32 : e);
-                const int rem = ec & 7;
-                return (1u << (4 * (ec >> 3) + (rem < 4 ? rem : 4))) - 1u;
-            };
-            unsigned keep = below(rs[qb].lo + (int)rs[qb].span + 1) & ~below(rs[qb].lo);
-            // text keys in the block (spelled out key by key this was 150 instructions, ten times in the kernel, and pushed the
-            // loop out of the instruction cache two compute units share)
-            if (j0 < img0 || j0 + 31 >= img1) keep |= below(text_begin + n_text) & ~below(text_begin);
-            // Each score then costs a signed one-bit extract (all ones or zero) and a bit-select between the score
-            // and -inf, in place.  No compare writes a lane mask that the next instruction would have to wait for
-            // (a compare and a select that reads its result cost 20 clocks a pair on this chip, four ordinary
-            // instructions 16), and the sixteen registers are not rebuilt elsewhere (a select per score into a
-            // fresh set of registers makes the compiler copy all sixteen over and back on every path through
-            // here, the one that changes nothing included).
-            // (one statement for the block's sixteen scores, written out so that the compiler neither turns
-            // the bit-select back into a compare and a select nor pads every score with a wait state)
-            float x[16];
+        for (int r = 0; r < 16; ++r) x[r] = s[r];
+        unsigned t0, t1;
+        asm volatile("v_bfe_i32 %16, %18, 0, 1\n\tv_bfe_i32 %17, %18, 1, 1\n\tv_bfi_b32 %0, %16, %0, %19\n\tv_bfi_b32 %1, %17, %1, %19\n\tv_bfe_i32 %16, %18, 2, 1\n\tv_bfe_i32 %17, %18, 3, 1\n\tv_bfi_b32 %2, %16, %2, %19\n\tv_bfi_b32 %3, %17, %3, %19\n\tv_bfe_i32 %16, %18, 4, 1\n\tv_bfe_i32 %17, %18, 5, 1\n\tv_bfi_b32 %4, %16, %4, %19\n\tv_bfi_b32 %5, %17, %5, %19\n\tv_bfe_i32 %16, %18, 6, 1\n\tv_bfe_i32 %17, %18, 7, 1\n\tv_bfi_b32 %6, %16, %6, %19\n\tv_bfi_b32 %7, %17, %7, %19\n\tv_bfe_i32 %16, %18, 8, 1\n\tv_bfe_i32 %17, %18, 9, 1\n\tv_bfi_b32 %8, %16, %8, %19\n\tv_bfi_b32 %9, %17, %9, %19\n\tv_bfe_i32 %16, %18, 10, 1\n\tv_bfe_i32 %17, %18, 11, 1\n\tv_bfi_b32 %10, %16, %10, %19\n\tv_bfi_b32 %11, %17, %11, %19\n\tv_bfe_i32 %16, %18, 12, 1\n\tv_bfe_i32 %17, %18, 13, 1\n\tv_bfi_b32 %12, %16, %12, %19\n\tv_bfi_b32 %13, %17, %13, %19\n\tv_bfe_i32 %16, %18, 14, 1\n\tv_bfe_i32 %17, %18, 15, 1\n\tv_bfi_b32 %14, %16, %14, %19\n\tv_bfi_b32 %15, %17, %15, %19"
+                     : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]),
+                       "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15]),
+                       "=&v"(t0), "=&v"(t1)
+                     : "v"(keep), "v"(ninf));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) x[r] = s[qb][r];
-            unsigned t0, t1;
-            asm volatile("v_bfe_i32 %16, %18, 0, 1\n\tv_bfe_i32 %17, %18, 1, 1\n\tv_bfi_b32 %0, %16, %0, %19\n\tv_bfi_b32 %1, %17, %1, %19\n\tv_bfe_i32 %16, %18, 2, 1\n\tv_bfe_i32 %17, %18, 3, 1\n\tv_bfi_b32 %2, %16, %2, %19\n\tv_bfi_b32 %3, %17, %3, %19\n\tv_bfe_i32 %16, %18, 4, 1\n\tv_bfe_i32 %17, %18, 5, 1\n\tv_bfi_b32 %4, %16, %4, %19\n\tv_bfi_b32 %5, %17, %5, %19\n\tv_bfe_i32 %16, %18, 6, 1\n\tv_bfe_i32 %17, %18, 7, 1\n\tv_bfi_b32 %6, %16, %6, %19\n\tv_bfi_b32 %7, %17, %7, %19\n\tv_bfe_i32 %16, %18, 8, 1\n\tv_bfe_i32 %17, %18, 9, 1\n\tv_bfi_b32 %8, %16, %8, %19\n\tv_bfi_b32 %9, %17, %9, %19\n\tv_bfe_i32 %16, %18, 10, 1\n\tv_bfe_i32 %17, %18, 11, 1\n\tv_bfi_b32 %10, %16, %10, %19\n\tv_bfi_b32 %11, %17, %11, %19\n\tv_bfe_i32 %16, %18, 12, 1\n\tv_bfe_i32 %17, %18, 13, 1\n\tv_bfi_b32 %12, %16, %12, %19\n\tv_bfi_b32 %13, %17, %13, %19\n\tv_bfe_i32 %16, %18, 14, 1\n\tv_bfe_i32 %17, %18, 15, 1\n\tv_bfi_b32 %14, %16, %14, %19\n\tv_bfi_b32 %15, %17, %15, %19"
-                         : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]),
-                           "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15]),
-                           "=&v"(t0), "=&v"(t1)
-                         : "v"(keep), "v"(ninf));
-#pragma unroll
-            for (int r = 0; r < 16; ++r) s[qb][r] = x[r];
-        }
+        for (int r = 0; r < 16; ++r) s[r] = x[r];
     };
     // ---- softmax of one 32-key block, cut into 16 pieces of six VALU instructions, one per slot, each
     // split in two halves that sit behind the slot's two MFMAs (a wavefront issues in order:
@@ -538,15 +525,15 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // Each piece ends in an empty volatile asm on its results: that keeps it in its slot (otherwise the
     // optimizer sinks the arithmetic to the block that uses it).
     auto pin = [](float& x) { asm volatile("" : "+v"(x)); };
-    auto softmax_a = [&](int s, const floatx16 (&sc)[QB], const float (&mneg)[QB], float (&x)[2]) __attribute__((always_inline)) {
-        const int qb = s >> 3, r = 2 * (s & 7);
-        x[0] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r], c, mneg[qb]));
-        x[1] = fmaf(sc[qb][r + 1], c, mneg[qb]);
+    auto softmax_a = [&](int s, const floatx16& sc, float mneg, float (&x)[2]) __attribute__((always_inline)) {
+        const int r = 2 * s;
+        x[0] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, mneg));
+        x[1] = fmaf(sc[r + 1], c, mneg);
         pin(x[0]);
         pin(x[1]);
     };
-    auto convert = [&](int s, const float (&x)[2], bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
-        const int qb = s >> 3, r = 2 * (s & 7);
+    auto convert = [&](int s, const float (&x)[2], bf16x8 (&pw)[2]) __attribute__((always_inline)) {
+        const int r = 2 * s;
         floatx2 pf;
         pf[0] = x[0];
         pf[1] = x[1];
@@ -554,8 +541,8 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         unsigned bits = __builtin_bit_cast(unsigned, pr);
         asm volatile("" : "+v"(bits));
         pr = __builtin_bit_cast(bf16x2, bits);
-        pw[qb][r >> 3][r & 7] = pr[0];
-        pw[qb][r >> 3][(r & 7) + 1] = pr[1];
+        pw[r >> 3][r & 7] = pr[0];
+        pw[r >> 3][(r & 7) + 1] = pr[1];
     };
     // Sum of a row's weights in a block from that row's lanes alone (rare paths: see sum_weights for the others).
     auto own_sum = [&](const bf16x8 (&pw)[2]) __attribute__((always_inline)) {
@@ -578,42 +565,36 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // reference; the block's weights and row sums are recomputed, the running sums and O are scaled.
     // The accumulators live in accumulation registers and are scaled in place there; the waits cover
     // MFMA results still in flight.
-    auto renormalise = [&](const floatx16 (&sc)[QB], float (&lb)[QB], bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
-        float alpha[QB];
+    auto renormalise = [&](const floatx16& sc, float& lb, bf16x8 (&pw)[2]) __attribute__((always_inline)) {
+        float tmax = -INFINITY;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float tmax = -INFINITY;
+        for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sc[r]);
+        const float t = halves_max(tmax) * c;
+        const float m_old = rs.m;
+        const float m_new = t > m_old + kBump ? t : m_old;
+        const float alpha = __builtin_amdgcn_exp2f(m_old - m_new);
+        rs.m = m_new;
+        rs.l *= alpha;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, sc[qb][r]);
-            const float t = halves_max(tmax) * c;
-            const float m_old = rs[qb].m;
-            const float m_new = t > m_old + kBump ? t : m_old;
-            alpha[qb] = __builtin_amdgcn_exp2f(m_old - m_new);
-            rs[qb].m = m_new;
-            rs[qb].l *= alpha[qb];
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                floatx2 pf;
-                pf[0] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r], c, -m_new));
-                pf[1] = __builtin_amdgcn_exp2f(fmaf(sc[qb][r + 1], c, -m_new));
-                const bf16x2 pr = __builtin_convertvector(pf, bf16x2);
-                pw[qb][r >> 3][r & 7] = pr[0];
-                pw[qb][r >> 3][(r & 7) + 1] = pr[1];
-            }
-            lb[qb] = own_sum(pw[qb]);
+        for (int r = 0; r < 16; r += 2) {
+            floatx2 pf;
+            pf[0] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, -m_new));
+            pf[1] = __builtin_amdgcn_exp2f(fmaf(sc[r + 1], c, -m_new));
+            const bf16x2 pr = __builtin_convertvector(pf, bf16x2);
+            pw[r >> 3][r & 7] = pr[0];
+            pw[r >> 3][(r & 7) + 1] = pr[1];
         }
+        lb = own_sum(pw);
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float e = o[db][qb][r], t;
-                    asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
-                                 : "+a"(e), "=&v"(t) : "v"(alpha[qb]));
-                    o[db][qb][r] = e;
-                }
+            for (int r = 0; r < 16; ++r) {
+                float e = o[db][r], t;
+                asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                             : "+a"(e), "=&v"(t) : "v"(alpha));
+                o[db][r] = e;
+            }
         asm volatile("s_nop 7" ::: "memory");
     };
     // ---- O^T += V^T P^T: k-slot e of a lane is key 32*jb + 16*tt + 4*half + (e<4 ? e : e+4)
@@ -632,14 +613,12 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // ordinary registers, this is where it has to move them over: a vector write needs two wait states
     // before a matrix instruction reads it, and only here are those guaranteed.
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qf[qb][ks]));
+    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+a"(qf[ks]));
     asm volatile("s_nop 1" ::: "memory");
     __syncthreads();
 
     // The pipeline advances by 32-key blocks g = 2*tile + jb.  One half-step for block g is one basic
-    // block of 8 * QB slots; slot s issues
+    // block of 8 slots; slot s issues
     //     MFMA s of S^T of block g+1   | two pieces of the softmax of block g |   MFMA s of P V of block g-1
     // so that consecutive MFMAs never depend on each other and every MFMA has a few VALU
     // instructions behind it.  LDS operands are fetched three operands ahead, across half-step
@@ -647,20 +626,18 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // factors the softmax just produced (after P V of block g-1, before P V of block g) and the
     // element mask of the scores of block g+1.  In the last iteration block g+1 is a reload of the
     // last tile whose scores are never used.
-    constexpr int NOP = D / 16;             // LDS operands per MFMA stream per half-step: 8 at D=128, 4 at D=64
-    constexpr int NMF = QB * NOP;           // MFMAs per stream per half-step
-    constexpr int NSLOT = 8 * QB;           // slots per half-step: one per pair of scores of a lane
+    constexpr int NOP = D / 16;             // MFMAs, and LDS operands, per stream and half-step: 8 at D=128, 4 at D=64
+    constexpr int NSLOT = 8;                // slots per half-step: one per pair of scores of a lane
     constexpr int AHEAD = 3;                // operands in flight per stream
     // head_dim 64 has half as many MFMAs as slots would take: S^T in the first four slots, P V in the last four (both in the
     // first four: 7 % more clocks), and a pair of weights is converted one slot after its exponentials, whose result the
     // conversion may not read in the very next instruction (at head_dim 128 the same costs 2 %: the MFMAs set the pace there and a
     // slot gets longer by the conversion).  With both SD3-like 1K 141.9 -> 139.3 us, 2K 1426 -> 1406, 512 px refresh 85.2 -> 84.1.
-    constexpr int PV0 = NSLOT - NMF;        // slot of the first P V MFMA
+    constexpr int PV0 = NSLOT - NOP;        // slot of the first P V MFMA
     constexpr int kLag = D == 64 ? 1 : 0;
-    static_assert(QB == 1 || kLag == 0, "a pair's slot and the next one belong to the same row block");
     static_assert(NOP == 8 || NOP == 4, "slot layout assumes head_dim 128 or 64");
-    floatx16 s0[QB], s1[QB];                  // scores of the even / odd block in flight
-    bf16x8 pa[QB][2], pb[QB][2];              // weights of the even / odd block in flight
+    floatx16 s0, s1;                        // scores of the even / odd block in flight
+    bf16x8 pa[2], pb[2];                    // weights of the even / odd block in flight
     bf16x8 kq[NOP], vq[NOP];                // LDS operands (entry j = operand j of the stream)
 
     // Row sums of a block's weights (the rounded ones, which are what P V multiplies), by the matrix core: two 16x16x32
@@ -671,71 +648,56 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // other inputs), video-like 1349 -> 1270 (1353 -> 1307), mixed 1021 -> 969, FLUX-like 1K 127.8 -> 122.0 (130.0 -> 126.3);
     // head_dim 64 within 0.5 %.  (v_add on the unrounded weights costs the same and is less exact: 2.0e-3 of
     // the result's norm off instead of 1.75e-3 where few keys carry a row.)
-    floatx4 wsum[QB];
-    auto sum_weights = [&](int qb, int tt, const bf16x8 (&pw)[QB][2]) __attribute__((always_inline)) {
-        wsum[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pw[qb][tt], tt ? wsum[qb] : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    floatx4 wsum;
+    auto sum_weights = [&](int tt, const bf16x8 (&pw)[2]) __attribute__((always_inline)) {
+        wsum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(row_ones, pw[tt], tt ? wsum : floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
     };
     // Closes a block: its row sums are checked (see renormalise) and added to the rows' running sums.
-    auto settle = [&](const floatx16 (&sc)[QB], bf16x8 (&pw)[QB][2], bool first) __attribute__((always_inline)) {
-        float lb[QB];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            lb[qb] = wsum[qb][0];
-            pin(lb[qb]);                    // (read here, whatever follows)
-        }
+    auto settle = [&](const floatx16& sc, bf16x8 (&pw)[2], bool first) __attribute__((always_inline)) {
+        float lb = wsum[0];
+        pin(lb);                            // (read here, whatever follows)
         // compared as integers: a row beside one with an infinite weight has the sum NaN (0 x inf), which has to count as large
-        unsigned top = __builtin_bit_cast(unsigned, lb[0]);
-        if (QB > 1) top = top > __builtin_bit_cast(unsigned, lb[QB - 1]) ? top : __builtin_bit_cast(unsigned, lb[QB - 1]);
-        const bool large = __builtin_amdgcn_ballot_w64(top > __builtin_bit_cast(unsigned, kTrip)) != 0;
+        const bool large = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(unsigned, lb) > __builtin_bit_cast(unsigned, kTrip)) != 0;
         if (first) {                        // the weights are at most 1, or NaN: a row of Q that is not finite, which stays with its own row
-            if (__builtin_expect(large, 0))
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) lb[qb] = own_sum(pw[qb]);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) rs[qb].l = lb[qb];
+            if (__builtin_expect(large, 0)) lb = own_sum(pw);
+            rs.l = lb;
             return;
         }
         if (__builtin_expect(large, 0)) renormalise(sc, lb, pw);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) rs[qb].l += lb[qb];
+        rs.l += lb;
     };
-    auto half_step = [&](const floatx16 (&s_cur)[QB], floatx16 (&s_nxt)[QB], const bf16x8 (&p_prev)[QB][2],
-                         bf16x8 (&p_cur)[QB][2], const __bf16* kst_nxt, const __bf16* kst_after,
+    auto half_step = [&](const floatx16& s_cur, floatx16& s_nxt, const bf16x8 (&p_prev)[2],
+                         bf16x8 (&p_cur)[2], const __bf16* kst_nxt, const __bf16* kst_after,
                          const __bf16* vst_prev, const __bf16* vst_cur, bool with_pv, bool mask_nxt,
                          int blk_nxt, int dma_tensor, unsigned dma_tb, unsigned dma_dst,
                          unsigned dma_tb2 = 0, unsigned dma_dst2 = 0) __attribute__((always_inline)) {
-        float mneg[QB], xs[2][2];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) mneg[qb] = -rs[qb].m;
+        const float mneg = -rs.m;
+        float xs[2][2];
 #pragma unroll
         for (int s = 0; s < NSLOT; ++s) {
-            const int j = s / QB, qb = s % QB, jn = j + AHEAD;    // operand jn is fetched while operand j is used
+            const int jn = s + AHEAD;              // operand jn is fetched while operand s is used
             float (&x)[2] = xs[s & 1];
-            if (s < NMF) {
-                if (j == 0) mfma_s_first(s_nxt[qb], kq[j], qf[qb][j]);
-                else mfma_s_acc(s_nxt[qb], kq[j], qf[qb][j]);
-                if (qb == 0) {
-                    if (jn < NOP) kq[jn] = k_operand(kst_nxt, jn);
-                    else kq[jn - NOP] = k_operand(kst_after, jn - NOP);
-                }
+            if (s < NOP) {
+                if (s == 0) mfma_s_first(s_nxt, kq[s], qf[s]);
+                else mfma_s_acc(s_nxt, kq[s], qf[s]);
+                if (jn < NOP) kq[jn] = k_operand(kst_nxt, jn);
+                else kq[jn - NOP] = k_operand(kst_after, jn - NOP);
             }
             softmax_a(s, s_cur, mneg, x);
             __builtin_amdgcn_sched_barrier(0);
-            if (s >= PV0 && s < PV0 + NMF) {
-                const int i = j - PV0, in = i + AHEAD;
+            if (s >= PV0) {
+                const int i = s - PV0, in = i + AHEAD;
                 if (with_pv)
-                    o[i >> 1][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[i], p_prev[qb][i & 1], o[i >> 1][qb], 0, 0, 0);
-                if (qb == 0) {
-                    if (in < NOP) { if (with_pv) vq[in] = v_operand(vst_prev, in); }
-                    else vq[in - NOP] = v_operand(vst_cur, in - NOP);
-                }
+                    o[i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[i], p_prev[i & 1], o[i >> 1], 0, 0, 0);
+                if (in < NOP) { if (with_pv) vq[in] = v_operand(vst_prev, in); }
+                else vq[in - NOP] = v_operand(vst_cur, in - NOP);
             }
             x[1] = __builtin_amdgcn_exp2f(x[1]);
             pin(x[1]);
             if (s >= kLag) convert(s - kLag, xs[(s - kLag) & 1], p_cur);
-            if ((s & 7) == 5 + kLag) sum_weights(qb, 0, p_cur);
+            if (s == 5 + kLag) sum_weights(0, p_cur);
             if (kLag && s == NSLOT - 1) convert(s, x, p_cur);
-            if ((s & 7) == 7) sum_weights(qb, 1, p_cur);
+            if (s == NSLOT - 1) sum_weights(1, p_cur);
             // the loads of a later tile are spread over the slots (a burst of them right after the
             // barrier stalls all wavefronts on the one memory pipe)
             if ((s & 3) == 1 && (s >> 2) < NDMA) dma_part(dma_tensor, s >> 2, dma_tb, dma_dst);
@@ -748,8 +710,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         // decisions about each edge of the band and a branch for each cost the SD3-like 512 px refresh 85.5 us instead of 82,
         // the 1K layer 138.3 instead of 134.5.)
         if (__builtin_expect(mask_nxt, 0)) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) settled_results(s_nxt[qb]);
+            settled_results(s_nxt);
             mask_block(tile_of(blk_nxt >> 1) * kBN + 32 * (blk_nxt & 1), s_nxt);
         }
     };
@@ -760,12 +721,11 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     // The rows' references: the maximum of the first block (a row that sees nothing of it keeps the initial one).  Left to
     // renormalise(), which finds it only after the block's weights have come out infinite, every segment paid for a second
     // set of weights: SD3-like 1K layer 141.8 us against 140.5, 2K 1457 / 1447, FLUX-like 2K mixed 981 / 974.
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
+    {
         float top = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) top = fmaxf(top, s0[qb][r]);
-        rs[qb].m = fmaxf(rs[qb].m, halves_max(top) * c);
+        for (int r = 0; r < 16; ++r) top = fmaxf(top, s0[r]);
+        rs.m = fmaxf(rs.m, halves_max(top) * c);
     }
 
     if constexpr (BLK) __syncthreads();     // block 0 has been read by everyone: its stage takes block 4
@@ -800,7 +760,7 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
     } else {
     half_step(s0, s1, pb, pa, kptr(k_cur, 1), kptr(k_nxt, 0), vptr(v_cur, 0), vptr(v_cur, 0), false,
               msk_cur, 1, 0, tb_k, k_lds + (unsigned)(k_ld * 2) + wave_lds);
-    if (QB == 1) mfma_results_visible();    // no P V MFMA separated this block's last S^T MFMA from its first reader
+    mfma_results_visible();    // no P V MFMA separated this block's last S^T MFMA from its first reader
     half_step(s1, s0, pa, pb, kptr(k_nxt, 0), kptr(k_nxt, 1), vptr(v_cur, 0), vptr(v_cur, 1), true,
               msk_nxt, 2, 1, tb_v, v_lds + (unsigned)(v_ld * 2) + wave_lds);
     }
@@ -895,16 +855,12 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
 #pragma unroll
         for (int i = 0; i < NOP; ++i) {
             if (i + AHEAD < NOP) vq[i + AHEAD] = v_operand(vst, i + AHEAD);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-                o[i >> 1][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[i], pb[qb][i & 1], o[i >> 1][qb], 0, 0, 0);
+            o[i >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vq[i], pb[i & 1], o[i >> 1], 0, 0, 0);
         }
     }
 
     // ---- epilogue: O^T register r of block db is feature d = 32*db + 8*(r/4) + 4*half + r%4
-    float l_fin[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) l_fin[qb] = rs[qb].l;
+    float l_fin = rs.l;
     bool writes_rows = it.part_slot < 0;
     if (it.part_slot >= 0) {
         // A piece of a cut record.  Its unnormalised fp32 accumulators, row reference (log2 domain) and row
@@ -919,29 +875,26 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         // whole L2, the K/V tiles its workgroups share included.
         const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(a.part_o, 0, 0x7fffffff, 0x00020000);
         const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(a.part_ml, 0, 0x7fffffff, 0x00020000);
-        auto slot_bytes = [&](int slot, int qb) { return ((slot * NW + (int)wave_u) * QB + qb) * (32 * D * 4); };
+        auto slot_bytes = [&](int slot) { return (slot * NW + (int)wave_u) * (32 * D * 4); };
         // A slot holds the accumulators in the order of the registers, 1 KiB per wavefront and store: the piece
         // that folds it in has them in the same registers, so no other order is ever needed.
         const int slot_lane = (half * 32 + l32) * 16;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int g = 0; g < 4; ++g) {
+                floatx4 w4;
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    floatx4 w4;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w4[e] = o[db][qb][4 * g + e];
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, w4), ro, slot_lane + 1024 * (4 * db + g),
-                                                           slot_bytes(it.part_slot, qb), kDeviceCoherent);
-                }
-            if (half == 0) {
-                floatx2 ml;
-                ml[0] = rs[qb].m;
-                ml[1] = l_fin[qb];
-                const int rl = it.part_slot * BM + wave * RW + 32 * qb + l32;       // row inside the scratch
-                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, ml), rm, rl * 8, 0, kDeviceCoherent);
+                for (int e = 0; e < 4; ++e) w4[e] = o[db][4 * g + e];
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, w4), ro, slot_lane + 1024 * (4 * db + g),
+                                                       slot_bytes(it.part_slot), kDeviceCoherent);
             }
+        if (half == 0) {
+            floatx2 ml;
+            ml[0] = rs.m;
+            ml[1] = l_fin;
+            const int rl = it.part_slot * BM + wave * RW + l32;       // row inside the scratch
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, ml), rm, rl * 8, 0, kDeviceCoherent);
         }
         // The slot has to be written before the ticket is taken.  The next segment's query rows and first
         // tiles are requested behind the slot stores, and the tiles are not waited for: memory operations
@@ -965,30 +918,27 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
             for (int p = 0; p < it.n_parts; ++p) {
                 const int slot = it.first_slot + p;
                 if (slot == it.part_slot) continue;
+                const int rl = slot * BM + wave * RW + l32;
+                // (whole vectors are reinterpreted: a bit_cast applied to one vector element reads element 0)
+                const floatx2 ml = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rm, rl * 8, 0, kDeviceCoherent));
+                floatx4 x[DB][4];
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    const int rl = slot * BM + wave * RW + 32 * qb + l32;
-                    // (whole vectors are reinterpreted: a bit_cast applied to one vector element reads element 0)
-                    const floatx2 ml = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rm, rl * 8, 0, kDeviceCoherent));
-                    floatx4 x[DB][4];
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db)
+                    for (int g = 0; g < 4; ++g)
+                        x[db][g] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
+                            ro, slot_lane + 1024 * (4 * db + g), slot_bytes(slot), kDeviceCoherent));
+                const float m_new = fmaxf(rs.m, ml[0]);
+                const float w_mine = __builtin_amdgcn_exp2f(rs.m - m_new), w_other = __builtin_amdgcn_exp2f(ml[0] - m_new);
+                rs.m = m_new;
+                l_fin = fmaf(ml[1], w_other, l_fin * w_mine);
 #pragma unroll
-                        for (int g = 0; g < 4; ++g)
-                            x[db][g] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                ro, slot_lane + 1024 * (4 * db + g), slot_bytes(slot, qb), kDeviceCoherent));
-                    const float m_new = fmaxf(rs[qb].m, ml[0]);
-                    const float w_mine = __builtin_amdgcn_exp2f(rs[qb].m - m_new), w_other = __builtin_amdgcn_exp2f(ml[0] - m_new);
-                    rs[qb].m = m_new;
-                    l_fin[qb] = fmaf(ml[1], w_other, l_fin[qb] * w_mine);
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int db = 0; db < DB; ++db)
+                    for (int g = 0; g < 4; ++g)
 #pragma unroll
-                        for (int g = 0; g < 4; ++g)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                o[db][qb][4 * g + e] = fmaf(x[db][g][e], w_other, o[db][qb][4 * g + e] * w_mine);
-                }
+                        for (int e = 0; e < 4; ++e)
+                            o[db][4 * g + e] = fmaf(x[db][g][e], w_other, o[db][4 * g + e] * w_mine);
             }
             if (tid == 0) atomicExch(cold_args()->tickets + it.merge_idx, 0);
             writes_rows = true;
@@ -1000,53 +950,50 @@ __global__ __launch_bounds__(2 * BM / QB, 2 / QB) void attn_bf16_kernel(AttnArgs
         // features 8g..8g+7 and the upper half 8(g+1)..8(g+1)+7: 16-byte stores, half as many of them (with
         // the next segment's loads already in flight, more memory instructions than the 63 the counter
         // can track would stall the wavefront until loads return).
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            float inv = 1.0f / l_fin[qb];
-            const int64_t row_off = (int64_t)(i_raw[qb] < N ? i_raw[qb] : N - 1) * a.stride_n;
-            __bf16* orow = og + row_off;
-            if (it.flags & DIFA_ITEM_ADD_RESIDUAL) {
-                // arrow attention with residual sharing: the head's kept difference is added to the
-                // normalised result before it is rounded (the lane's features: four in a row per (db, g))
-                const __bf16* rrow = (const __bf16*)cold_args()->residual + (og - (__bf16*)a.out) + row_off;
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const bf16x4 rv = *(const bf16x4*)(rrow + 32 * db + 8 * g + 4 * half);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            o[db][qb][4 * g + e] = fmaf(o[db][qb][4 * g + e], inv, (float)rv[e]);
-                    }
-                inv = 1.0f;
-            }
+        float inv = 1.0f / l_fin;
+        const int64_t row_off = (int64_t)(i_raw < N ? i_raw : N - 1) * a.stride_n;
+        __bf16* orow = og + row_off;
+        if (it.flags & DIFA_ITEM_ADD_RESIDUAL) {
+            // arrow attention with residual sharing: the head's kept difference is added to the
+            // normalised result before it is rounded (the lane's features: four in a row per (db, g))
+            const __bf16* rrow = (const __bf16*)cold_args()->residual + (og - (__bf16*)a.out) + row_off;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int gp = 0; gp < 2; ++gp) {
-                    unsigned w[2][2];                        // [g - 2*gp][pair of features]
+                for (int g = 0; g < 4; ++g) {
+                    const bf16x4 rv = *(const bf16x4*)(rrow + 32 * db + 8 * g + 4 * half);
 #pragma unroll
-                    for (int gg = 0; gg < 2; ++gg)
+                    for (int e = 0; e < 4; ++e)
+                        o[db][4 * g + e] = fmaf(o[db][4 * g + e], inv, (float)rv[e]);
+                }
+            inv = 1.0f;
+        }
 #pragma unroll
-                        for (int e2 = 0; e2 < 2; ++e2) {
-                            floatx2 f;
-                            f[0] = o[db][qb][4 * (2 * gp + gg) + 2 * e2] * inv;
-                            f[1] = o[db][qb][4 * (2 * gp + gg) + 2 * e2 + 1] * inv;
-                            w[gg][e2] = __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
-                        }
-                    uintx4 q4;
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int gp = 0; gp < 2; ++gp) {
+                unsigned w[2][2];                        // [g - 2*gp][pair of features]
+#pragma unroll
+                for (int gg = 0; gg < 2; ++gg)
 #pragma unroll
                     for (int e2 = 0; e2 < 2; ++e2) {
-                        // lower half keeps its quad of g and receives the upper half's; the upper half receives
-                        // the lower half's quad of g+1 and keeps its own
-                        const auto r = __builtin_amdgcn_permlane32_swap(w[0][e2], w[1][e2], false, false);
-                        const unsigned first = r[0], second = r[1];
-                        q4[e2] = first;
-                        q4[2 + e2] = second;
+                        floatx2 f;
+                        f[0] = o[db][4 * (2 * gp + gg) + 2 * e2] * inv;
+                        f[1] = o[db][4 * (2 * gp + gg) + 2 * e2 + 1] * inv;
+                        w[gg][e2] = __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2));
                     }
-                    if (i_raw[qb] < N) *(uintx4*)(orow + 32 * db + 16 * gp + 8 * half) = q4;
+                uintx4 q4;
+#pragma unroll
+                for (int e2 = 0; e2 < 2; ++e2) {
+                    // lower half keeps its quad of g and receives the upper half's; the upper half receives
+                    // the lower half's quad of g+1 and keeps its own
+                    const auto r = __builtin_amdgcn_permlane32_swap(w[0][e2], w[1][e2], false, false);
+                    const unsigned first = r[0], second = r[1];
+                    q4[e2] = first;
+                    q4[2 + e2] = second;
                 }
-        }
+                if (i_raw < N) *(uintx4*)(orow + 32 * db + 16 * gp + 8 * half) = q4;
+            }
     }
     sbase = sbase_next;
     // one chunk of the cached-head copy, while the next segment's first tiles are on their way
@@ -1107,20 +1054,12 @@ float* static_scratch(int device, size_t* bytes) {
     return g_scratch_ptr[device];
 }
 
-// 32-row blocks per wavefront (the kernel's QB).  1: eight wavefronts per workgroup, two per SIMD, so that
-// one wavefront's softmax arithmetic runs while the other's MFMA occupies the matrix core; 2: four
-// wavefronts, one per SIMD, each LDS operand read feeding two MFMAs.  Measured on one MI355X, 1 against 2:
-// 16 % fewer clocks per key tile, and at the 1K layers, head_dim 64 and narrow windows 5-19 % less time;
-// at the long 2K layers the time is the same, because there the chip runs at its power limit and
-// lowers its clock by as much as the schedule got tighter.
-constexpr int kRowBlocks = 1;
-
 hipError_t launch_attn_bf16(const AttnArgs& a, int head_dim, int rows, int n_wg, hipStream_t stream) {
     if (n_wg <= 0) return hipSuccess;
-    const dim3 grid(n_wg), threads(2 * rows / kRowBlocks);
-    if (head_dim == 128 && rows == kRowsLong) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsLong, kRowBlocks>), grid, threads, 0, stream, a);
-    else if (head_dim == 128 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsShort, kRowBlocks>), grid, threads, 0, stream, a);
-    else if (head_dim == 64 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<64, kRowsShort, kRowBlocks>), grid, threads, 0, stream, a);
+    const dim3 grid(n_wg), threads(2 * rows);
+    if (head_dim == 128 && rows == kRowsLong) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsLong>), grid, threads, 0, stream, a);
+    else if (head_dim == 128 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<128, kRowsShort>), grid, threads, 0, stream, a);
+    else if (head_dim == 64 && rows == kRowsShort) hipLaunchKernelGGL((attn_bf16_kernel<64, kRowsShort>), grid, threads, 0, stream, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
