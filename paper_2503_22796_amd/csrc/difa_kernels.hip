@@ -86,15 +86,16 @@ __device__ __forceinline__ bf16x4 lds_read_tr16(const __bf16* p) {
 // compiler's own choice for a kernel this size is accumulation registers plus one copy per score),
 // and the Q operand sits in accumulation registers, which only matrix instructions read.
 // The hardware does not interlock a vector instruction that reads a matrix result too early and the
-// compiler does not see through the assembly, so every reader is either a full half-step away or
-// preceded by an explicit wait (mfma_results_visible).
+// compiler does not see through the assembly, so every reader is a full half-step away, preceded by an explicit wait
+// (mfma_results_visible, tied to the registers: a wait that names only memory holds back no read of a register), or behind the read
+// of a younger matrix instruction's result, one that the compiler knows about and waits for (settled_results).
 __device__ __forceinline__ void mfma_s_first(floatx16& d, const bf16x8& k, const bf16x8& q) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(k), "a"(q));
 }
 __device__ __forceinline__ void mfma_s_acc(floatx16& d, const bf16x8& k, const bf16x8& q) {
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(k), "a"(q));
 }
-__device__ __forceinline__ void mfma_results_visible() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+__device__ __forceinline__ void mfma_results_visible(floatx16& d) { asm volatile("s_nop 15\n\ts_nop 15" : "+v"(d) :: "memory"); }
 // No wait, only the order: for results of an MFMA that a younger MFMA's result has already been read behind.  (The matrix
 // pipe works in order.)
 __device__ __forceinline__ void settled_results(floatx16& d) { asm volatile("" : "+v"(d) :: "memory"); }
@@ -460,7 +461,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
             if (ks == 0) mfma_s_first(s, ka, qf[ks]);
             else mfma_s_acc(s, ka, qf[ks]);
         }
-        mfma_results_visible();
+        mfma_results_visible(s);
     };
     // Element mask of one 32-key block whose first key is j0.  The host marks a tile as masked when any
     // of the record's rows has a forbidden key in it; for the rows of one wavefront most such
@@ -755,14 +756,14 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
     if constexpr (BLK) {
         half_step(s0, s1, pb, pa, kptr(stage(1), 0), kptr(stage(2), 0), vptr(stage(0), 0), vptr(stage(0), 0), false, msk_cur, 1,
                   0, tb_k, dst(k_lds, stage(4)), tb_v, dst(v_lds, stage(2)));
-        mfma_results_visible();
+        mfma_results_visible(s1);
         __syncthreads();
         half_step(s1, s0, pa, pb, kptr(stage(2), 0), kptr(stage(3), 0), vptr(stage(0), 0), vptr(stage(1), 0), true, msk_nxt, 2,
                   0, tb_k + half_tile, dst(k_lds, stage(5)), tb_v + half_tile, dst(v_lds, stage(3)));
     } else {
     half_step(s0, s1, pb, pa, kptr(k_cur, 1), kptr(k_nxt, 0), vptr(v_cur, 0), vptr(v_cur, 0), false,
               msk_cur, 1, 0, tb_k, k_lds + (unsigned)(k_ld * 2) + wave_lds);
-    mfma_results_visible();    // no P V MFMA separated this block's last S^T MFMA from its first reader
+    mfma_results_visible(s1);  // no P V MFMA separated this block's last S^T MFMA from its first reader
     half_step(s1, s0, pa, pb, kptr(k_nxt, 0), kptr(k_nxt, 1), vptr(v_cur, 0), vptr(v_cur, 1), true,
               msk_nxt, 2, 1, tb_v, v_lds + (unsigned)(v_ld * 2) + wave_lds);
     }
