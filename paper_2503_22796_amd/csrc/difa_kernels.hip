@@ -208,9 +208,11 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
     constexpr int NDMA = RKEYS / RPI / NW;                     // load instructions per wavefront, tensor and tile
     const unsigned head_bytes = (unsigned)(((int64_t)(N - 1) * a.stride_n + D) * 2);
     uintx4 krsrc, vrsrc;                                    // descriptors of the head whose tiles are being loaded
-    // (This wavefront's number as a scalar, everywhere: products of a vector one, held from segment to segment, came to 28 bytes of
-    // scratch a lane in the 256-row kernel, with a reload in each segment's first half-step that waited for every load in flight.)
+    // (Products of the vector form of the wavefront's number, held from segment to segment, came to 28 bytes of scratch a lane in the
+    // 256-row kernel, with a reload in each segment's first half-step that waited for every load in flight.  The scalar
+    // form in the others as well: the SD3-like 512 px refresh 79.7 us instead of 79.2.)
     const unsigned wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = BM == kRowsLong ? (int)wave_u : tid >> 6;
     unsigned gk[NDMA], gv[NDMA];                            // per-lane byte offsets inside a tile
     // These sixteen-odd registers are derived from the lane number again at the start of every segment,
     // through a copy the compiler cannot see through.  Held for the whole kernel instead, they would be
@@ -232,7 +234,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < NDMA; ++u) {
-            const int r = ((int)wave_u * NDMA + u) * RPI + lane / CPR, pc = lane % CPR;   // tile row, chunk slot in LDS
+            const int r = (wave * NDMA + u) * RPI + lane / CPR, pc = lane % CPR;   // tile row, chunk slot in LDS
             gk[u] = (unsigned)(r * (int)a.stride_n + 8 * (pc ^ kswz(r))) * 2u;
             gv[u] = (unsigned)(r * (int)a.stride_n + 8 * (pc ^ vswz(r))) * 2u;
         }
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
         const int b = sg.bh / a.heads, h = sg.bh - b * a.heads;
         const int64_t base = (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
         const __bf16* qg = (const __bf16*)a.q + base;
-        const int i_r = sg.q_tile * BM + (int)wave_u * RW + l32;
+        const int i_r = sg.q_tile * BM + wave * RW + l32;
         const int i = i_r < N ? i_r : N - 1;            // rows past the end recompute row N-1
         // B operand of S^T = K Q^T: column = query l32, k-slots 8*half..8*half+7 of each 16-wide step
         const __bf16* qrow = qg + (int64_t)i * a.stride_n + 8 * half;
@@ -404,7 +406,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
 
     const int b = it.bh / a.heads, h = it.bh - b * a.heads;
     __bf16* __restrict__ og = (__bf16*)a.out + (int64_t)b * a.stride_b + (int64_t)h * a.stride_h;
-    const int row0 = it.q_tile * BM + (int)wave_u * RW;           // first query row of this wavefront
+    const int row0 = it.q_tile * BM + wave * RW;           // first query row of this wavefront
 
     // ---- per-lane query row and its allowed key range
     RowState rs;
@@ -896,7 +898,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
             floatx2 ml;
             ml[0] = rs.m;
             ml[1] = l_fin;
-            const int rl = it.part_slot * BM + (int)wave_u * RW + l32;       // row inside the scratch
+            const int rl = it.part_slot * BM + wave * RW + l32;       // row inside the scratch
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, ml), rm, rl * 8, 0, kDeviceCoherent);
         }
         // The slot has to be written before the ticket is taken.  The next segment's query rows and first
@@ -921,7 +923,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
             for (int p = 0; p < it.n_parts; ++p) {
                 const int slot = it.first_slot + p;
                 if (slot == it.part_slot) continue;
-                const int rl = slot * BM + (int)wave_u * RW + l32;
+                const int rl = slot * BM + wave * RW + l32;
                 // (whole vectors are reinterpreted: a bit_cast applied to one vector element reads element 0)
                 const floatx2 ml = __builtin_bit_cast(floatx2, __builtin_amdgcn_raw_buffer_load_b64(rm, rl * 8, 0, kDeviceCoherent));
                 floatx4 x[DB][4];
