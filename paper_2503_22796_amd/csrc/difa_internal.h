@@ -31,6 +31,9 @@ constexpr int kBN = 64;   // keys per K/V tile
 //                         8 + 16 at 9216 (1.7 %) 454 / 440; 4 + 20 at 16896 (1.8 %) 991 / 959; mixed 2K (1.2 %) 958 / 964
 //   all arrow             16896 tokens, w = 4224 (1.3 %, 14.6 M pairs a compute unit) 1404 / 1408, 2112 (2.3 %) 883 / 858,
 //                         528 (5.3 %) 458 / 424; pairs of them, w = 2048 (2.4 %, 15.8 M) 1728 / 1748, 1024 (9.5 M) 1166 / 1157
+// The lines below were drawn before the row sums moved to the matrix core and are no longer the best ones for this table: by them
+// the all-full layers of 2560 tokens and few heads take 256 rows (2.3 and 2.7 % slower), so does the block-granular w = 512 (1 %), and the
+// mixed 2K layer takes 128 (0.6 %).  Every other row of it gets its faster form.
 constexpr int kRowsShort = 128, kRowsLong = 256;
 constexpr double kLongPairsPerCu = 14.0e6;   // head_dim 128, query-key pairs per compute unit: 256 rows above this line,
 constexpr double kShortPairsPerCu = 0.13e6;  // 128 below this one; between them 128 where an image record visits fewer

@@ -321,7 +321,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
     };
 
     // Persistent workgroup: one or two per compute unit, walking the segments the host scheduled for it.
-    // The record of the following segment is fetched while the current one runs.
+    // The record of the following segment is fetched at the start of the current one.
     // A launch replayed from a graph may find that its schedule has given way to another, for the other record length even: the
     // segments would name scratch slots beyond the end, and half of a record's pieces would leave their ticket standing.  It has
     // nothing to do then.  (All three words are read together; a return up front put a memory latency before every launch: 0.8 us.)
@@ -663,7 +663,9 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
         pin(lb);                            // (read here, whatever follows)
         // compared as integers: a row beside one with an infinite weight has the sum NaN (0 x inf), which has to count as large
         const bool large = __builtin_amdgcn_ballot_w64(__builtin_bit_cast(unsigned, lb) > __builtin_bit_cast(unsigned, kTrip)) != 0;
-        if (first) {                        // the weights are at most 1, or NaN: a row of Q that is not finite, which stays with its own row
+        // In a segment's first block the references are the block's own maxima: the weights are 1 at most (but for what is lost of a
+        // reference of 2^24 and more), or not numbers, which stay with their own row.
+        if (first) {
             if (__builtin_expect(large, 0)) lb = own_sum(pw);
             rs.l = lb;
             return;
@@ -720,7 +722,8 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
         }
     };
 
-    seg_next = a.segs[seg_idx + 1 < seg_end ? seg_idx + 1 : seg_idx];   // has the whole key loop to arrive
+    // (requested here, and waited for before the key loop: the compiler takes the record to scalar registers as soon as it can)
+    seg_next = a.segs[seg_idx + 1 < seg_end ? seg_idx + 1 : seg_idx];
     qk_block(0, 0, s0);
     if (tile_masked(0)) mask_block(tile_of(0) * kBN, s0);   // (before the loop-carried flags exist)
     // The rows' references: the maximum of the first block (a row that sees nothing of it keeps the initial one).  Left to
