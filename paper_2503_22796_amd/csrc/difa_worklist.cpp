@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <limits>
 #include <new>
 #include <vector>
 
@@ -575,12 +576,12 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
     std::vector<std::vector<std::pair<int64_t, int>>> die((size_t)n_xcd);
     std::vector<int64_t> die_cost((size_t)n_xcd);
     // The dies' plans for given shares of the work (up to a common factor), and the predicted finishing times of the first, the
-    // last and all of them together, in cost units of a die of speed 1.
+    // last and all of them together, in cost units of a die of speed 1.  Given up with the first die that does not finish before `limit`.
     struct Plans {
         std::vector<DiePlan> die;
         double t_min = 0.0, t_max = 0.0, t_sum = 0.0;
     };
-    const auto plans_for = [&](const std::vector<double>& share) {
+    const auto plans_for = [&](const std::vector<double>& share, double limit) {
         std::vector<double> upto((size_t)n_xcd + 1, 0.0);  // cumulative share of the work that dies 0 .. x-1 take
         {
             double sum = 0.0;
@@ -616,6 +617,7 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
             p.t_min = x == 0 ? t : std::min(p.t_min, t);
             p.t_max = std::max(p.t_max, t);
             p.t_sum += t;
+            if (t >= limit) break;
         }
         return p;
     };
@@ -623,28 +625,31 @@ difa_status_t schedule_build(const CostModel& m, const std::vector<difa_work_ite
     // First the work is handed out in proportion to the dies' speeds; where the plans that come out of it would finish more
     // than three hundredths apart (a die whose records had to be cut carries the overhead of the cuts), the shares are corrected
     // by that and the plans made again, and kept if they are better.
-    // Where the last die is still predicted to end well behind the mean, equal shares are tried as well, and corrected in their turn.
-    // A layer with no more records than workgroups needs them most: there a share a few hundredths larger can be one record more
-    // than the die has workgroups, which takes as long as two, or has records cut to avoid that. (512 records of 1024 keys at
+    // Where the last die is still predicted to end well behind the mean, equal shares are tried as well, and corrected where they are
+    // earlier.  A layer with no more records than workgroups needs them most: there a share a few hundredths larger can be one record
+    // more than the die has workgroups, which takes as long as two, or has records cut to avoid that. (512 records of 1024 keys at
     // head_dim 128, one for each workgroup: 39 us, and 51 in those processes whose measured die speeds gave some die 65 of them; 4096
-    // keys: 122 us, 131-142 with records cut; head_dim 64 72.7 and 80.)  No way rules out another, the earliest end is kept: equal
-    // shares instead of the correction, whichever came first, end up to three times as late (6 heads, 3658 tokens).
-    const Plans first = plans_for(speed);
-    Plans best = first;
-    const auto keep_better = [&](Plans next) { if (next.t_max < best.t_max) best = std::move(next); };
-    const auto corrected = [&](const Plans& p, std::vector<double> share) {
+    // keys: 122 us, 131-142 with records cut; head_dim 64 72.7 and 80.)  They come after the correction, not in its place: that way some
+    // layers ended up to three times as late (6 heads, 3658 tokens).  First calls wait for all this, hence the limit: 139 us in
+    // the mean for such a layer on uneven dies, 132 with the correction alone.
+    Plans best = plans_for(speed, std::numeric_limits<double>::infinity());
+    const auto try_shares = [&](const std::vector<double>& share) {
+        Plans next = plans_for(share, best.t_max);
+        if (next.t_max >= best.t_max) return false;
+        best = std::move(next);
+        return true;
+    };
+    const auto try_corrected = [&](std::vector<double> share) {      // (the shares that `best` was made for)
         for (int x = 0; x < n_xcd; ++x)
-            share[(size_t)x] *= (p.t_sum / n_xcd) / ((double)p.die[(size_t)x].makespan / speed[(size_t)x]);
-        return plans_for(share);
+            share[(size_t)x] *= (best.t_sum / n_xcd) / ((double)best.die[(size_t)x].makespan / speed[(size_t)x]);
+        try_shares(share);
     };
     const auto late = [&](double by) { return best.t_max * n_xcd > (1.0 + by) * best.t_sum; };   // the last die, behind the mean
     const bool uneven = *std::max_element(speed.begin(), speed.end()) > *std::min_element(speed.begin(), speed.end());
-    if (apart(first)) keep_better(corrected(first, speed));
+    if (apart(best)) try_corrected(speed);
     if (uneven && late(recs.size() <= (size_t)n_wg ? 0.02 : 0.1)) {
         const std::vector<double> equal((size_t)n_xcd, 1.0);
-        const Plans even = plans_for(equal);
-        keep_better(even);
-        if (apart(even) && late(0.1)) keep_better(corrected(even, equal));
+        if (try_shares(equal) && apart(best) && late(0.1)) try_corrected(equal);
     }
     std::vector<DiePlan>& plans = best.die;
 
