@@ -179,7 +179,7 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
         return (const AttnArgs*)kp;
     };
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, wave_v = tid >> 6;
     // How long the workgroup runs is reported to the host, which learns from it how fast each accelerator
     // die is going (their clocks differ by a few percent under load) and shares out later work accordingly.
     // The start time waits in LDS (ctl_sm[2..3]): no register is held for it across the kernel.
@@ -211,8 +211,8 @@ __global__ __launch_bounds__(2 * BM, 2) void attn_bf16_kernel(AttnArgs a) {
     // (Products of the vector form of the wavefront's number, held from segment to segment, came to 28 bytes of scratch a lane in the
     // 256-row kernel, with a reload in each segment's first half-step that waited for every load in flight.  The scalar
     // form in the others as well: the SD3-like 512 px refresh 79.7 us instead of 79.2.)
-    const unsigned wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave = BM == kRowsLong ? (int)wave_u : tid >> 6;
+    const unsigned wave_u = __builtin_amdgcn_readfirstlane(wave_v);
+    const int wave = BM == kRowsLong ? (int)wave_u : wave_v;
     unsigned gk[NDMA], gv[NDMA];                            // per-lane byte offsets inside a tile
     // These sixteen-odd registers are derived from the lane number again at the start of every segment,
     // through a copy the compiler cannot see through.  Held for the whole kernel instead, they would be
